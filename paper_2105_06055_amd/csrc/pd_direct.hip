@@ -1,0 +1,208 @@
+// pd_direct.hip -- launches of the direct horizon sums (pd_direct.hpp),
+// compiled in parallel units: PD_INST_T = float or double, PD_DIR_PART = 0 ..
+// 4 (3D LPS, 3D bond-based and the element-wise kernels, 2D, 2D adjoint and
+// damage, nonlinear).
+#include <algorithm>
+
+#include "pd_direct.hpp"
+#include "pd_direct_api.hpp"
+
+#ifndef PD_INST_T
+#error "PD_INST_T must be defined (float or double)"
+#endif
+#ifndef PD_DIR_PART
+#error "PD_DIR_PART must be defined (0 .. 4)"
+#endif
+
+namespace pdd {
+
+using pdi::allow_lds;
+using pdi::ProfScope;
+
+// p->red[0 .. nr) = the sums of the blocks' partials
+inline pd_status finish_reduction(pd_plan p, long nblk, int nr, hipStream_t st) {
+    hipLaunchKernelGGL(k_reduce_final, dim3(1), dim3(256), 0, st, p->partials, nblk, nr, p->red, (double*)nullptr);
+    return pdh::check(hipGetLastError());
+}
+
+// ------------------------------------------------------------ 3D launches
+template <class T, class Op, class Ep, int MT>
+pd_status launch3(pd_plan p, const D3In<T>& in, double ka, const Ep& ep, const char* name, hipStream_t st) {
+    using S = Shape3<T, Op, MT>;
+    const Geo& g = p->geo;
+    D3Geo d;
+    d.b1 = g.b1; d.b2 = g.b2; d.b3 = g.b3;
+    d.ntx = (g.b1 + S::TX - 1) / S::TX;
+    d.nty = (g.b2 + S::TY - 1) / S::TY;
+    d.zc = (g.b3 + p->dir_nzc - 1) / p->dir_nzc;
+    d.nzc = (g.b3 + d.zc - 1) / d.zc;
+    Taps<T, MT> tp;
+    constexpr TapIds<MT> ids = kTapIds<MT>;
+    for (int r2 = 1; r2 <= MT * MT; ++r2) {
+        for (int pr = 1; pr <= MT * MT; ++pr)
+            if (ids.c[r2][pr] >= 0) tp.c[ids.c[r2][pr]] = T(p->dir_c[r2] * pr);
+        for (int a = 1; a <= MT; ++a)
+            if (ids.a[r2][a] >= 0) tp.a[ids.a[r2][a]] = T(ka * p->dir_a[r2] * a);
+    }
+    const long nblk = (long)d.ntx * d.nty * d.nzc;
+    if (nblk > 0x7fffffffL) return PD_EUNSUPPORTED;
+    if (Ep::NRED > 0 && nblk * Ep::NRED > p->partials_cap) return PD_EINVAL;
+    constexpr size_t lds = S::lds();
+    if (lds > (size_t)p->max_lds) return PD_EUNSUPPORTED;
+    auto kern = k_dir3<T, Op, Ep, MT, S::TX, S::TY, S::NX>;
+    allow_lds(kern, lds);
+    ProfScope ps(p, st);
+    hipLaunchKernelGGL(kern, dim3((unsigned)nblk), dim3(S::NT), lds, st, d, in, tp, ep, p->partials);
+    if (p->prof) {
+        char nm[32];
+        std::snprintf(nm, sizeof nm, "%s_m%d", name, MT);
+        ps.done(nm, ep.nbytes() * (double)g.nb);
+    }
+    if (pd_status s = pdh::check(hipGetLastError()); s != PD_OK) return s;
+    if (Ep::NRED > 0) return finish_reduction(p, nblk, Ep::NRED, st);
+    return PD_OK;
+}
+
+template <class T, class Op, class Ep>
+pd_status by_radius(pd_plan p, const D3In<T>& in, double ka, const Ep& ep, const char* name, hipStream_t st) {
+    switch (p->dir_mt) {
+        case 2: return launch3<T, Op, Ep, 2>(p, in, ka, ep, name, st);
+        case 3: return launch3<T, Op, Ep, 3>(p, in, ka, ep, name, st);
+        case 4: return launch3<T, Op, Ep, 4>(p, in, ka, ep, name, st);
+        default: return PD_EUNSUPPORTED;
+    }
+}
+
+template <class T, bool LPS, int NR>
+pd_status force3(pd_plan p, const Eval<T>& e, hipStream_t st) {
+    EpForce<T, LPS, NR> ep{};
+    ep.c = pdi::ctx<T>(p);
+    ep.mode = e.mode;
+    ep.ka = T(p->ka);
+    ep.u = e.u; ep.theta = e.theta;
+    ep.L = e.L; ep.v = e.v; ep.F = e.F; ep.b = e.b; ep.w = e.w;
+    ep.c1 = e.c1; ep.rho = e.rho; ep.dt = e.dt;
+    ep.u_next = e.u_next;
+    ep.nanflag = e.nanflag;
+    ep.vh_in = e.vh_in; ep.vh_out = e.vh_out;
+    D3In<T> in{{e.u, e.u + p->nb, e.u + 2 * p->nb, e.theta}, p->chiB};
+    if constexpr (LPS) return by_radius<T, OpB>(p, in, p->ka, ep, "dir3_lps", st);
+    else return by_radius<T, OpC>(p, in, 0.0, ep, "dir3_bb", st);
+}
+
+#if PD_DIR_PART == 0
+template <class T>
+pd_status dir3_theta(pd_plan p, const T* u, T* theta, hipStream_t st) {
+    EpTheta<T> ep{};
+    ep.c = pdi::ctx<T>(p);
+    ep.u = u;
+    ep.theta = theta;
+    D3In<T> in{{u, u + p->nb, u + 2 * p->nb, nullptr}, p->chiB};
+    return by_radius<T, OpA>(p, in, 1.0, ep, "dir3_theta", st);
+}
+template pd_status dir3_theta<PD_INST_T>(pd_plan, const PD_INST_T*, PD_INST_T*, hipStream_t);
+
+template <class T>
+pd_status dir3_lps(pd_plan p, const Eval<T>& e, hipStream_t st) {
+    if (e.mode >= 2) return force3<T, true, 1>(p, e, st);
+    if (e.energy) return force3<T, true, 4>(p, e, st);
+    return force3<T, true, 0>(p, e, st);
+}
+template pd_status dir3_lps<PD_INST_T>(pd_plan, const Eval<PD_INST_T>&, hipStream_t);
+#elif PD_DIR_PART == 1
+template <class T>
+pd_status dir3_lps(pd_plan p, const Eval<T>& e, hipStream_t st);
+
+template <class T>
+pd_status dir3_force(pd_plan p, const Eval<T>& e, hipStream_t st) {
+    if (p->kern.model == PD_LPS_LINEAR) return dir3_lps<T>(p, e, st);
+    if (e.mode >= 2) return force3<T, false, 1>(p, e, st);
+    if (e.energy) return force3<T, false, 4>(p, e, st);
+    return force3<T, false, 0>(p, e, st);
+}
+template pd_status dir3_force<PD_INST_T>(pd_plan, const Eval<PD_INST_T>&, hipStream_t);
+
+template <class T>
+pd_status dir_drift(pd_plan p, const T* u, T* u_out, const T* v, const T* F, const T* w, T dt, T c2,
+                    const uint8_t* lam, uint8_t* lam_out, const T* W, T Wc, int fail, hipStream_t st) {
+    ProfScope ps(p, st);
+    const long n = p->nb;
+    const unsigned nblk = (unsigned)std::max<long>(1, std::min<long>((n + 255) / 256, 8192L));
+    auto go = [&](auto Dc) {
+        hipLaunchKernelGGL((k_drift<T, decltype(Dc)::value>), dim3(nblk), dim3(256), 0, st, n, p->chiB, u, u_out, v, F,
+                           w, dt, c2, lam, lam_out, W, Wc, fail);
+    };
+    if (p->dim == 2) go(std::integral_constant<int, 2>{});
+    else go(std::integral_constant<int, 3>{});
+    if (p->prof)
+        ps.done("drift", (double)n * (p->dim * sizeof(T) * (w ? 5.0 : 4.0) + 1.0 +
+                                      (lam ? 2.0 + (fail ? sizeof(T) : 0) : 0.0)));
+    return pdh::check(hipGetLastError());
+}
+template pd_status dir_drift<PD_INST_T>(pd_plan, const PD_INST_T*, PD_INST_T*, const PD_INST_T*, const PD_INST_T*,
+                                        const PD_INST_T*, PD_INST_T, PD_INST_T, const uint8_t*, uint8_t*,
+                                        const PD_INST_T*, PD_INST_T, int, hipStream_t);
+
+#if PD_DIR_FIRST   // once: not per type
+// The chunk count along z: enough blocks for every CU to hold its resident
+// ones, chunks no shorter than that needs, since every chunk also sweeps up
+// to 2 MT planes of its neighbours.  Taken as the count that minimises
+// rounds * (planes swept per chunk), a round being the blocks that 256 CUs
+// hold at once.
+void dir_launch_shape(pd_plan p) {
+    const Geo& g = p->geo;
+    if (p->dim != 3 || p->kern.model == PD_BB_NONLINEAR) {
+        p->dir_mt = 0;
+        return;
+    }
+    p->dir_nzc = 1;
+    p->dir_blocks = (long)((g.b1 + 15) / 16) * ((g.b2 + 3) / 4);
+    if (p->dim != 3) return;
+    const long tiles = (long)((g.b1 + kTX3 - 1) / kTX3) * ((g.b2 + kTY3 - 1) / kTY3);
+    const long slots = 256 * kRes3;
+    double best = 0;
+    for (int nz = 1; nz <= g.b3; ++nz) {
+        const int zc = (g.b3 + nz - 1) / nz;
+        const long blocks = tiles * ((g.b3 + zc - 1) / zc);
+        const double cost = (double)((blocks + slots - 1) / slots) * (zc + (nz > 1 ? 1.2 * p->dir_mt : 0.0) + 2.0);
+        if (nz == 1 || cost < 0.98 * best) {
+            best = cost;
+            p->dir_nzc = nz;
+        }
+        if (blocks > 16 * slots) break;
+    }
+    const int zc = (g.b3 + p->dir_nzc - 1) / p->dir_nzc;
+    p->dir_blocks = tiles * ((g.b3 + zc - 1) / zc);
+}
+#endif
+#endif
+
+// Not built yet: plans of these kinds do not qualify (dir_launch_shape).
+#if PD_DIR_PART == 2
+using R = PD_INST_T;
+template <class T>
+pd_status dir2_force(pd_plan, const Eval<T>&, hipStream_t) { return PD_EUNSUPPORTED; }
+template pd_status dir2_force<R>(pd_plan, const Eval<R>&, hipStream_t);
+#elif PD_DIR_PART == 3
+using R = PD_INST_T;
+template <class T>
+pd_status dir2_adjoint(pd_plan, const T*, const T*, const T*, const T*, T*, T*, T, int, hipStream_t) {
+    return PD_EUNSUPPORTED;
+}
+template <class T>
+pd_status dir2_verlet_adjoint(pd_plan, const T*, const T*, const T*, T*, T*, T*, T*, T, T, T, T*, T*, hipStream_t) {
+    return PD_EUNSUPPORTED;
+}
+template <class T>
+pd_status dir2_damage(pd_plan, const uint8_t*, T*, hipStream_t) { return PD_EUNSUPPORTED; }
+template pd_status dir2_adjoint<R>(pd_plan, const R*, const R*, const R*, const R*, R*, R*, R, int, hipStream_t);
+template pd_status dir2_verlet_adjoint<R>(pd_plan, const R*, const R*, const R*, R*, R*, R*, R*, R, R, R, R*, R*,
+                                          hipStream_t);
+template pd_status dir2_damage<R>(pd_plan, const uint8_t*, R*, hipStream_t);
+#elif PD_DIR_PART == 4
+template <class T>
+pd_status dir_nbb(pd_plan, const T*, T*, hipStream_t) { return PD_EUNSUPPORTED; }
+template pd_status dir_nbb<PD_INST_T>(pd_plan, const PD_INST_T*, PD_INST_T*, hipStream_t);
+#endif
+
+}  // namespace pdd

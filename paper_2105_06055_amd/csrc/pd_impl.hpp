@@ -14,6 +14,7 @@
 #include <type_traits>
 #include <vector>
 
+#include "pd_direct_api.hpp"
 #include "pd_plan.hpp"
 
 using namespace pdk;
@@ -165,30 +166,6 @@ __global__ void k_fill(T* p, long n, T v) {
 
 }  // namespace pdi
 
-namespace pdk {
-
-static __global__ void k_reduce_final(const double* __restrict__ part, long nblk, int NR, double* __restrict__ out,
-                                      double* __restrict__ host) {
-    __shared__ double sm[256];
-    for (int r = 0; r < NR; ++r) {
-        double s = 0;
-        for (long b = threadIdx.x; b < nblk; b += blockDim.x) s += part[b * NR + r];
-        sm[threadIdx.x] = s;
-        __syncthreads();
-        for (int w = blockDim.x / 2; w > 0; w >>= 1) {
-            if ((int)threadIdx.x < w) sm[threadIdx.x] += sm[threadIdx.x + w];
-            __syncthreads();
-        }
-        if (threadIdx.x == 0) {
-            out[r] = sm[0];
-            if (host) host[r] = sm[0];
-        }
-        __syncthreads();
-    }
-}
-
-}  // namespace pdk
-
 namespace pdi {
 
 // ------------------------------------------------------------------ helpers
@@ -210,19 +187,6 @@ template <class T>
 inline cx<T>* SBp(pd_plan p) { return reinterpret_cast<cx<T>*>(p->SB); }
 template <class T>
 inline const cx<T>* TWp(pd_plan p) { return reinterpret_cast<const cx<T>*>(p->tw); }
-
-template <class T>
-NodeCtx<T> ctx(pd_plan p) {
-    NodeCtx<T> c;
-    c.nb = p->nb;
-    c.chiB = p->chiB;
-    c.stat = reinterpret_cast<const T*>(p->stat);
-    c.ncs = p->ncs;
-    c.stat_int = reinterpret_cast<const T*>(p->stat_int);
-    for (int q = 0; q < 10; ++q) c.sint[q] = T(q < p->ncs ? p->stat_int_h[q] : 0.0);
-    c.edge_frac = p->nb > 0 ? (double)p->n_edge / (double)p->nb : 0.0;
-    return c;
-}
 
 // Lengths with compile-time specialisations of the x and y passes (the
 // 512^3 box: 256-point complex rows along x, 512-point lines along y; the
@@ -262,35 +226,6 @@ int cols_per_block(pd_plan p, int nc_taps) {
     while (Lc > 1 && need(Lc) > (size_t)p->max_lds) Lc >>= 1;
     return Lc;
 }
-
-template <class K>
-void allow_lds(K kern, size_t bytes) {
-    if (bytes > 65536) (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-}
-
-// Records a pair of events around one launch when timing is enabled.
-struct ProfScope {
-    pd_plan p;
-    hipStream_t st;
-    hipEvent_t a = nullptr;
-    ProfScope(pd_plan p_, hipStream_t st_) : p(p_), st(st_) {
-        if (p->prof && hipEventCreate(&a) == hipSuccess) (void)hipEventRecord(a, st);
-    }
-    void done(const char* name, double bytes) {
-        if (!p->prof || !a) return;
-        hipEvent_t b;
-        if (hipEventCreate(&b) != hipSuccess) return;
-        (void)hipEventRecord(b, st);
-        ProfRec r;
-        std::snprintf(r.name, sizeof(r.name), "%s", name);
-        r.a = a;
-        r.b = b;
-        r.bytes = bytes;
-        p->prof->push_back(r);
-        a = nullptr;
-    }
-};
 
 template <class T>
 long xinv_blocks(pd_plan p) {
@@ -1151,7 +1086,7 @@ pd_status plan_alloc(pd_plan p, hipStream_t st, const uint8_t* chiB_h, const uin
         // (the fewest rows per block any x pass takes: 8 for the Verlet c2r)
         const int Lt = std::min(rows_per_block<T>(p), rows_per_block<T>(p, 8));
         long nblk = (long)((g.b2 + Lt - 1) / Lt) * g.b3;
-        p->partials_cap = std::max(nblk * 8, 4096L);
+        p->partials_cap = std::max(std::max(nblk * 8, 4096L), p->dir_blocks * 4);
         HIP_TRY(hipMalloc(&p->partials, sizeof(double) * p->partials_cap));
         HIP_TRY(hipMalloc(&p->red, sizeof(double) * 16));
         HIP_TRY(hipHostMalloc(&p->red_host, sizeof(double) * 16, hipHostMallocDefault));
@@ -1166,6 +1101,35 @@ pd_status plan_alloc(pd_plan p, hipStream_t st, const uint8_t* chiB_h, const uin
         for (hipEvent_t& e : p->lag_ev) HIP_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming));
     }
     return PD_OK;
+}
+
+// Direct horizon sums: one spacing along every axis and a stencil inside a
+// ball of 2 .. 4 (3D) or 2 .. 8 (2D) spacings (the smallest that holds it;
+// kernel values of offsets beyond the horizon are zero).  Beyond, the sums'
+// cost (the ball's volume) passes that of the transforms, and other spacings
+// take a kernel value per component and offset, more than fit in scalar
+// registers.
+inline void dir_plan(pd_plan p, const std::vector<Bond>& S) {
+    const int D = p->dim;
+    p->dir_mt = 0;
+    for (int d = 1; d < D; ++d)
+        if (p->dx[d] != p->dx[0]) return;
+    int r2max = 0;
+    for (const Bond& bd : S) r2max = std::max(r2max, bd.o[0] * bd.o[0] + bd.o[1] * bd.o[1] + bd.o[2] * bd.o[2]);
+    int mt = 2;
+    while (mt * mt < r2max) ++mt;
+    if (mt > (D == 3 ? 4 : 8)) return;
+    if (D == 2 && mt == 7) mt = 8;   // not instantiated on its own
+    const double cC = (p->kern.model == PD_LPS_LINEAR) ? 30.0 * p->mu / p->m0 : p->alpha;
+    for (int q = 0; q < 65; ++q) p->dir_c[q] = p->dir_a[q] = 0.0;
+    for (const Bond& bd : S) {
+        const int r2 = bd.o[0] * bd.o[0] + bd.o[1] * bd.o[1] + bd.o[2] * bd.o[2];
+        const double w = p->influence == 0 ? 1.0 / bd.r : 1.0;
+        p->dir_c[r2] = cC * w * p->dx[0] * p->dx[0] / (bd.r * bd.r) * p->dV;
+        p->dir_a[r2] = w * p->dx[0] * p->dV;
+    }
+    p->dir_mt = mt;
+    pdd::dir_launch_shape(p);
 }
 
 inline pd_status plan_create_impl(const pd_grid* grid, const pd_horizon* hz, const pd_kernel* kern, const pd_mask* mask,
@@ -1258,6 +1222,7 @@ inline pd_status plan_create_impl(const pd_grid* grid, const pd_horizon* hz, con
     const double lmax = symbol_lambda_max(p, S);
     p->dt_max = (lmax > 0 && kern->rho > 0) ? 2.0 / std::sqrt(lmax / kern->rho) : 0.0;
 
+    dir_plan(p, S);
     pd_status s = (dtype == PD_F32) ? plan_alloc<float>(p, st, mask ? mask->chi_B : nullptr, mask ? mask->chi_Omega : nullptr)
                                     : plan_alloc<double>(p, st, mask ? mask->chi_B : nullptr, mask ? mask->chi_Omega : nullptr);
     if (s == PD_OK)
@@ -1392,11 +1357,36 @@ pd_status run_lps(pd_plan p, const GA& gA, const FinTheta<T>& fA, const MulLPSB<
     return run_chain<T>(p, gB, mB, fB, st, 3);
 }
 
+// The two LPS stages as direct sums: theta, then the force of e.u.
+template <class T>
+pd_status lps_direct(pd_plan p, pdd::Eval<T>& e, hipStream_t st) {
+    T* theta = reinterpret_cast<T*>(p->theta);
+    PD_TRY((pdd::dir3_theta<T>(p, e.u, theta, st)));
+    e.theta = theta;
+    return pdd::dir3_force<T>(p, e, st);
+}
+
 template <class T>
 pd_status force_impl(pd_plan p, const T* u, const void* weight, T* L, T* W, hipStream_t st) {
     const int D = p->dim;
     const pd_weight_kind wk = p->kern.weight;
     if (wk != PD_WEIGHT_NONE && !weight) return PD_EINVAL;
+    if (pdd::on(p)) {
+        pdd::Eval<T> e{};
+        e.u = u;
+        e.L = L;
+        if (p->kern.model == PD_LPS_LINEAR) return W ? PD_EUNSUPPORTED : lps_direct<T>(p, e, st);
+        if (p->kern.model == PD_BB_NONLINEAR) {
+            if (pdd::nbb_on(p)) return W ? PD_EUNSUPPORTED : pdd::dir_nbb<T>(p, u, L, st);
+        } else if (D == 3) {
+            if (wk == PD_WEIGHT_NONE && !W) return pdd::dir3_force<T>(p, e, st);
+        } else if (!W || p->energy_form == PD_ENERGY_DIRECT) {
+            e.W = W;
+            if (wk == PD_WEIGHT_INTEGRITY) e.lam = reinterpret_cast<const uint8_t*>(weight);
+            if (wk == PD_WEIGHT_SCALE) e.s = reinterpret_cast<const T*>(weight);
+            return pdd::dir2_force<T>(p, e, st);
+        }
+    }
     if (p->kern.model == PD_LPS_LINEAR) {
         if (W) return PD_EUNSUPPORTED;
         // stage A: dilatation
@@ -1682,6 +1672,15 @@ inline pd_status fetch_red(pd_plan p, int n, hipStream_t st, double* dst) {
 template <class T, int MODE>
 pd_status lin_apply(pd_plan p, const T* x, T* out, const T* b, hipStream_t st) {
     const int D = p->dim;
+    if (pdd::on(p)) {
+        pdd::Eval<T> e{};
+        e.mode = MODE;
+        e.u = x;
+        e.L = out;
+        e.b = b;
+        if (p->kern.model == PD_LPS_LINEAR) return lps_direct<T>(p, e, st);
+        return D == 2 ? pdd::dir2_force<T>(p, e, st) : pdd::dir3_force<T>(p, e, st);
+    }
     if (p->kern.model == PD_LPS_LINEAR) {
         GenU<T, 3, WK_NONE, false, false, false> gA{};
         gA.c = ctx<T>(p);
@@ -1851,6 +1850,85 @@ pd_status force_impl_any(pd_plan p, const T* u, const void* weight, T* L, T* W, 
 // slot of red / red_host holding the Verlet call's non-finite flag
 constexpr int kNanSlot = 12;
 
+// The energies of one step from the reduction's sums (KE, PE, EXT,
+// |chi_O F|^2): kinetic, internal, external, shadow.
+inline pd_status verlet_energies(pd_plan p, double dt, double* energy, hipStream_t st) {
+    double r[4];
+    PD_TRY(fetch_red(p, 4, st, r));
+    const double dV = p->dV;
+    energy[0] = r[0] * dV;
+    energy[1] = r[1] * dV;
+    energy[2] = r[2] * dV;
+    energy[3] = (r[0] + r[1] + r[2]) * dV - dt * dt / (8.0 * p->kern.rho) * r[3] * dV;
+    for (int q = 0; q < 4; ++q)
+        if (!std::isfinite(energy[q])) return PD_ENUMERIC;
+    return PD_OK;
+}
+
+// End of a Verlet call: reads the non-finite flag.
+inline pd_status verlet_end(pd_plan p, double* flag, int nsteps, hipStream_t st) {
+    if (nsteps > 0) {
+        if (!p->red_host_dev)
+            HIP_TRY(hipMemcpyAsync(p->red_host + kNanSlot, flag, sizeof(double), hipMemcpyDeviceToHost, st));
+        HIP_TRY(hipStreamSynchronize(st));
+        if (p->red_host[kNanSlot] != 0.0) return PD_ENUMERIC;
+    }
+    return PD_OK;
+}
+
+// The steps of a call on the direct sums.  A step is the force stage(s) on
+// updated positions; its epilogue updates the velocities and, inside a
+// multi-step call (kdk), also makes the next step's position (and integrity)
+// update into a second buffer, since other blocks still read the current one
+// as neighbours.  The first update of a call, and every one with (v, F) kept,
+// is an element-wise pass; it writes to the buffer from which the alternation
+// ends in the caller's arrays.
+template <class T>
+pd_status verlet_direct(pd_plan p, pd_state* S, const T* b, const T* w, double dt, int nsteps, double* energy,
+                        bool kdk, double* flag, hipStream_t st) {
+    const T rho = T(p->kern.rho);
+    const T c1 = T(dt) / (T(2) * rho), c2 = T(dt) * T(dt) / (T(2) * rho);
+    T* ub[2] = {reinterpret_cast<T*>(S->u), reinterpret_cast<T*>(p->vtmp)};
+    uint8_t* lb[2] = {S->lambda, reinterpret_cast<uint8_t*>(p->vtmp2)};
+    const bool lam = p->kern.weight == PD_WEIGHT_INTEGRITY;
+    const int fail = (lam && S->W && p->Wc > 0) ? 1 : 0;
+    T* W = lam ? reinterpret_cast<T*>(S->W) : nullptr;
+    int cur = 0;   // buffer of the current positions
+    for (int k = 0; k < nsteps; ++k) {
+        const int vh_in = (kdk && k > 0) ? 1 : 0, vh_out = (kdk && k + 1 < nsteps) ? 1 : 0;
+        if (!vh_in) {
+            const int to = kdk ? ((nsteps - 1) & 1) : 0;
+            PD_TRY((pdd::dir_drift<T>(p, ub[0], ub[to], reinterpret_cast<const T*>(S->v),
+                                      reinterpret_cast<const T*>(S->F), w, T(dt), c2, lam ? lb[0] : nullptr,
+                                      lam ? lb[to] : nullptr, W, T(p->Wc), fail, st)));
+            cur = to;
+        }
+        pdd::Eval<T> e{};
+        e.mode = 1;
+        e.u = ub[cur];
+        e.lam = lam ? lb[cur] : nullptr;
+        e.s = p->kern.weight == PD_WEIGHT_SCALE ? reinterpret_cast<const T*>(S->s) : nullptr;
+        e.W = W;
+        e.v = reinterpret_cast<T*>(S->v);
+        e.F = reinterpret_cast<T*>(S->F);
+        e.b = b; e.w = w;
+        e.c1 = c1; e.dt = T(dt); e.rho = rho;
+        e.vh_in = vh_in; e.vh_out = vh_out;
+        e.energy = energy ? 1 : 0;
+        e.u_next = ub[1 - cur];
+        e.lam_next = lam ? lb[1 - cur] : nullptr;
+        e.Wc = T(p->Wc); e.fail = fail;
+        e.nanflag = flag;
+        if (p->kern.model == PD_LPS_LINEAR) PD_TRY((lps_direct<T>(p, e, st)));
+        else if (p->dim == 3) PD_TRY((pdd::dir3_force<T>(p, e, st)));
+        else PD_TRY((pdd::dir2_force<T>(p, e, st)));
+        if (vh_out) cur = 1 - cur;
+        if (energy) PD_TRY(verlet_energies(p, dt, energy + 4 * k, st));
+        S->step += 1;
+    }
+    return PD_OK;
+}
+
 template <class T>
 pd_status verlet_impl(pd_plan p, pd_state* S, const T* b, const T* w, double dt, int nsteps, double* energy,
                       hipStream_t st) {
@@ -1894,34 +1972,25 @@ pd_status verlet_impl(pd_plan p, pd_state* S, const T* b, const T* w, double dt,
     // Steps with energy output, and calls with PD_STATE_EXACT_STEPS, keep
     // (v, F) throughout.
     const bool kdk = !energy && !(S->flags & PD_STATE_EXACT_STEPS);
+    if (pdd::on(p) && (p->dim == 2 || p->kern.weight == PD_WEIGHT_NONE) &&
+        !(S->W && p->energy_form != PD_ENERGY_DIRECT)) {
+        PD_TRY((verlet_direct<T>(p, S, b, w, dt, nsteps, energy, kdk, flag, st)));
+        return verlet_end(p, flag, nsteps, st);
+    }
     int drifted = 0;   // u already holds this step's updated positions
     for (int k = 0; k < nsteps; ++k) {
         const int vh_in = (kdk && k > 0) ? 1 : 0, vh_out = (kdk && k + 1 < nsteps) ? 1 : 0;
         int drift = 0;
         if (energy) {
             PD_TRY((verlet_one<T, true>(p, S, b, w, T(dt), flag, 0, 0, 0, &drift, st)));
-            double r[4];
-            PD_TRY(fetch_red(p, 4, st, r));
-            const double dV = p->dV;
-            energy[4 * k + 0] = r[0] * dV;
-            energy[4 * k + 1] = r[1] * dV;
-            energy[4 * k + 2] = r[2] * dV;
-            energy[4 * k + 3] = (r[0] + r[1] + r[2]) * dV - dt * dt / (8.0 * p->kern.rho) * r[3] * dV;
-            for (int q = 0; q < 4; ++q)
-                if (!std::isfinite(energy[4 * k + q])) return PD_ENUMERIC;
+            PD_TRY(verlet_energies(p, dt, energy + 4 * k, st));
         } else {
             PD_TRY((verlet_one<T, false>(p, S, b, w, T(dt), flag, vh_in, vh_out, drifted, &drift, st)));
         }
         drifted = drift;
         S->step += 1;
     }
-    if (nsteps > 0) {
-        if (!p->red_host_dev)
-            HIP_TRY(hipMemcpyAsync(p->red_host + kNanSlot, flag, sizeof(double), hipMemcpyDeviceToHost, st));
-        HIP_TRY(hipStreamSynchronize(st));
-        if (p->red_host[kNanSlot] != 0.0) return PD_ENUMERIC;
-    }
-    return PD_OK;
+    return verlet_end(p, flag, nsteps, st);
 }
 
 // -------------------------------------------------------------- force
@@ -1942,6 +2011,9 @@ pd_status adjoint_impl(pd_plan p, const T* u, const T* u2, const void* weight, c
     if (p->kern.weight != PD_WEIGHT_SCALE || p->kern.model != PD_BB_LINEAR) return PD_EUNSUPPORTED;
     if (!weight) return PD_EINVAL;
     if (p->dim != 2) return PD_EUNSUPPORTED;
+    if (pdd::on(p))
+        return pdd::dir2_adjoint<T>(p, u, u2, reinterpret_cast<const T*>(weight), g, ubar, wbar, wscale, accumulate,
+                                    st);
     auto go = [&](auto Dc) -> pd_status {
         constexpr int DD = decltype(Dc)::value;
         GenAdj<T, DD, WK_SCALE> gg{};
@@ -1970,6 +2042,10 @@ pd_status verlet_adjoint_impl(pd_plan p, const T* un, const T* unp1, const T* s,
     T* Lut = ut + n;
     const T rho = T(p->kern.rho), c1 = T(dt / (2.0 * p->kern.rho)), c2 = T(dt * dt / (2.0 * p->kern.rho));
     (void)rho;
+    if (pdd::on(p) && p->dim == 2) {
+        if (sb && p->kern.weight != PD_WEIGHT_SCALE) return PD_EUNSUPPORTED;
+        return pdd::dir2_verlet_adjoint<T>(p, un, unp1, s, ub, vb, sb, bb, c1, c2, T(dt), ut, La, st);
+    }
     const void* wgt = (p->kern.weight == PD_WEIGHT_SCALE) ? (const void*)s : nullptr;
     hipLaunchKernelGGL(k_mask_copy<T>, dim3(ew_blocks(n)), dim3(EW_THREADS), 0, st, a, (const T*)vb, p->chiO, n);
     HIP_TRY(hipGetLastError());
@@ -2292,6 +2368,7 @@ template <class T>
 pd_status damage_impl(pd_plan p, const uint8_t* lam, T* d, hipStream_t st) {
     if (p->kern.model != PD_BB_LINEAR || p->kern.weight != PD_WEIGHT_INTEGRITY) return PD_EUNSUPPORTED;
     if (!lam || !d) return PD_EINVAL;
+    if (pdd::on(p) && p->dim == 2) return pdd::dir2_damage<T>(p, lam, d, st);
     auto go = [&](auto Dc) -> pd_status {
         constexpr int DD = decltype(Dc)::value;
         GenPhi<T> gg{};

@@ -1481,6 +1481,23 @@ __global__ void __launch_bounds__(512) k_xinv(Geo g, F fin, const cx<T>* __restr
 // (one block, fixed order tree), also written to host[r] when host is not
 // null (the device address of a pinned host buffer).
 static __global__ void k_reduce_final(const double* __restrict__ part, long nblk, int NR, double* __restrict__ out,
-                                      double* __restrict__ host);
+                                      double* __restrict__ host) {
+    __shared__ double sm[256];
+    for (int r = 0; r < NR; ++r) {
+        double s = 0;
+        for (long b = threadIdx.x; b < nblk; b += blockDim.x) s += part[b * NR + r];
+        sm[threadIdx.x] = s;
+        __syncthreads();
+        for (int w = blockDim.x / 2; w > 0; w >>= 1) {
+            if ((int)threadIdx.x < w) sm[threadIdx.x] += sm[threadIdx.x + w];
+            __syncthreads();
+        }
+        if (threadIdx.x == 0) {
+            out[r] = sm[0];
+            if (host) host[r] = sm[0];
+        }
+        __syncthreads();
+    }
+}
 
 }  // namespace pdk

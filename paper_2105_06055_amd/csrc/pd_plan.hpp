@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <cstdio>
 #include <vector>
 
 #include "pd_fcbm.h"
@@ -77,6 +78,13 @@ struct pd_plan_s {
     int emt;                     // largest |o_x|, |o_y| of the stencil (halo of the energy kernel)
     int energy_form;             // 0: W by direct bond sums, 1: by the convolution form (test mode)
     double* kval_dev;            // kernel values [ns][ncs]
+    // direct horizon sums (pd_direct.hpp): radius of the ball of offsets in
+    // spacings (0: the plan does not qualify) and, by r^2 in spacings, the
+    // radial factors c and a with C_ij(o) = c[r^2] o_i o_j, a_i(o) = a[r^2] o_i
+    int dir_mt;
+    double dir_c[65], dir_a[65];
+    int dir_nzc;                 // 3D: chunks along z
+    long dir_blocks;             // most blocks of a launch (reduction partials)
     size_t bytes;
     std::vector<ProfRec>* prof;  // non-null while pass timing is enabled
     pd_plan_s* sub32;            // FP32 operator for the mixed solve
@@ -88,3 +96,49 @@ namespace pdh {
 pd_status check(hipError_t e);
 
 }  // namespace pdh
+
+namespace pdi {
+
+template <class T>
+pdk::NodeCtx<T> ctx(pd_plan p) {
+    pdk::NodeCtx<T> c;
+    c.nb = p->nb;
+    c.chiB = p->chiB;
+    c.stat = reinterpret_cast<const T*>(p->stat);
+    c.ncs = p->ncs;
+    c.stat_int = reinterpret_cast<const T*>(p->stat_int);
+    for (int q = 0; q < 10; ++q) c.sint[q] = T(q < p->ncs ? p->stat_int_h[q] : 0.0);
+    c.edge_frac = p->nb > 0 ? (double)p->n_edge / (double)p->nb : 0.0;
+    return c;
+}
+
+template <class K>
+void allow_lds(K kern, size_t bytes) {
+    if (bytes > 65536) (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+}
+
+// Records a pair of events around one launch when timing is enabled.
+struct ProfScope {
+    pd_plan p;
+    hipStream_t st;
+    hipEvent_t a = nullptr;
+    ProfScope(pd_plan p_, hipStream_t st_) : p(p_), st(st_) {
+        if (p->prof && hipEventCreate(&a) == hipSuccess) (void)hipEventRecord(a, st);
+    }
+    void done(const char* name, double bytes) {
+        if (!p->prof || !a) return;
+        hipEvent_t b;
+        if (hipEventCreate(&b) != hipSuccess) return;
+        (void)hipEventRecord(b, st);
+        ProfRec r;
+        std::snprintf(r.name, sizeof(r.name), "%s", name);
+        r.a = a;
+        r.b = b;
+        r.bytes = bytes;
+        p->prof->push_back(r);
+        a = nullptr;
+    }
+};
+
+}  // namespace pdi
