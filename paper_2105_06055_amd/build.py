@@ -19,7 +19,7 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libpdfcbm.so")
-HEADERS = ["pd_fft.hpp", "pd_ops.hpp", "pd_passes.hpp", "pd_plan.hpp", "pd_direct_api.hpp", "pd_direct.hpp",
+HEADERS = ["pd_fft.hpp", "pd_ops.hpp", "pd_passes.hpp", "pd_plan.hpp", "pd_direct_api.hpp", "pd_direct.hpp", "pd_direct2.hpp",
            "pd_impl.hpp"]
 UNITS = [("pd_fcbm.hip", [])] + [
     ("pd_inst.hip", ["-DPD_INST_T=%s" % t, "-DPD_INST_PART=%d" % part, "-DPD_INST_F32=%d" % (t == "float")])

@@ -4,7 +4,7 @@
 // damage, nonlinear).
 #include <algorithm>
 
-#include "pd_direct.hpp"
+#include "pd_direct2.hpp"
 #include "pd_direct_api.hpp"
 
 #ifndef PD_INST_T
@@ -151,7 +151,7 @@ template pd_status dir_drift<PD_INST_T>(pd_plan, const PD_INST_T*, PD_INST_T*, c
 // hold at once.
 void dir_launch_shape(pd_plan p) {
     const Geo& g = p->geo;
-    if (p->dim != 3 || p->kern.model == PD_BB_NONLINEAR) {
+    if (p->kern.model == PD_BB_NONLINEAR) {
         p->dir_mt = 0;
         return;
     }
@@ -177,29 +177,163 @@ void dir_launch_shape(pd_plan p) {
 #endif
 #endif
 
-// Not built yet: plans of these kinds do not qualify (dir_launch_shape).
+// ------------------------------------------------------------ 2D launches
+template <class T, int M>
+Radial<T, M> radial(pd_plan p, double scale = 1.0) {
+    Radial<T, M> r;
+    for (int q = 0; q <= M * M; ++q) r.k[q] = T(p->dir_c[q] * scale);
+    return r;
+}
+inline D2Geo geo2(pd_plan p) { return D2Geo{p->geo.b1, p->geo.b2, p->nb}; }
+template <class TL>
+dim3 grid2(pd_plan p) {
+    return dim3((unsigned)((p->geo.b1 + TL::TX - 1) / TL::TX), (unsigned)((p->geo.b2 + TL::TY - 1) / TL::TY));
+}
+// The radii compiled for the plate kernels; f(integral_constant<M>).
+template <class F>
+pd_status by_radius2(pd_plan p, F&& f) {
+    switch (p->dir_mt) {
+        case 2: return f(std::integral_constant<int, 2>{});
+        case 3: return f(std::integral_constant<int, 3>{});
+        case 4: return f(std::integral_constant<int, 4>{});
+        case 5: return f(std::integral_constant<int, 5>{});
+        case 6: return f(std::integral_constant<int, 6>{});
+        case 8: return f(std::integral_constant<int, 8>{});
+        default: return PD_EUNSUPPORTED;
+    }
+}
+// Small plates (fewer nodes than the large tile gives every CU one block of)
+// take a small tile with one node per thread: more blocks, shorter chains.
+template <class T, int M> using Large = Tile2<T, M, 64, 8, 2>;
+template <class T, int M> using Small = Tile2<T, M, 32, 4, 1>;
+inline bool small_plate(pd_plan p) { return p->nb < 256L * 512; }
+
 #if PD_DIR_PART == 2
-using R = PD_INST_T;
+template <class T, int M, class TL, bool WE, int NR>
+pd_status run2(pd_plan p, const Args2<T>& A, hipStream_t st) {
+    const dim3 grid = grid2<TL>(p);
+    const long nblk = (long)grid.x * grid.y;
+    if (NR > 0 && nblk * NR > p->partials_cap) return PD_EINVAL;
+    constexpr size_t lds = 3 * TL::PL * sizeof(T);
+    if (lds > (size_t)p->max_lds) return PD_EUNSUPPORTED;
+    auto kern = k_dir2<T, M, TL, WE, NR>;
+    allow_lds(kern, lds);
+    ProfScope ps(p, st);
+    hipLaunchKernelGGL(kern, grid, dim3(TL::NT), lds, st, geo2(p), radial<T, M>(p), A, p->partials);
+    if (p->prof) {
+        char nm[32];
+        std::snprintf(nm, sizeof nm, "dir2_m%d", M);
+        const double t = sizeof(T);
+        double by = 2 * t + 1 + (A.wt.lam ? 1 : 0) + (A.wt.s ? t : 0) + (A.Wo ? t : 0) + (A.b ? 2 * t : 0);
+        if (A.mode == 1) by += 2 * t * (3 + (A.vh_in ? 0 : 1)) + (A.vh_out && A.lam_next ? 1 : 0);
+        else by += 2 * t;
+        ps.done(nm, by * (double)p->nb);
+    }
+    if (pd_status s = pdh::check(hipGetLastError()); s != PD_OK) return s;
+    return NR > 0 ? finish_reduction(p, nblk, NR, st) : PD_OK;
+}
+
 template <class T>
-pd_status dir2_force(pd_plan, const Eval<T>&, hipStream_t) { return PD_EUNSUPPORTED; }
-template pd_status dir2_force<R>(pd_plan, const Eval<R>&, hipStream_t);
+pd_status dir2_force(pd_plan p, const Eval<T>& e, hipStream_t st) {
+    Args2<T> A{};
+    A.mode = e.mode;
+    A.wt = Weight<T>{p->chiB, e.lam, e.s};
+    A.u = e.u;
+    A.L = e.L; A.Wo = e.W;
+    A.v = e.v; A.F = e.F; A.b = e.b; A.w = e.w;
+    A.c1 = e.c1; A.dt = e.dt; A.rho = e.rho;
+    A.vh_in = e.vh_in; A.vh_out = e.vh_out;
+    A.u_next = e.u_next; A.lam_next = e.lam_next;
+    A.Wc = e.Wc; A.fail = e.fail;
+    A.nanflag = e.nanflag;
+    return by_radius2(p, [&](auto mc) -> pd_status {
+        constexpr int M = decltype(mc)::value;
+        auto go = [&](auto we, auto nr) -> pd_status {
+            constexpr bool WE = decltype(we)::value;
+            constexpr int NR = decltype(nr)::value;
+            return small_plate(p) ? run2<T, M, Small<T, M>, WE, NR>(p, A, st)
+                                  : run2<T, M, Large<T, M>, WE, NR>(p, A, st);
+        };
+        if (e.mode >= 2) return go(std::false_type{}, std::integral_constant<int, 1>{});
+        if (e.energy) return go(std::true_type{}, std::integral_constant<int, 4>{});
+        if (e.W) return go(std::true_type{}, std::integral_constant<int, 0>{});
+        return go(std::false_type{}, std::integral_constant<int, 0>{});
+    });
+}
+template pd_status dir2_force<PD_INST_T>(pd_plan, const Eval<PD_INST_T>&, hipStream_t);
 #elif PD_DIR_PART == 3
+template <class T>
+pd_status run_adj(pd_plan p, const ArgsAdj<T>& A, hipStream_t st) {
+    return by_radius2(p, [&](auto mc) -> pd_status {
+        constexpr int M = decltype(mc)::value;
+        auto go = [&](auto tl) -> pd_status {
+            using TL = decltype(tl);
+            constexpr size_t lds = 5 * TL::PL * sizeof(T);
+            if (lds > (size_t)p->max_lds) return PD_EUNSUPPORTED;
+            auto kern = k_adj2<T, M, TL>;
+            allow_lds(kern, lds);
+            ProfScope ps(p, st);
+            hipLaunchKernelGGL(kern, grid2<TL>(p), dim3(TL::NT), lds, st, geo2(p), radial<T, M>(p), A);
+            if (p->prof) {
+                char nm[32];
+                std::snprintf(nm, sizeof nm, "adj2_m%d", M);
+                const double t = sizeof(T);
+                double by = 2 * t + 1 + (A.wt.s ? t : 0) + (A.wbar ? 2 * t + (A.u2 ? 2 * t : 0) + (A.acc ? 2 : 1) * t : 0);
+                by += A.stage == 0 ? (A.ubar ? 2 * t : 0) : (A.stage == 1 ? 6 * t : 8 * t + (A.bb ? 4 * t : 0));
+                ps.done(nm, by * (double)p->nb);
+            }
+            return pdh::check(hipGetLastError());
+        };
+        return small_plate(p) ? go(Small<T, M>{}) : go(Large<T, M>{});
+    });
+}
+
+template <class T>
+pd_status dir2_adjoint(pd_plan p, const T* u, const T* u2, const T* s, const T* g, T* ubar, T* wbar, T wscale,
+                       int acc, hipStream_t st) {
+    ArgsAdj<T> A{};
+    A.wt = Weight<T>{p->chiB, nullptr, s};
+    A.u = u; A.u2 = u2; A.g = g;
+    A.ubar = ubar; A.wbar = wbar; A.wscale = wscale; A.acc = acc;
+    return run_adj<T>(p, A, st);
+}
+
+template <class T>
+pd_status dir2_verlet_adjoint(pd_plan p, const T* un, const T* unp1, const T* s, T* ub, T* vb, T* sb, T* bb, T c1,
+                              T c2, T dt, T* ut, T* tmp, hipStream_t st) {
+    ArgsAdj<T> A{};
+    A.wt = Weight<T>{p->chiB, nullptr, p->kern.weight == PD_WEIGHT_SCALE ? s : nullptr};
+    A.u = un; A.u2 = unp1; A.g = vb;
+    A.wbar = sb; A.wscale = c1; A.acc = 1;
+    A.stage = 1;
+    A.ub = ub; A.vb = vb; A.bb = bb; A.ut = ut; A.tmp = tmp;
+    A.c1 = c1; A.c2 = c2; A.dt = dt;
+    if (pd_status r = run_adj<T>(p, A, st); r != PD_OK) return r;
+    A.u2 = nullptr;
+    A.g = ut;
+    A.wscale = c2;
+    A.stage = 2;
+    return run_adj<T>(p, A, st);
+}
+
+template <class T>
+pd_status dir2_damage(pd_plan p, const uint8_t* lam, T* d, hipStream_t st) {
+    uint64_t member = 0;
+    for (int q = 1; q <= 64; ++q)
+        if (p->dir_c[q] != 0.0) member |= 1ull << (q - 1);
+    ProfScope ps(p, st);
+    hipLaunchKernelGGL((k_damage2<T>), dim3((unsigned)((p->geo.b1 + 63) / 64), (unsigned)((p->geo.b2 + 3) / 4)),
+                       dim3(256), 0, st, geo2(p), p->dir_mt, member, pdi::ctx<T>(p), p->beta_comp, lam, d);
+    if (p->prof) ps.done("damage2", (double)p->nb * (2.0 + sizeof(T)));
+    return pdh::check(hipGetLastError());
+}
 using R = PD_INST_T;
-template <class T>
-pd_status dir2_adjoint(pd_plan, const T*, const T*, const T*, const T*, T*, T*, T, int, hipStream_t) {
-    return PD_EUNSUPPORTED;
-}
-template <class T>
-pd_status dir2_verlet_adjoint(pd_plan, const T*, const T*, const T*, T*, T*, T*, T*, T, T, T, T*, T*, hipStream_t) {
-    return PD_EUNSUPPORTED;
-}
-template <class T>
-pd_status dir2_damage(pd_plan, const uint8_t*, T*, hipStream_t) { return PD_EUNSUPPORTED; }
 template pd_status dir2_adjoint<R>(pd_plan, const R*, const R*, const R*, const R*, R*, R*, R, int, hipStream_t);
 template pd_status dir2_verlet_adjoint<R>(pd_plan, const R*, const R*, const R*, R*, R*, R*, R*, R, R, R, R*, R*,
                                           hipStream_t);
 template pd_status dir2_damage<R>(pd_plan, const uint8_t*, R*, hipStream_t);
 #elif PD_DIR_PART == 4
+// Not built yet: nonlinear plans do not qualify (dir_launch_shape).
 template <class T>
 pd_status dir_nbb(pd_plan, const T*, T*, hipStream_t) { return PD_EUNSUPPORTED; }
 template pd_status dir_nbb<PD_INST_T>(pd_plan, const PD_INST_T*, PD_INST_T*, hipStream_t);

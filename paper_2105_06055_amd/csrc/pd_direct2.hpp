@@ -1,0 +1,469 @@
+// pd_direct2.hpp -- direct bond sums per node (internal): the 2D bond-based
+// plate (force, energy density, Verlet, adjoint, damage count).
+//
+// The bond weights change per node (integrity, micromodulus scale), so
+// nothing folds; a node sums its bonds one by one in terms of the differences eta = u(x + o) - u(x):
+//   s = phi(x + o) c(r) (o . eta),   L += s o,   W += s (o . eta) / 2.
+// A block loads a tile of nodes and its halo of M nodes once into LDS; each
+// thread takes NX consecutive nodes and reads each row of the horizon disc as
+// a window of NX + 2R values.  Offsets and the order of the bonds are
+// compile-time constants, the radial factors are kernel arguments in scalar
+// registers.  A plate of 400,000 nodes (48 bonds) stays in the caches, so one
+// launch per step replaces four passes over padded spectra; the sums are
+// bound by the vector ALU (~9 instructions a bond).  Measured against the
+// transform passes: 20 FP32 fracture steps of the 1000 x 400 plate 1465 -> 284
+// us, 20 FP64 steps of a 601 x 241 plate at six spacings 3948 -> 378 us, 10
+// steps forward and backward on the 512 x 512 plate 3239 -> 961 us, the force
+// of a 64 x 64 plate 22.4 -> 9.5 us.
+#pragma once
+
+#include "pd_direct.hpp"
+
+namespace pdd {
+
+struct D2Geo {
+    int b1, b2;
+    long nb;
+};
+template <class T, int M>
+struct Radial {
+    T k[M * M + 1];
+};
+
+// nodal weight phi = chi_B [lam] [s]
+template <class T>
+struct Weight {
+    const uint8_t* chiB;
+    const uint8_t* lam;
+    const T* s;
+    __device__ __forceinline__ T at(uint32_t i) const {
+        bool on = chiB[i] != 0;
+        if (lam) on = on && lam[i] != 0;
+        T ph = on ? T(1) : T(0);
+        if (s) ph *= s[i];
+        return ph;
+    }
+};
+
+template <class T, int N>
+struct Node {
+    T v[N];
+};
+
+// Tile of TX x TY nodes, NX per thread; rows of W values, HY rows.
+template <class T, int M, int TX_, int TY_, int NX_>
+struct Tile2 {
+    static constexpr int TX = TX_, TY = TY_, NX = NX_, NT = TX / NX * TY;
+    static constexpr int H = (M + NX - 1) / NX * NX, W = TX + 2 * H, HY = TY + 2 * M, FX = TX + 2 * M;
+    static constexpr int PL = W * HY;
+    // The tile with its halo: get(in, i) loads the values of box node i (0 and
+    // unused where !in), put(slot, value) stores them; all loads of a thread
+    // are issued before its first store.
+    static constexpr int NE = (FX * HY + NT - 1) / NT;
+    template <class G, class P>
+    __device__ __forceinline__ static void fill(const D2Geo& g, int x0, int y0, G&& get, P&& put) {
+        decltype(get(false, 0u)) v[NE];
+#pragma unroll
+        for (int k = 0; k < NE; ++k) {
+            const int e = threadIdx.x + NT * k, r = e / FX, cx = e - r * FX, gx = x0 - M + cx, gy = y0 - M + r;
+            const bool in = e < FX * HY && gx >= 0 && gx < g.b1 && gy >= 0 && gy < g.b2;
+            v[k] = get(in, in ? (uint32_t)(gy * g.b1 + gx) : 0u);
+        }
+#pragma unroll
+        for (int k = 0; k < NE; ++k) {
+            const int e = threadIdx.x + NT * k, r = e / FX, cx = e - r * FX;
+            if (e < FX * HY) put(r * W + cx + (H - M), v[k]);
+        }
+    }
+    // row window: values at columns -RA .. NX - 1 + RA around the thread's
+    // nodes (RA: R rounded up to NX)
+    template <int R>
+    __device__ __forceinline__ static void row(lds_ptr<T> p, T (&w)[NX + 2 * ((R + NX - 1) / NX * NX)]) {
+        constexpr int RA = (R + NX - 1) / NX * NX;
+#pragma unroll
+        for (int k = 0; k < (NX + 2 * RA) / NX; ++k) {
+            const typename Vec<T, NX>::A a = *(lds_ptr<typename Vec<T, NX>::A>)(p - RA + k * NX);
+#pragma unroll
+            for (int n = 0; n < NX; ++n) w[k * NX + n] = a[n];
+        }
+    }
+};
+
+// ------------------------------------------------------------ force, 2D
+template <class T>
+struct Args2 {
+    int mode;
+    Weight<T> wt;
+    const T* u;
+    T* L; T* Wo;
+    T* v; T* F; const T* b; const T* w;
+    T c1, dt, rho;
+    int vh_in, vh_out;
+    T* u_next; uint8_t* lam_next;
+    T Wc;
+    int fail;
+    double* nanflag;
+};
+
+// WE: with the energy density.  NR: reductions (0, 1: modes 2 and 3, 4: the
+// energy sums of mode 1).  Modes as pdd::Eval.
+template <class T, int M, class TL, bool WE, int NR>
+__global__ void __launch_bounds__(TL::NT) k_dir2(D2Geo g, Radial<T, M> tp, Args2<T> A, double* __restrict__ partials) {
+    constexpr int NX = TL::NX, W = TL::W, PL = TL::PL;
+    extern __shared__ __align__(16) unsigned char smem_raw[];   // 3 PL values
+    lds_ptr<T> s0 = as_lds(reinterpret_cast<T*>(smem_raw)), s1 = s0 + PL, sp = s0 + 2 * PL;
+    const int x0 = blockIdx.x * TL::TX, y0 = blockIdx.y * TL::TY;
+    TL::fill(
+        g, x0, y0,
+        [&](bool in, uint32_t i) {
+            const T a = A.u[i], b = A.u[g.nb + i], ph = A.wt.at(i);
+            return Node<T, 3>{{in ? a : T(0), in ? b : T(0), in ? ph : T(0)}};
+        },
+        [&](int slot, const Node<T, 3>& q) {
+            s0[slot] = q.v[0];
+            s1[slot] = q.v[1];
+            sp[slot] = q.v[2];
+        });
+    const int tx = threadIdx.x % (TL::TX / NX), ty = threadIdx.x / (TL::TX / NX);
+    const int x = x0 + tx * NX, y = y0 + ty;
+    const int nx = y < g.b2 ? min(max(g.b1 - x, 0), NX) : 0;
+    const uint32_t off = nx > 0 ? (uint32_t)(y * g.b1 + x) : 0u;
+    // the node's other fields, in flight during the fill and the sums
+    uint8_t cb[NX];
+    T vv[2][NX], FF[2][NX], bb[2][NX];
+    ldn<NX>(A.wt.chiB, 0, off, nx, cb);
+#pragma unroll
+    for (int d = 0; d < 2; ++d) {
+        if (NR != 1 && A.mode == 1) {
+            ldn<NX>(A.v + d * g.nb, 0, off, nx, vv[d]);
+            if (!A.vh_in) ldn<NX>(A.F + d * g.nb, 0, off, nx, FF[d]);
+        }
+        if (A.b) ldn<NX>(A.b + d * g.nb, 0, off, nx, bb[d]);
+        else {
+#pragma unroll
+            for (int n = 0; n < NX; ++n) bb[d][n] = T(0);
+        }
+    }
+    __syncthreads();
+    const int c = (ty + M) * W + tx * NX + TL::H;
+    T u0[NX], u1[NX], ph[NX], a0[NX], a1[NX], en[NX];
+#pragma unroll
+    for (int n = 0; n < NX; ++n) {
+        u0[n] = s0[c + n];
+        u1[n] = s1[c + n];
+        ph[n] = sp[c + n];
+        a0[n] = a1[n] = en[n] = T(0);
+    }
+    each<0, 2 * M + 1>([&](auto rc) {
+        constexpr int b = decltype(rc)::value - M, R = isqrt(M * M - b * b), RA = (R + NX - 1) / NX * NX;
+        pin(a0);
+        pin(a1);
+        if constexpr (WE) pin(en);
+        row_fence();
+        T w0[NX + 2 * RA], w1[NX + 2 * RA], wp[NX + 2 * RA];
+        TL::template row<R>(s0 + c + b * W, w0);
+        TL::template row<R>(s1 + c + b * W, w1);
+        TL::template row<R>(sp + c + b * W, wp);
+        T rs[NX];   // sum of s along the row (it enters L_y times b)
+#pragma unroll
+        for (int n = 0; n < NX; ++n) rs[n] = T(0);
+        each<0, 2 * R + 1>([&](auto ac) {
+            constexpr int a = decltype(ac)::value - R, r2 = a * a + b * b;
+            if constexpr (r2 > 0) {
+#pragma unroll
+                for (int n = 0; n < NX; ++n) {
+                    T e = T(0);
+                    if constexpr (a != 0) e += T(a) * (w0[RA + n + a] - u0[n]);
+                    if constexpr (b != 0) e += T(b) * (w1[RA + n + a] - u1[n]);
+                    const T s = tp.k[r2] * wp[RA + n + a] * e;
+                    if constexpr (a != 0) a0[n] += T(a) * s;
+                    if constexpr (b != 0) rs[n] += s;
+                    if constexpr (WE) en[n] += s * e;
+                }
+            }
+        });
+        if constexpr (b != 0) {
+#pragma unroll
+            for (int n = 0; n < NX; ++n) a1[n] += T(b) * rs[n];
+        }
+    });
+    double red[NR > 0 ? NR : 1];
+#pragma unroll
+    for (int r = 0; r < (NR > 0 ? NR : 1); ++r) red[r] = 0.0;
+    if (nx > 0) {
+        T L[2][NX], Wn[NX];
+#pragma unroll
+        for (int n = 0; n < NX; ++n) {
+            L[0][n] = ph[n] * a0[n];
+            L[1][n] = ph[n] * a1[n];
+            Wn[n] = T(0.5) * ph[n] * en[n];
+        }
+        if constexpr (WE) {
+            if (A.Wo) stn<NX>(A.Wo, 0, off, nx, Wn);
+        }
+        if constexpr (NR == 1) {
+#pragma unroll
+            for (int d = 0; d < 2; ++d) {
+                T out[NX];
+#pragma unroll
+                for (int n = 0; n < NX; ++n) {
+                    const bool o = omega_bit(cb[n], d) && n < nx;
+                    if (A.mode == 2) {
+                        out[n] = o ? -L[d][n] : T(0);
+                        red[0] += o ? double(d ? u1[n] : u0[n]) * double(out[n]) : 0.0;
+                    } else {
+                        out[n] = o ? L[d][n] + bb[d][n] : T(0);
+                        red[0] += double(out[n]) * double(out[n]);
+                    }
+                }
+                stn<NX>(A.L + d * g.nb, 0, off, nx, out);
+            }
+        } else if (A.mode == 0) {
+            stn<NX>(A.L, 0, off, nx, L[0]);
+            stn<NX>(A.L + g.nb, 0, off, nx, L[1]);
+        } else {
+#pragma unroll
+            for (int d = 0; d < 2; ++d) {
+                T vo[NX], fo[NX];
+#pragma unroll
+                for (int n = 0; n < NX; ++n) {
+                    const bool o = omega_bit(cb[n], d);
+                    const T Fn = L[d][n] + bb[d][n];
+                    const T Fo = A.vh_in ? T(0) : FF[d][n];
+                    const T vf = vv[d][n] + A.c1 * (Fo + Fn);
+                    const T vn = o ? vf : T(0);
+                    if (n < nx) flag_nonfinite(A.nanflag, Fn, vn);
+                    fo[n] = Fn;
+                    vo[n] = A.vh_out ? (o ? vn + A.c1 * Fn : T(0)) : vn;
+                    if constexpr (NR == 4) {
+                        if (n < nx) {
+                            const double un = double(d ? u1[n] : u0[n]);
+                            red[0] += 0.5 * double(A.rho) * double(vn) * double(vn);
+                            red[1] += -0.5 * un * double(L[d][n]);
+                            red[2] += -double(bb[d][n]) * un;
+                            red[3] += o ? double(Fn) * double(Fn) : 0.0;
+                        }
+                    }
+                }
+                stn<NX>(A.v + d * g.nb, 0, off, nx, vo);
+                if (!A.vh_out) stn<NX>(A.F + d * g.nb, 0, off, nx, fo);
+                else {
+                    T wk[NX];
+                    if (A.w) ldn<NX>(A.w + d * g.nb, 0, off, nx, wk);
+#pragma unroll
+                    for (int n = 0; n < NX; ++n)
+                        wk[n] = omega_bit(cb[n], d) ? (d ? u1[n] : u0[n]) + A.dt * vo[n] : (A.w ? wk[n] : T(0));
+                    stn<NX>(A.u_next + d * g.nb, 0, off, nx, wk);
+                }
+            }
+            if (A.vh_out && A.lam_next) {
+                uint8_t ln[NX];
+                ldn<NX>(A.wt.lam, 0, off, nx, ln);
+                if constexpr (WE) {
+                    if (A.fail) {
+#pragma unroll
+                        for (int n = 0; n < NX; ++n) ln[n] = (ln[n] != 0 && Wn[n] <= A.Wc) ? 1 : 0;
+                    }
+                }
+                stn<NX>(A.lam_next, 0, off, nx, ln);
+            }
+        }
+    }
+    if constexpr (NR > 0) {
+        __syncthreads();
+        block_reduce_store<NR>(red, partials + ((long)blockIdx.y * gridDim.x + blockIdx.x) * NR,
+                               reinterpret_cast<double*>(smem_raw));
+    }
+}
+
+// ------------------------------------------------------------ adjoint, 2D
+// u_bar = phi sum phi' c (o . gamma) o, gamma = g' - g;
+// w_bar = -chi_B sum phi' c (o . eta)(o . gamma)  (the derivative of <g, L>
+// with respect to the weight at this node, from its bonds as either end).
+template <class T>
+struct ArgsAdj {
+    Weight<T> wt;
+    const T* u; const T* u2;      // primal field u (+ u2)
+    const T* g;                   // cotangent; masked by chi_Omega in stage 1
+    T* ubar;
+    T* wbar;
+    T wscale;
+    int acc;
+    // reverse Verlet step: stage 0 a plain adjoint; stage 1: ut = chi_O (ub +
+    // c1 L a), tmp = c1 L a + ut; stage 2: ub = tmp + c2 L ut, vb = a + dt ut,
+    // bb += c2 ut + 2 c1 a with a = chi_O vb
+    int stage;
+    T* ub; T* vb; T* bb; T* ut; T* tmp;
+    T c1, c2, dt;
+};
+template <class T, int M, class TL>
+__global__ void __launch_bounds__(TL::NT) k_adj2(D2Geo g, Radial<T, M> tp, ArgsAdj<T> A) {
+    constexpr int NX = TL::NX, W = TL::W, PL = TL::PL;
+    extern __shared__ __align__(16) unsigned char smem_raw[];   // 5 PL values
+    lds_ptr<T> s0 = as_lds(reinterpret_cast<T*>(smem_raw)), s1 = s0 + PL, q0 = s0 + 2 * PL, q1 = s0 + 3 * PL, sp = s0 + 4 * PL;
+    const int x0 = blockIdx.x * TL::TX, y0 = blockIdx.y * TL::TY;
+    TL::fill(
+        g, x0, y0,
+        [&](bool in, uint32_t i) {
+        T a = T(0), b = T(0);
+        if (A.wbar) {
+            a = A.u[i];
+            b = A.u[g.nb + i];
+            if (A.u2) {
+                a += A.u2[i];
+                b += A.u2[g.nb + i];
+            }
+        }
+        T ga = A.g[i], gb = A.g[g.nb + i];
+        if (A.stage == 1) {
+            const uint8_t cbi = A.wt.chiB[i];
+            ga = omega_bit(cbi, 0) ? ga : T(0);
+            gb = omega_bit(cbi, 1) ? gb : T(0);
+        }
+        const T ph = A.wt.at(i);
+        return Node<T, 5>{{in ? a : T(0), in ? b : T(0), in ? ga : T(0), in ? gb : T(0), in ? ph : T(0)}};
+        },
+        [&](int slot, const Node<T, 5>& q) {
+            s0[slot] = q.v[0];
+            s1[slot] = q.v[1];
+            q0[slot] = q.v[2];
+            q1[slot] = q.v[3];
+            sp[slot] = q.v[4];
+        });
+    __syncthreads();
+    const int tx = threadIdx.x % (TL::TX / NX), ty = threadIdx.x / (TL::TX / NX);
+    const int x = x0 + tx * NX, y = y0 + ty;
+    const int nx = y < g.b2 ? min(max(g.b1 - x, 0), NX) : 0;
+    const uint32_t off = nx > 0 ? (uint32_t)(y * g.b1 + x) : 0u;
+    const int c = (ty + M) * W + tx * NX + TL::H;
+    T u0[NX], u1[NX], g0[NX], g1[NX], a0[NX], a1[NX], pb[NX];
+#pragma unroll
+    for (int n = 0; n < NX; ++n) {
+        u0[n] = s0[c + n]; u1[n] = s1[c + n];
+        g0[n] = q0[c + n]; g1[n] = q1[c + n];
+        a0[n] = a1[n] = pb[n] = T(0);
+    }
+    each<0, 2 * M + 1>([&](auto rc) {
+        constexpr int b = decltype(rc)::value - M, R = isqrt(M * M - b * b), RA = (R + NX - 1) / NX * NX;
+        pin(a0);
+        pin(a1);
+        pin(pb);
+        row_fence();
+        T w0[NX + 2 * RA], w1[NX + 2 * RA], h0[NX + 2 * RA], h1[NX + 2 * RA], wp[NX + 2 * RA];
+        TL::template row<R>(s0 + c + b * W, w0);
+        TL::template row<R>(s1 + c + b * W, w1);
+        TL::template row<R>(q0 + c + b * W, h0);
+        TL::template row<R>(q1 + c + b * W, h1);
+        TL::template row<R>(sp + c + b * W, wp);
+        T rs[NX];
+#pragma unroll
+        for (int n = 0; n < NX; ++n) rs[n] = T(0);
+        each<0, 2 * R + 1>([&](auto ac) {
+            constexpr int a = decltype(ac)::value - R, r2 = a * a + b * b;
+            if constexpr (r2 > 0) {
+#pragma unroll
+                for (int n = 0; n < NX; ++n) {
+                    T e = T(0), f = T(0);
+                    if constexpr (a != 0) {
+                        e += T(a) * (w0[RA + n + a] - u0[n]);
+                        f += T(a) * (h0[RA + n + a] - g0[n]);
+                    }
+                    if constexpr (b != 0) {
+                        e += T(b) * (w1[RA + n + a] - u1[n]);
+                        f += T(b) * (h1[RA + n + a] - g1[n]);
+                    }
+                    const T s = tp.k[r2] * wp[RA + n + a] * f;
+                    if constexpr (a != 0) a0[n] += T(a) * s;
+                    if constexpr (b != 0) rs[n] += s;
+                    pb[n] += s * e;
+                }
+            }
+        });
+        if constexpr (b != 0) {
+#pragma unroll
+            for (int n = 0; n < NX; ++n) a1[n] += T(b) * rs[n];
+        }
+    });
+    if (nx <= 0) return;
+    uint8_t cb[NX];
+    ldn<NX>(A.wt.chiB, 0, off, nx, cb);
+#pragma unroll
+    for (int d = 0; d < 2; ++d) {
+        T Lg[NX];
+#pragma unroll
+        for (int n = 0; n < NX; ++n) Lg[n] = sp[c + n] * (d ? a1[n] : a0[n]);
+        if (A.stage == 0) {
+            if (A.ubar) stn<NX>(A.ubar + d * g.nb, 0, off, nx, Lg);
+        } else if (A.stage == 1) {
+            T ub[NX], ut[NX];
+            ldn<NX>(A.ub + d * g.nb, 0, off, nx, ub);
+#pragma unroll
+            for (int n = 0; n < NX; ++n) {
+                ut[n] = omega_bit(cb[n], d) ? ub[n] + A.c1 * Lg[n] : T(0);
+                ub[n] = A.c1 * Lg[n] + ut[n];
+            }
+            stn<NX>(A.ut + d * g.nb, 0, off, nx, ut);
+            stn<NX>(A.tmp + d * g.nb, 0, off, nx, ub);
+        } else {
+            T tp_[NX], vb[NX], bb[NX];
+            ldn<NX>(A.tmp + d * g.nb, 0, off, nx, tp_);
+            ldn<NX>(A.vb + d * g.nb, 0, off, nx, vb);
+            if (A.bb) ldn<NX>(A.bb + d * g.nb, 0, off, nx, bb);
+#pragma unroll
+            for (int n = 0; n < NX; ++n) {
+                const T a = omega_bit(cb[n], d) ? vb[n] : T(0), ut = d ? g1[n] : g0[n];
+                tp_[n] += A.c2 * Lg[n];
+                vb[n] = a + A.dt * ut;
+                if (A.bb) bb[n] += A.c2 * ut + T(2) * A.c1 * a;
+            }
+            stn<NX>(A.ub + d * g.nb, 0, off, nx, tp_);
+            stn<NX>(A.vb + d * g.nb, 0, off, nx, vb);
+            if (A.bb) stn<NX>(A.bb + d * g.nb, 0, off, nx, bb);
+        }
+    }
+    if (A.wbar) {
+        T wb[NX];
+        if (A.acc) ldn<NX>(A.wbar, 0, off, nx, wb);
+#pragma unroll
+        for (int n = 0; n < NX; ++n) {
+            const T add = cb[n] ? -A.wscale * pb[n] : T(0);
+            wb[n] = A.acc ? wb[n] + add : add;
+        }
+        stn<NX>(A.wbar, 0, off, nx, wb);
+    }
+}
+
+// ------------------------------------------------------------ damage count
+// cnt = number of intact partners within the horizon, itself included,
+// d = 1 - phi cnt / beta on the body.  member: bit r^2 - 1 set when offsets
+// of that length belong to the horizon.
+template <class T>
+__global__ void __launch_bounds__(256) k_damage2(D2Geo g, int M, uint64_t member, NodeCtx<T> c, int beta_comp,
+                                                 const uint8_t* __restrict__ lam, T* __restrict__ d) {
+    __shared__ uint8_t sm[(64 + 16) * (4 + 16)];
+    const int FX = 64 + 2 * M, HY = 4 + 2 * M;
+    const int x0 = blockIdx.x * 64, y0 = blockIdx.y * 4;
+    for (int e = threadIdx.x; e < FX * HY; e += 256) {
+        const int r = e / FX, cx = e - r * FX, gx = x0 - M + cx, gy = y0 - M + r;
+        const bool in = gx >= 0 && gx < g.b1 && gy >= 0 && gy < g.b2;
+        const long i = in ? (long)gy * g.b1 + gx : 0;
+        sm[e] = (in && c.chiB[i] && lam[i]) ? 1 : 0;
+    }
+    __syncthreads();
+    const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6, x = x0 + tx, y = y0 + ty;
+    if (x >= g.b1 || y >= g.b2) return;
+    const uint32_t i = (uint32_t)(y * g.b1 + x);
+    const uint8_t cb = c.chiB[i];
+    int cnt = 0;
+    for (int b = -M; b <= M; ++b)
+        for (int a = -M; a <= M; ++a) {
+            const int r2 = a * a + b * b;
+            if (r2 > 0 && r2 <= 64 && ((member >> (r2 - 1)) & 1)) cnt += sm[(ty + M + b) * FX + tx + M + a];
+        }
+    const int phi = sm[(ty + M) * FX + tx + M];
+    cnt += phi;
+    const long beta = (long)rint(c.st(beta_comp, Nd{0, i}, cb)) + (cb ? 1 : 0);
+    d[i] = cb ? T(1.0 - double((long)phi * cnt) / double(beta > 0 ? beta : 1)) : T(0);
+}
+
+}  // namespace pdd
