@@ -151,10 +151,6 @@ template pd_status dir_drift<PD_INST_T>(pd_plan, const PD_INST_T*, PD_INST_T*, c
 // hold at once.
 void dir_launch_shape(pd_plan p) {
     const Geo& g = p->geo;
-    if (p->kern.model == PD_BB_NONLINEAR) {
-        p->dir_mt = 0;
-        return;
-    }
     p->dir_nzc = 1;
     p->dir_blocks = (long)((g.b1 + 15) / 16) * ((g.b2 + 3) / 4);
     if (p->dim != 3) return;
@@ -333,9 +329,47 @@ template pd_status dir2_verlet_adjoint<R>(pd_plan, const R*, const R*, const R*,
                                           hipStream_t);
 template pd_status dir2_damage<R>(pd_plan, const uint8_t*, R*, hipStream_t);
 #elif PD_DIR_PART == 4
-// Not built yet: nonlinear plans do not qualify (dir_launch_shape).
 template <class T>
-pd_status dir_nbb(pd_plan, const T*, T*, hipStream_t) { return PD_EUNSUPPORTED; }
+pd_status dir_nbb(pd_plan p, const T* u, T* L, hipStream_t st) {
+    const Geo& g = p->geo;
+    ProfScope ps(p, st);
+    pd_status s = PD_EUNSUPPORTED;
+    const double inv = 1.0 / (p->dx[0] * p->dx[0]);   // c per bond, not per o_i o_j
+    if (p->dim == 2) {
+        s = by_radius2(p, [&](auto mc) -> pd_status {
+            constexpr int M = decltype(mc)::value;
+            auto go = [&](auto tl) -> pd_status {
+                using TL = decltype(tl);
+                constexpr size_t lds = 3 * TL::PL * sizeof(T);
+                if (lds > (size_t)p->max_lds) return PD_EUNSUPPORTED;
+                auto kern = k_nbb2<T, M, TL>;
+                allow_lds(kern, lds);
+                hipLaunchKernelGGL(kern, grid2<TL>(p), dim3(TL::NT), lds, st, geo2(p), radial<T, M>(p, inv), T(p->dx[0]),
+                                   p->chiB, u, L);
+                return pdh::check(hipGetLastError());
+            };
+            return small_plate(p) ? go(Small<T, M>{}) : go(Large<T, M>{});
+        });
+    } else {
+        auto go = [&](auto mc) -> pd_status {
+            constexpr int M = decltype(mc)::value;
+            using TL = Tile3;
+            constexpr size_t lds = sizeof(T) * 4 * (TL::TX + 2 * ((M + TL::NX - 1) / TL::NX * TL::NX)) *
+                                   (TL::TY + 2 * M) * (TL::TZ + 2 * M);
+            if (lds > (size_t)p->max_lds) return PD_EUNSUPPORTED;
+            auto kern = k_nbb3<T, M>;
+            allow_lds(kern, lds);
+            dim3 grid((g.b1 + TL::TX - 1) / TL::TX, (g.b2 + TL::TY - 1) / TL::TY, (g.b3 + TL::TZ - 1) / TL::TZ);
+            hipLaunchKernelGGL(kern, grid, dim3(TL::NT), lds, st, g.b1, g.b2, g.b3, radial<T, M>(p, inv), T(p->dx[0]),
+                               p->chiB, u, L);
+            return pdh::check(hipGetLastError());
+        };
+        if (p->dir_mt == 2) s = go(std::integral_constant<int, 2>{});
+        else if (p->dir_mt == 3) s = go(std::integral_constant<int, 3>{});
+    }
+    if (p->prof) ps.done(p->dim == 2 ? "nbb2" : "nbb3", (double)p->nb * (2.0 * p->dim * sizeof(T) + 1.0));
+    return s;
+}
 template pd_status dir_nbb<PD_INST_T>(pd_plan, const PD_INST_T*, PD_INST_T*, hipStream_t);
 #endif
 

@@ -1,8 +1,10 @@
 // pd_direct2.hpp -- direct bond sums per node (internal): the 2D bond-based
-// plate (force, energy density, Verlet, adjoint, damage count).
+// plate (force, energy density, Verlet, adjoint, damage count) and the
+// nonlinear bond-based model in 2D and 3D.
 //
-// The bond weights change per node (integrity, micromodulus scale), so
-// nothing folds; a node sums its bonds one by one in terms of the differences eta = u(x + o) - u(x):
+// Where the bond weights change per node (integrity, micromodulus scale), or
+// the bond force is not linear, nothing folds; a node sums its bonds one by
+// one in terms of the differences eta = u(x + o) - u(x):
 //   s = phi(x + o) c(r) (o . eta),   L += s o,   W += s (o . eta) / 2.
 // A block loads a tile of nodes and its halo of M nodes once into LDS; each
 // thread takes NX consecutive nodes and reads each row of the horizon disc as
@@ -464,6 +466,208 @@ __global__ void __launch_bounds__(256) k_damage2(D2Geo g, int M, uint64_t member
     cnt += phi;
     const long beta = (long)rint(c.st(beta_comp, Nd{0, i}, cb)) + (cb ? 1 : 0);
     d[i] = cb ? T(1.0 - double((long)phi * cnt) / double(beta > 0 ? beta : 1)) : T(0);
+}
+
+// ------------------------------------------------------------ nonlinear
+// f = c (2 xi . eta + eta . eta)(xi + eta) / 2 per bond, xi = dx o.
+template <class T, int M, class TL>
+__global__ void __launch_bounds__(TL::NT) k_nbb2(D2Geo g, Radial<T, M> tp, T dx, const uint8_t* __restrict__ chiB,
+                                                 const T* __restrict__ u, T* __restrict__ L) {
+    constexpr int NX = TL::NX, W = TL::W, PL = TL::PL;
+    extern __shared__ __align__(16) unsigned char smem_raw[];   // 3 PL values
+    lds_ptr<T> s0 = as_lds(reinterpret_cast<T*>(smem_raw)), s1 = s0 + PL, sp = s0 + 2 * PL;
+    const int x0 = blockIdx.x * TL::TX, y0 = blockIdx.y * TL::TY;
+    TL::fill(
+        g, x0, y0,
+        [&](bool in, uint32_t i) {
+            const T a = u[i], b = u[g.nb + i], ph = chiB[i] ? T(1) : T(0);
+            return Node<T, 3>{{in ? a : T(0), in ? b : T(0), in ? ph : T(0)}};
+        },
+        [&](int slot, const Node<T, 3>& q) {
+            s0[slot] = q.v[0];
+            s1[slot] = q.v[1];
+            sp[slot] = q.v[2];
+        });
+    __syncthreads();
+    const int tx = threadIdx.x % (TL::TX / NX), ty = threadIdx.x / (TL::TX / NX);
+    const int x = x0 + tx * NX, y = y0 + ty;
+    const int nx = y < g.b2 ? min(max(g.b1 - x, 0), NX) : 0;
+    const uint32_t off = nx > 0 ? (uint32_t)(y * g.b1 + x) : 0u;
+    const int c = (ty + M) * W + tx * NX + TL::H;
+    const T dx2 = T(2) * dx;
+    T u0[NX], u1[NX], o0[NX], o1[NX], e0[NX], e1[NX];
+#pragma unroll
+    for (int n = 0; n < NX; ++n) {
+        u0[n] = s0[c + n]; u1[n] = s1[c + n];
+        o0[n] = o1[n] = e0[n] = e1[n] = T(0);
+    }
+    each<0, 2 * M + 1>([&](auto rc) {
+        constexpr int b = decltype(rc)::value - M, R = isqrt(M * M - b * b), RA = (R + NX - 1) / NX * NX;
+        pin(o0);
+        pin(o1);
+        pin(e0);
+        pin(e1);
+        row_fence();
+        T w0[NX + 2 * RA], w1[NX + 2 * RA], wp[NX + 2 * RA];
+        TL::template row<R>(s0 + c + b * W, w0);
+        TL::template row<R>(s1 + c + b * W, w1);
+        TL::template row<R>(sp + c + b * W, wp);
+        each<0, 2 * R + 1>([&](auto ac) {
+            constexpr int a = decltype(ac)::value - R, r2 = a * a + b * b;
+            if constexpr (r2 > 0) {
+#pragma unroll
+                for (int n = 0; n < NX; ++n) {
+                    const T h0 = w0[RA + n + a] - u0[n], h1 = w1[RA + n + a] - u1[n];
+                    const T e = T(a) * h0 + T(b) * h1;
+                    const T s = tp.k[r2] * wp[RA + n + a] * (dx2 * e + h0 * h0 + h1 * h1);
+                    o0[n] += T(a) * s;
+                    o1[n] += T(b) * s;
+                    e0[n] += s * h0;
+                    e1[n] += s * h1;
+                }
+            }
+        });
+    });
+    if (nx <= 0) return;
+    T out[2][NX];
+#pragma unroll
+    for (int n = 0; n < NX; ++n) {
+        const T ph = T(0.5) * sp[c + n];
+        out[0][n] = ph * (dx * o0[n] + e0[n]);
+        out[1][n] = ph * (dx * o1[n] + e1[n]);
+    }
+    stn<NX>(L, 0, off, nx, out[0]);
+    stn<NX>(L + g.nb, 0, off, nx, out[1]);
+}
+
+// 3D: a block takes 16 x 8 x 8 nodes, two per thread along x, with a halo of
+// M nodes on every side in LDS (u and chi: 75 KB in FP32, 150 KB in FP64 at M
+// = 3), which keeps eight waves on a CU in either type; the 4.6 halo loads
+// per node are small beside the ~2000 vector instructions of 122 bonds.
+// Measured on the 128^3 block: FP32 420 -> 96 us against the 13-field chain of
+// the (y, z) pass.
+struct Tile3 {
+    static constexpr int TX = 16, TY = 8, TZ = 8, NX = 2, NT = TX / NX * TY * TZ;
+};
+template <class T, int M>
+__global__ void __launch_bounds__(Tile3::NT) k_nbb3(int b1, int b2, int b3, Radial<T, M> tp, T dx,
+                                                    const uint8_t* __restrict__ chiB, const T* __restrict__ u,
+                                                    T* __restrict__ L) {
+    using TL = Tile3;
+    using VA = typename Vec<T, TL::NX>::A;
+    constexpr int NX = TL::NX, H = (M + NX - 1) / NX * NX, W = TL::TX + 2 * H, HY = TL::TY + 2 * M;
+    constexpr int HZ = TL::TZ + 2 * M, FX = TL::TX + 2 * M, PL = W * HY, VOL = PL * HZ;
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    lds_ptr<T> sm = as_lds(reinterpret_cast<T*>(smem_raw));
+    const int x0 = blockIdx.x * TL::TX, y0 = blockIdx.y * TL::TY, z0 = blockIdx.z * TL::TZ;
+    const long nb = (long)b1 * b2 * b3;
+    constexpr int NE = (FX * HY * HZ + TL::NT - 1) / TL::NT;
+    Node<T, 4> pre[NE];
+#pragma unroll
+    for (int k = 0; k < NE; ++k) {
+        const int e = threadIdx.x + TL::NT * k, cx = e % FX, t = e / FX, ry = t % HY, rz = t / HY;
+        const int gx = x0 - M + cx, gy = y0 - M + ry, gz = z0 - M + rz;
+        const bool in = rz < HZ && gx >= 0 && gx < b1 && gy >= 0 && gy < b2 && gz >= 0 && gz < b3;
+        const long i = in ? ((long)gz * b2 + gy) * b1 + gx : 0;
+        const T a0 = u[i], a1 = u[nb + i], a2 = u[2 * nb + i], ph = chiB[i] ? T(1) : T(0);
+        pre[k] = Node<T, 4>{{in ? a0 : T(0), in ? a1 : T(0), in ? a2 : T(0), in ? ph : T(0)}};
+    }
+#pragma unroll
+    for (int k = 0; k < NE; ++k) {
+        const int e = threadIdx.x + TL::NT * k, cx = e % FX, t = e / FX, ry = t % HY, rz = t / HY;
+        const int slot = rz * PL + ry * W + cx + (H - M);
+        if (rz < HZ) {
+#pragma unroll
+            for (int f = 0; f < 4; ++f) sm[f * VOL + slot] = pre[k].v[f];
+        }
+    }
+    __syncthreads();
+    // eight lanes cover a row of 16 nodes; the row bits are swapped so that
+    // the two rows of a 16-lane group are two apart (rows of 24 values: half
+    // the banks each)
+    const int tx = threadIdx.x & 7, t8 = (threadIdx.x >> 3) & 7, tz = threadIdx.x >> 6;
+    const int ty = ((t8 & 1) << 1) | ((t8 >> 1) & 1) | (t8 & 4);
+    const int x = x0 + tx * NX, y = y0 + ty, z = z0 + tz;
+    const int nx = (y < b2 && z < b3) ? min(max(b1 - x, 0), NX) : 0;
+    const int c = (tz + M) * PL + (ty + M) * W + tx * NX + H;
+    const T dx2 = T(2) * dx;
+    T uc[3][NX], so[3][NX], se[3][NX];
+#pragma unroll
+    for (int d = 0; d < 3; ++d)
+#pragma unroll
+        for (int n = 0; n < NX; ++n) {
+            uc[d][n] = sm[d * VOL + c + n];
+            so[d][n] = se[d][n] = T(0);
+        }
+    each<0, 2 * M + 1>([&](auto zc) {
+        constexpr int cz = decltype(zc)::value - M;
+        T zs[NX];   // sum of s over the plane
+#pragma unroll
+        for (int n = 0; n < NX; ++n) zs[n] = T(0);
+        each<0, 2 * M + 1>([&](auto rc) {
+            constexpr int b = decltype(rc)::value - M, R2 = M * M - b * b - cz * cz;
+            if constexpr (R2 >= 0) {
+                constexpr int R = isqrt(R2), RA = (R + NX - 1) / NX * NX, WN = NX + 2 * RA;
+                pin(zs);
+#pragma unroll
+                for (int d = 0; d < 3; ++d) {
+                    if (d < 2) pin(so[d]);
+                    pin(se[d]);
+                }
+                row_fence();
+                T w[4][WN];
+#pragma unroll
+                for (int f = 0; f < 4; ++f)
+#pragma unroll
+                    for (int k = 0; k < WN / NX; ++k) {
+                        const VA a = *(lds_ptr<VA>)(sm + f * VOL + c + cz * PL + b * W - RA + k * NX);
+#pragma unroll
+                        for (int n = 0; n < NX; ++n) w[f][k * NX + n] = a[n];
+                    }
+                T rs[NX];   // sum of s along the row
+#pragma unroll
+                for (int n = 0; n < NX; ++n) rs[n] = T(0);
+                each<0, 2 * R + 1>([&](auto ac) {
+                    constexpr int a = decltype(ac)::value - R, r2 = a * a + b * b + cz * cz;
+                    if constexpr (r2 > 0) {
+#pragma unroll
+                        for (int n = 0; n < NX; ++n) {
+                            T h[3];
+#pragma unroll
+                            for (int d = 0; d < 3; ++d) h[d] = w[d][RA + n + a] - uc[d][n];
+                            T e = T(0);
+                            if constexpr (a != 0) e += T(a) * h[0];
+                            if constexpr (b != 0) e += T(b) * h[1];
+                            if constexpr (cz != 0) e += T(cz) * h[2];
+                            const T s = tp.k[r2] * w[3][RA + n + a] * (dx2 * e + h[0] * h[0] + h[1] * h[1] + h[2] * h[2]);
+                            if constexpr (a != 0) so[0][n] += T(a) * s;
+                            rs[n] += s;
+#pragma unroll
+                            for (int d = 0; d < 3; ++d) se[d][n] += s * h[d];
+                        }
+                    }
+                });
+#pragma unroll
+                for (int n = 0; n < NX; ++n) {
+                    if constexpr (b != 0) so[1][n] += T(b) * rs[n];
+                    zs[n] += rs[n];
+                }
+            }
+        });
+        if constexpr (cz != 0) {
+#pragma unroll
+            for (int n = 0; n < NX; ++n) so[2][n] += T(cz) * zs[n];
+        }
+    });
+    if (nx <= 0) return;
+    const uint32_t off = (uint32_t)(y * b1 + x);
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        T out[NX];
+#pragma unroll
+        for (int n = 0; n < NX; ++n) out[n] = T(0.5) * sm[3 * VOL + c + n] * (dx * so[d][n] + se[d][n]);
+        stn<NX>(L + d * nb + (long)z * b1 * b2, 0, off, nx, out);
+    }
 }
 
 }  // namespace pdd
