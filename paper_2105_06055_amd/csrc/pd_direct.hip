@@ -30,13 +30,17 @@ template <class T, class Op, class Ep, int MT>
 pd_status launch3(pd_plan p, const D3In<T>& in, double ka, const Ep& ep, const char* name, hipStream_t st) {
     using S = Shape3<T, Op, MT>;
     const Geo& g = p->geo;
-    D3Geo d;
+    D3Args<T, Ep, MT> a{};
+    D3Geo& d = a.g;
     d.b1 = g.b1; d.b2 = g.b2; d.b3 = g.b3;
     d.ntx = (g.b1 + S::TX - 1) / S::TX;
     d.nty = (g.b2 + S::TY - 1) / S::TY;
-    d.zc = (g.b3 + p->dir_nzc - 1) / p->dir_nzc;
+    d.zc = chunk3(g, MT, S::TX, S::TY, S::RES);
     d.nzc = (g.b3 + d.zc - 1) / d.zc;
-    Taps<T, MT> tp;
+    a.in = in;
+    a.partials = p->partials;
+    a.ep = ep;
+    Taps<T, MT>& tp = a.tp;
     constexpr TapIds<MT> ids = kTapIds<MT>;
     for (int r2 = 1; r2 <= MT * MT; ++r2) {
         for (int pr = 1; pr <= MT * MT; ++pr)
@@ -52,7 +56,7 @@ pd_status launch3(pd_plan p, const D3In<T>& in, double ka, const Ep& ep, const c
     auto kern = k_dir3<T, Op, Ep, MT, S::TX, S::TY, S::NX>;
     allow_lds(kern, lds);
     ProfScope ps(p, st);
-    hipLaunchKernelGGL(kern, dim3((unsigned)nblk), dim3(S::NT), lds, st, d, in, tp, ep, p->partials);
+    hipLaunchKernelGGL(kern, dim3((unsigned)nblk), dim3(S::NT), lds, st, a);
     if (p->prof) {
         char nm[32];
         std::snprintf(nm, sizeof nm, "%s_m%d", name, MT);
@@ -144,31 +148,12 @@ template pd_status dir_drift<PD_INST_T>(pd_plan, const PD_INST_T*, PD_INST_T*, c
                                         const PD_INST_T*, PD_INST_T, int, hipStream_t);
 
 #if PD_DIR_FIRST   // once: not per type
-// The chunk count along z: enough blocks for every CU to hold its resident
-// ones, chunks no shorter than that needs, since every chunk also sweeps up
-// to 2 MT planes of its neighbours.  Taken as the count that minimises
-// rounds * (planes swept per chunk), a round being the blocks that 256 CUs
-// hold at once.
+// Most blocks of a launch with a reduction: plate tiles of 32 x 4 nodes, or
+// four rounds of three resident blocks per CU and one more of tiles (chunk3).
 void dir_launch_shape(pd_plan p) {
     const Geo& g = p->geo;
-    p->dir_nzc = 1;
-    p->dir_blocks = (long)((g.b1 + 15) / 16) * ((g.b2 + 3) / 4);
-    if (p->dim != 3) return;
-    const long tiles = (long)((g.b1 + kTX3 - 1) / kTX3) * ((g.b2 + kTY3 - 1) / kTY3);
-    const long slots = 256 * kRes3;
-    double best = 0;
-    for (int nz = 1; nz <= g.b3; ++nz) {
-        const int zc = (g.b3 + nz - 1) / nz;
-        const long blocks = tiles * ((g.b3 + zc - 1) / zc);
-        const double cost = (double)((blocks + slots - 1) / slots) * (zc + (nz > 1 ? 1.2 * p->dir_mt : 0.0) + 2.0);
-        if (nz == 1 || cost < 0.98 * best) {
-            best = cost;
-            p->dir_nzc = nz;
-        }
-        if (blocks > 16 * slots) break;
-    }
-    const int zc = (g.b3 + p->dir_nzc - 1) / p->dir_nzc;
-    p->dir_blocks = tiles * ((g.b3 + zc - 1) / zc);
+    const long tiles = (long)((g.b1 + 31) / 32) * ((g.b2 + 3) / 4);
+    p->dir_blocks = p->dim == 2 ? tiles : std::max(4L * 256 * 4, tiles) + tiles;
 }
 #endif
 #endif

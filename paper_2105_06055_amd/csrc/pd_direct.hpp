@@ -149,6 +149,22 @@ __host__ __device__ constexpr bool takes(int MT, int O, int pz, int c) {
     }
     return false;
 }
+// Whether (J, b, a) is the first of the sweep's order (inputs, then rows, then
+// columns) whose term goes to the plane sum of output O, z-parity pz, offset
+// c > 0: it starts the sum.
+template <class Op>
+__host__ __device__ constexpr bool starts(int MT, int O, int pz, int c, int J, int b, int a) {
+    for (int j = 0; j <= J; ++j) {
+        const Term t = Op::term(O, j);
+        if (t.i < 0 || t_par(t, 2) != pz) continue;
+        for (int bb = 0; bb <= MT; ++bb)
+            for (int aa = 0; aa <= MT; ++aa) {
+                if (j == J && (bb > b || (bb == b && aa >= a))) continue;
+                if (t_nonzero(t, MT, aa, bb, c)) return false;
+            }
+    }
+    return true;
+}
 // whether input J has a nonzero term with x/y parities (px, py) at (a, b)
 template <class Op>
 __host__ __device__ constexpr bool uses(int MT, int J, int px, int py, int a, int b) {
@@ -198,6 +214,117 @@ __device__ __forceinline__ void stn(T* p, long base, uint32_t off, int n, const 
     }
 }
 
+// ------------------------------------------------------------ plane accesses
+// A field's plane as a buffer: the base and the plane's size sit in scalar
+// registers, an access takes one 32-bit offset per thread, and an offset
+// beyond the plane (kOut) reads zero and writes nothing, which stands for the
+// nodes outside the body box without a branch or a select.
+constexpr uint32_t kOut = 0x40000000u;
+template <class T>
+struct Plane {
+#if defined(__HIP_DEVICE_COMPILE__)
+    __amdgpu_buffer_rsrc_t r;
+    __device__ __forceinline__ Plane(const T* p, long base, long nodes)
+        : r(__builtin_amdgcn_make_buffer_rsrc((void*)(p + base), 0, (int)(nodes * (long)sizeof(T)), 0x00020000)) {}
+    __device__ __forceinline__ T ld(uint32_t off) const {
+        if constexpr (sizeof(T) == 1) return T(__builtin_amdgcn_raw_buffer_load_b8(r, off, 0, 0));
+        else if constexpr (sizeof(T) == 4) return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
+        else return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0));
+    }
+    __device__ __forceinline__ void st(uint32_t off, T v) const {
+        if constexpr (sizeof(T) == 4) __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), r, off, 0, 0);
+        else __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, off, 0, 0);
+    }
+    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    // NX values at byte offset off; with tail the values from n on do not
+    // exist (rows that NX does not divide: block-uniform)
+    template <int NX>
+    __device__ __forceinline__ void ldv(uint32_t off, bool tail, int n, T (&out)[NX]) const {
+        constexpr int B = NX * (int)sizeof(T);
+        if constexpr (NX == 1) out[0] = ld(off);
+        else if constexpr (sizeof(T) == 1) {
+#pragma unroll
+            for (int q = 0; q < NX; ++q) out[q] = ld(q < n ? off + q : kOut);
+        } else if (tail) {
+#pragma unroll
+            for (int q = 0; q < NX; ++q) out[q] = ld(q < n ? off + q * (uint32_t)sizeof(T) : kOut);
+        } else if constexpr (B == 8) {
+            const auto w = __builtin_bit_cast(typename Vec<T, NX>::A, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0));
+#pragma unroll
+            for (int q = 0; q < NX; ++q) out[q] = w[q];
+        } else {
+            static_assert(B == 16, "8 or 16 bytes per thread");
+            const auto w = __builtin_bit_cast(typename Vec<T, NX>::A, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0));
+#pragma unroll
+            for (int q = 0; q < NX; ++q) out[q] = w[q];
+        }
+    }
+    template <int NX>
+    __device__ __forceinline__ void stv(uint32_t off, bool tail, int n, const T (&val)[NX]) const {
+        constexpr int B = NX * (int)sizeof(T);
+        if (NX == 1) st(off, val[0]);
+        else if (tail) {
+#pragma unroll
+            for (int q = 0; q < NX; ++q) st(q < n ? off + q * (uint32_t)sizeof(T) : kOut, val[q]);
+        } else {
+            typename Vec<T, NX>::A w;
+#pragma unroll
+            for (int q = 0; q < NX; ++q) w[q] = val[q];
+            if constexpr (B == 8) __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, w), r, off, 0, 0);
+            else if constexpr (B == 16) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, w), r, off, 0, 0);
+        }
+    }
+#else   // host pass: never runs
+    __device__ Plane(const T*, long, long) {}
+    __device__ T ld(uint32_t) const { return T(0); }
+    template <int NX>
+    __device__ void ldv(uint32_t, bool, int, T (&)[NX]) const {}
+    template <int NX>
+    __device__ void stv(uint32_t, bool, int, const T (&)[NX]) const {}
+#endif
+};
+
+// Where a thread's nodes are: plane [base, base + pl) of the box, NX nodes
+// from off on, of which n exist (n is 0 or NX unless tail).
+struct At {
+    long base, pl;
+    uint32_t off;
+    int n;
+    bool tail;
+    template <class T>
+    __device__ __forceinline__ uint32_t at() const { return n > 0 ? off * (uint32_t)sizeof(T) : kOut; }
+    template <int NX, class T>
+    __device__ __forceinline__ void ld(const T* p, T (&out)[NX]) const {
+        Plane<T>(p, base, pl).template ldv<NX>(at<T>(), tail, n, out);
+    }
+    template <int NX, class T>
+    __device__ __forceinline__ void st(T* p, const T (&val)[NX]) const {
+        Plane<T>(p, base, pl).template stv<NX>(at<T>(), tail, n, val);
+    }
+};
+// Static fields Q0 .. Q0 + N - 1 of the NX nodes: the interior values (scalar
+// registers) in a wave without edge nodes; else edge nodes load their own.
+template <int Q0, int N, int NX, class T, class F>
+__device__ __forceinline__ void with_static(const NodeCtx<T>& c, const At& a, const uint8_t (&cb)[NX], F&& f) {
+    bool edge = false;
+#pragma unroll
+    for (int q = 0; q < NX; ++q) edge = edge || (q < a.n && !(cb[q] & 2));
+    T st[NX][N];
+#pragma unroll
+    for (int q = 0; q < NX; ++q)
+#pragma unroll
+        for (int k = 0; k < N; ++k) st[q][k] = c.sint[Q0 + k];
+    if (__ballot(edge) == 0) {
+        f(st);
+        return;
+    }
+#pragma unroll
+    for (int q = 0; q < NX; ++q)
+        if (q < a.n) c.template st_range<Q0, N>(Nd{a.base, a.off + q}, cb[q], st[q]);
+    f(st);
+}
+
 // ------------------------------------------------------------ epilogues
 // Dilatation: theta = 3 chi / m (S - g_i u_i), 0 off the body or where m = 0.
 template <class T>
@@ -210,26 +337,26 @@ struct EpTheta {
     template <int NX>
     struct Ld { T u[3][NX]; uint8_t cb[NX]; };
     template <int NX>
-    __device__ __forceinline__ void load(long base, uint32_t off, int n, Ld<NX>& Q) const {
-        ldn<NX>(c.chiB, base, off, n, Q.cb);
+    __device__ __forceinline__ void load(const At& a, Ld<NX>& Q) const {
+        a.ld<NX>(c.chiB, Q.cb);
 #pragma unroll
-        for (int d = 0; d < 3; ++d) ldn<NX>(u + d * c.nb, base, off, n, Q.u[d]);
+        for (int d = 0; d < 3; ++d) a.ld<NX>(u + d * c.nb, Q.u[d]);
     }
     template <int NX>
-    __device__ __forceinline__ void fin(long base, uint32_t off, int n, const Ld<NX>& Q, const T (&val)[1][NX],
-                                        double*) const {
-        T out[NX];
+    __device__ __forceinline__ void fin(const At& a, const Ld<NX>& Q, const T (&val)[1][NX], double*) const {
+        with_static<6, 4, NX>(c, a, Q.cb, [&](const T (&st)[NX][4]) {
+            T out[NX];
 #pragma unroll
-        for (int q = 0; q < NX; ++q) {
-            T st[4] = {c.sint[6], c.sint[7], c.sint[8], c.sint[9]};
-            if (q < n) c.template st_range<6, 4>(Nd{base, off + q}, Q.cb[q], st);
-            T acc = val[0][q];
+            for (int q = 0; q < NX; ++q) {
+                T acc = val[0][q];
 #pragma unroll
-            for (int d = 0; d < 3; ++d) acc -= st[d] * Q.u[d][q];
-            const bool on = Q.cb[q] && st[3] != T(0);
-            out[q] = on ? T(3) / (on ? st[3] : T(1)) * acc : T(0);
-        }
-        stn<NX>(theta, base, off, n, out);
+                for (int d = 0; d < 3; ++d) acc -= st[q][d] * Q.u[d][q];
+                const T m = st[q][3];
+                const bool on = Q.cb[q] && m != T(0);
+                out[q] = on ? T(3) / (on ? m : T(1)) * acc : T(0);
+            }
+            a.st<NX>(theta, out);
+        });
     }
 };
 
@@ -265,48 +392,50 @@ struct EpForce {
     template <int NX>
     struct Ld { T u[3][NX], th[NX], x[NR == 1 ? 1 : 3][NX], y[3][NX]; uint8_t cb[NX]; };
     template <int NX>
-    __device__ __forceinline__ void load(long base, uint32_t off, int n, Ld<NX>& Q) const {
-        ldn<NX>(c.chiB, base, off, n, Q.cb);
+    __device__ __forceinline__ void load(const At& a, Ld<NX>& Q) const {
+        a.ld<NX>(c.chiB, Q.cb);
 #pragma unroll
-        for (int d = 0; d < 3; ++d) ldn<NX>(u + d * c.nb, base, off, n, Q.u[d]);
-        if constexpr (LPS) ldn<NX>(theta, base, off, n, Q.th);
+        for (int d = 0; d < 3; ++d) a.ld<NX>(u + d * c.nb, Q.u[d]);
+        if constexpr (LPS) a.ld<NX>(theta, Q.th);
         if constexpr (NR != 1) {
             if (mode == 1) {
 #pragma unroll
-                for (int d = 0; d < 3; ++d) ldn<NX>(v + d * c.nb, base, off, n, Q.x[d]);
+                for (int d = 0; d < 3; ++d) a.ld<NX>(v + d * c.nb, Q.x[d]);
                 if (!vh_in) {
 #pragma unroll
-                    for (int d = 0; d < 3; ++d) ldn<NX>(F + d * c.nb, base, off, n, Q.y[d]);
+                    for (int d = 0; d < 3; ++d) a.ld<NX>(F + d * c.nb, Q.y[d]);
                 }
             }
         } else {
             if (mode == 3) {
 #pragma unroll
-                for (int d = 0; d < 3; ++d) ldn<NX>(b + d * c.nb, base, off, n, Q.y[d]);
+                for (int d = 0; d < 3; ++d) a.ld<NX>(b + d * c.nb, Q.y[d]);
             }
         }
     }
     template <int NX>
-    __device__ __forceinline__ void fin(long base, uint32_t off, int n, const Ld<NX>& Q, const T (&val)[3][NX],
-                                        double* red) const {
+    __device__ __forceinline__ void fin(const At& a, const Ld<NX>& Q, const T (&val)[3][NX], double* red) const {
+        constexpr int NS = LPS ? 9 : 6;
         T La[3][NX];
+        with_static<0, NS, NX>(c, a, Q.cb, [&](const T (&st)[NX][NS]) {
 #pragma unroll
-        for (int q = 0; q < NX; ++q) {
-            constexpr int NS = LPS ? 9 : 6;
-            T st[NS];
+            for (int q = 0; q < NX; ++q) {
+                const T chi = Q.cb[q] ? T(1) : T(0);
 #pragma unroll
-            for (int k = 0; k < NS; ++k) st[k] = c.sint[k];
-            if (q < n) c.template st_range<0, NS>(Nd{base, off + q}, Q.cb[q], st);
-            const T chi = Q.cb[q] ? T(1) : T(0);
+                for (int d = 0; d < 3; ++d) {
+                    T acc = val[d][q];
 #pragma unroll
-            for (int a = 0; a < 3; ++a) {
-                T acc = val[a][q];
-#pragma unroll
-                for (int j = 0; j < 3; ++j) acc -= st[symi(3, a, j)] * Q.u[j][q];
-                if constexpr (LPS) acc += ka * Q.th[q] * st[6 + a];
-                La[a][q] = chi * acc;
+                    for (int j = 0; j < 3; ++j) acc -= st[q][symi(3, d, j)] * Q.u[j][q];
+                    if constexpr (LPS) acc += ka * Q.th[q] * st[q][6 + d];
+                    La[d][q] = chi * acc;
+                }
             }
-        }
+        });
+        finish<NX>(a, Q, La, red);
+    }
+    template <int NX>
+    __device__ __forceinline__ void finish(const At& at, const Ld<NX>& Q, const T (&La)[3][NX], double* red) const {
+        const int n = at.n;
         if constexpr (NR == 1) {
 #pragma unroll
             for (int a = 0; a < 3; ++a) {
@@ -322,18 +451,18 @@ struct EpForce {
                         red[0] += double(out[q]) * double(out[q]);
                     }
                 }
-                stn<NX>(L + a * c.nb, base, off, n, out);
+                at.st<NX>(L + a * c.nb, out);
             }
         } else {
             if (mode == 0) {
 #pragma unroll
-                for (int a = 0; a < 3; ++a) stn<NX>(L + a * c.nb, base, off, n, La[a]);
+                for (int a = 0; a < 3; ++a) at.st<NX>(L + a * c.nb, La[a]);
                 return;
             }
 #pragma unroll
             for (int a = 0; a < 3; ++a) {
                 T bk[NX], vo[NX], fo[NX];
-                if (b) ldn<NX>(b + a * c.nb, base, off, n, bk);
+                if (b) at.ld<NX>(b + a * c.nb, bk);
                 else {
 #pragma unroll
                     for (int q = 0; q < NX; ++q) bk[q] = T(0);
@@ -357,15 +486,15 @@ struct EpForce {
                         }
                     }
                 }
-                stn<NX>(v + a * c.nb, base, off, n, vo);
-                if (!vh_out) stn<NX>(F + a * c.nb, base, off, n, fo);
+                at.st<NX>(v + a * c.nb, vo);
+                if (!vh_out) at.st<NX>(F + a * c.nb, fo);
                 else {
                     T wk[NX];
-                    if (w) ldn<NX>(w + a * c.nb, base, off, n, wk);
+                    if (w) at.ld<NX>(w + a * c.nb, wk);
 #pragma unroll
                     for (int q = 0; q < NX; ++q)
                         wk[q] = omega_bit(Q.cb[q], a) ? Q.u[a][q] + dt * vo[q] : (w ? wk[q] : T(0));
-                    stn<NX>(u_next + a * c.nb, base, off, n, wk);
+                    at.st<NX>(u_next + a * c.nb, wk);
                 }
             }
         }
@@ -383,11 +512,33 @@ struct D3In {
     const T* f[4];           // input fields (each one component)
     const uint8_t* chiB;     // node flags: inputs are multiplied by chi_B
 };
+// All arguments of a launch.  The epilogue's are read from the argument
+// segment plane by plane through an address the compiler cannot follow: held
+// in scalar registers over the sweep, next to the kernel values, they would
+// spill.
+template <class T, class Ep, int MT>
+struct D3Args {
+    D3Geo g;
+    D3In<T> in;
+    Taps<T, MT> tp;
+    double* partials;
+    Ep ep;
+};
+template <class A>
+__device__ __forceinline__ const A& launch_args() {
+#if defined(__HIP_DEVICE_COMPILE__)
+    auto p = (const __attribute__((address_space(4))) A*)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return *(const A*)p;
+#else
+    return *(const A*)nullptr;
+#endif
+}
 
 // FP32 and FP64 tiles: TX columns along x, TY along y, NX nodes per thread.
 template <class T, class Op, class Ep, int MT, int TX, int TY, int NX>
 __global__ void __launch_bounds__((TX / NX) * TY) __attribute__((amdgpu_waves_per_eu(2)))
-k_dir3(D3Geo g, D3In<T> in, Taps<T, MT> tp, Ep ep, double* __restrict__ partials) {
+k_dir3(D3Args<T, Ep, MT> A) {
     using VA = typename Vec<T, NX>::A;
     constexpr int NI = Op::NI, NO = Op::NO, NT = (TX / NX) * TY;
     constexpr int H = (MT + NX - 1) / NX * NX;       // halo columns kept (aligned)
@@ -396,6 +547,8 @@ k_dir3(D3Geo g, D3In<T> in, Taps<T, MT> tp, Ep ep, double* __restrict__ partials
     constexpr int NE = (FX * HY + NT - 1) / NT;      // nodes a thread fills
     extern __shared__ __align__(16) unsigned char smem_raw[];
     lds_ptr<T> lds = as_lds(reinterpret_cast<T*>(smem_raw));
+    const D3Geo g = A.g;
+    const Taps<T, MT>& tp = A.tp;
 
     // consecutive blocks of a z-chunk on one XCD (the hardware deals blocks to
     // the 8 XCDs in turn), so that the tiles sharing halos share an L2
@@ -407,34 +560,40 @@ k_dir3(D3Geo g, D3In<T> in, Taps<T, MT> tp, Ep ep, double* __restrict__ partials
     const long pl = (long)g.b1 * g.b2;
 
     const int tid = threadIdx.x, tx = tid % (TX / NX), ty = tid / (TX / NX);
-    const int x = tx0 + tx * NX, y = ty0 + ty;
-    const int nx = y < g.b2 ? min(max(g.b1 - x, 0), NX) : 0;   // nodes of this thread in the body box
-    const uint32_t off = nx > 0 ? (uint32_t)(y * g.b1 + x) : 0u;
+    At at;
+    {
+        const int x = tx0 + tx * NX, y = ty0 + ty;
+        at.pl = pl;
+        at.n = y < g.b2 ? min(max(g.b1 - x, 0), NX) : 0;   // nodes of this thread in the body box
+        at.off = at.n > 0 ? (uint32_t)(y * g.b1 + x) : 0u;
+        at.tail = g.b1 % NX != 0;
+    }
 
-    // this thread's share of the plane fill
+    // this thread's share of the plane fill: node offsets (kOut / 8 outside the
+    // box, which reads zero) and LDS slots
     uint32_t go[NE];
     int lo[NE];
-    uint32_t okm = 0;
 #pragma unroll
     for (int i = 0; i < NE; ++i) {
         const int e = tid + NT * i, r = e / FX, cx = e - r * FX;
         const int gx = tx0 - MT + cx, gy = ty0 - MT + r;
-        const bool in_tile = e < FX * HY;
-        const bool ok = in_tile && gx >= 0 && gx < g.b1 && gy >= 0 && gy < g.b2;
-        go[i] = ok ? (uint32_t)(gy * g.b1 + gx) : 0u;
-        lo[i] = in_tile ? r * W + cx + (H - MT) : -1;
-        okm |= ok ? 1u << i : 0u;
+        const bool ok = e < FX * HY && gx >= 0 && gx < g.b1 && gy >= 0 && gy < g.b2;
+        go[i] = ok ? (uint32_t)(gy * g.b1 + gx) : kOut / 8;
+        lo[i] = r * W + cx + (H - MT);
     }
     T pre[NI][NE];
     uint8_t pcb[NE];
     auto fetch = [&](int z) {
-        const long base = (long)min(max(z, 0), g.b3 - 1) * pl;
+        const long base = (long)z * pl, in = z < g.b3 ? pl : 0;   // planes beyond the body read zero
+        const Plane<uint8_t> fc(A.in.chiB, base, in);
 #pragma unroll
-        for (int i = 0; i < NE; ++i) pcb[i] = ldf(in.chiB, Nd{base, go[i]});
+        for (int i = 0; i < NE; ++i) pcb[i] = fc.ld(go[i]);
 #pragma unroll
-        for (int J = 0; J < NI; ++J)
+        for (int J = 0; J < NI; ++J) {
+            const Plane<T> f(A.in.f[J], base, in);
 #pragma unroll
-            for (int i = 0; i < NE; ++i) pre[J][i] = ldf(in.f[J], Nd{base, go[i]});
+            for (int i = 0; i < NE; ++i) pre[J][i] = f.ld(go[i] * (uint32_t)sizeof(T));
+        }
     };
 
     T acc[2 * MT][NO][NX];   // outputs at planes zi - MT .. zi + MT - 1 on entry of a plane
@@ -448,31 +607,27 @@ k_dir3(D3Geo g, D3In<T> in, Taps<T, MT> tp, Ep ep, double* __restrict__ partials
 #pragma unroll
     for (int r = 0; r < (Ep::NRED > 0 ? Ep::NRED : 1); ++r) red[r] = 0.0;
 
-    // planes outside the body hold zeros: the sweep starts and ends inside
+    // (planes below the body would only add zeros)
     const int zb = max(z0 - MT, 0), ze = z1 + MT;
     fetch(zb);
     for (int zi = zb; zi < ze; ++zi) {
-        const bool act = zi < g.b3;   // block-uniform
         lds_ptr<T> buf = lds + ((zi & 1) ? NI * HY * W : 0);
-        if (act) {
 #pragma unroll
-            for (int i = 0; i < NE; ++i) {
-                if (lo[i] >= 0) {
-                    const bool ok = (okm >> i) & 1u;
-                    const T chi = pcb[i] ? T(1) : T(0);
+        for (int i = 0; i < NE; ++i) {
+            if (NT * (i + 1) <= FX * HY || tid + NT * i < FX * HY) {
+                const T chi = pcb[i] ? T(1) : T(0);
 #pragma unroll
-                    for (int J = 0; J < NI; ++J) buf[J * HY * W + lo[i]] = ok ? chi * pre[J][i] : T(0);
-                }
+                for (int J = 0; J < NI; ++J) buf[J * HY * W + lo[i]] = chi * pre[J][i];
             }
         }
         __syncthreads();
-        if (zi + 1 < min(ze, g.b3)) fetch(zi + 1);
+        if (zi + 1 < ze) fetch(zi + 1);
         // the finished plane's node fields, in flight during the arithmetic
         const int zo = zi - MT;
         const bool outp = zo >= z0;   // block-uniform (zo < z1 by the sweep)
-        const long ob = (long)max(zo, 0) * pl;
+        at.base = (long)max(zo, 0) * pl;
         typename Ep::template Ld<NX> ld;
-        if (outp) ep.template load<NX>(ob, off, nx, ld);
+        if (outp) launch_args<D3Args<T, Ep, MT>>().ep.template load<NX>(at, ld);
 
         // plane sums: a0 (offset 0, into the accumulator of plane zi), qe and
         // qo (offsets 1 .. MT, even and odd along z)
@@ -482,92 +637,93 @@ k_dir3(D3Geo g, D3In<T> in, Taps<T, MT> tp, Ep ep, double* __restrict__ partials
 #pragma unroll
             for (int n = 0; n < NX; ++n) {
                 a0[o][n] = acc[MT][o][n];
-#pragma unroll
-                for (int c = 1; c <= MT; ++c) qe[c][o][n] = qo[c][o][n] = T(0);
             }
-        if (act) {
-            each<0, NI>([&](auto Jc) {
-                constexpr int J = decltype(Jc)::value;
-                lds_ptr<T> fld = buf + J * HY * W + (ty + MT) * W + tx * NX;
-                each<0, MT + 1>([&](auto bc) {
-                    constexpr int b = decltype(bc)::value, R = isqrt(MT * MT - b * b);
-                    constexpr int RA = (R + NX - 1) / NX * NX, WN = NX + 2 * RA;
-                    each<0, NO>([&](auto Oc) {
-                        constexpr int O = decltype(Oc)::value;
-                        constexpr Term t = Op::term(O, J);
-                        if constexpr (t.i >= 0) {
-                            if constexpr (t_par(t, 2) == 0) pin(a0[O]);
-                            each<1, MT + 1>([&](auto cc) {
-                                constexpr int c = decltype(cc)::value;
-                                if constexpr (t_par(t, 2) == 0 && takes<Op>(MT, O, 0, c)) pin(qe[c][O]);
-                                if constexpr (t_par(t, 2) == 1 && takes<Op>(MT, O, 1, c)) pin(qo[c][O]);
-                            });
-                        }
-                    });
-                    row_fence();
-                    // rows y + b and y - b around the thread's nodes: columns
-                    // -RA .. NX - 1 + RA
-                    T up[WN], dn[WN], E[WN], D[WN];
-#pragma unroll
-                    for (int k = 0; k < WN / NX; ++k) {
-                        const VA a = *(lds_ptr<VA>)(fld + b * W + (H - RA) + k * NX);
-#pragma unroll
-                        for (int n = 0; n < NX; ++n) up[k * NX + n] = a[n];
-                        if constexpr (b > 0) {
-                            const VA d = *(lds_ptr<VA>)(fld - b * W + (H - RA) + k * NX);
-#pragma unroll
-                            for (int n = 0; n < NX; ++n) dn[k * NX + n] = d[n];
-                        }
-                    }
-#pragma unroll
-                    for (int k = 0; k < WN; ++k) {
-                        if constexpr (b > 0) {
-                            E[k] = up[k] + dn[k];
-                            D[k] = up[k] - dn[k];
-                        } else {
-                            E[k] = up[k];
-                            D[k] = T(0);
-                        }
-                    }
-                    each<0, R + 1>([&](auto ac) {
-                        constexpr int a = decltype(ac)::value;
-                        each<0, 4>([&](auto pc) {
-                            constexpr int px = decltype(pc)::value & 1, py = decltype(pc)::value >> 1;
-                            if constexpr (uses<Op>(MT, J, px, py, a, b)) {
-#pragma unroll
-                                for (int n = 0; n < NX; ++n) {
-                                    const T p = py ? D[RA + n + a] : E[RA + n + a];
-                                    const T m = py ? D[RA + n - a] : E[RA + n - a];
-                                    const T f = a == 0 ? p : (px ? p - m : p + m);
-                                    each<0, NO>([&](auto Oc) {
-                                        constexpr int O = decltype(Oc)::value;
-                                        constexpr Term t = Op::term(O, J);
-                                        if constexpr (t.i >= 0 && t_par(t, 0) == px && t_par(t, 1) == py) {
-                                            each<0, MT + 1>([&](auto cc) {
-                                                constexpr int c = decltype(cc)::value;
-                                                if constexpr (t_nonzero(t, MT, a, b, c)) {
-                                                    constexpr int r2 = a * a + b * b + c * c;
-                                                    constexpr int oi = t_coord(t.i, a, b, c);
-                                                    constexpr int oj = t_coord(t.j < 0 ? 0 : t.j, a, b, c);
-                                                    constexpr int id = t.j >= 0 ? kTapIds<MT>.c[r2][oi * oj]
-                                                                                : kTapIds<MT>.a[r2][oi];
-                                                    T k;
-                                                    if constexpr (t.j >= 0) k = tp.c[id];
-                                                    else k = tp.a[id];
-                                                    if constexpr (c == 0) a0[O][n] += k * f;
-                                                    else if constexpr (t_par(t, 2) == 0) qe[c][O][n] += k * f;
-                                                    else qo[c][O][n] += k * f;
-                                                }
-                                            });
-                                        }
-                                    });
-                                }
-                            }
+        each<0, NI>([&](auto Jc) {
+            constexpr int J = decltype(Jc)::value;
+            lds_ptr<T> fld = buf + J * HY * W + (ty + MT) * W + tx * NX;
+            each<0, MT + 1>([&](auto bc) {
+                constexpr int b = decltype(bc)::value, R = isqrt(MT * MT - b * b);
+                constexpr int RA = (R + NX - 1) / NX * NX, WN = NX + 2 * RA;
+                each<0, NO>([&](auto Oc) {
+                    constexpr int O = decltype(Oc)::value;
+                    constexpr Term t = Op::term(O, J);
+                    if constexpr (t.i >= 0) {
+                        if constexpr (t_par(t, 2) == 0) pin(a0[O]);
+                        each<1, MT + 1>([&](auto cc) {
+                            constexpr int c = decltype(cc)::value;
+                            constexpr int pz = t_par(t, 2);
+                            if constexpr (takes<Op>(MT, O, pz, c) && !starts<Op>(MT, O, pz, c, J, b, 0))
+                                pin(pz ? qo[c][O] : qe[c][O]);
                         });
+                    }
+                });
+                row_fence();
+                // rows y + b and y - b around the thread's nodes: columns
+                // -RA .. NX - 1 + RA
+                T up[WN], dn[WN], E[WN], D[WN];
+#pragma unroll
+                for (int k = 0; k < WN / NX; ++k) {
+                    const VA a = *(lds_ptr<VA>)(fld + b * W + (H - RA) + k * NX);
+#pragma unroll
+                    for (int n = 0; n < NX; ++n) up[k * NX + n] = a[n];
+                    if constexpr (b > 0) {
+                        const VA d = *(lds_ptr<VA>)(fld - b * W + (H - RA) + k * NX);
+#pragma unroll
+                        for (int n = 0; n < NX; ++n) dn[k * NX + n] = d[n];
+                    }
+                }
+#pragma unroll
+                for (int k = 0; k < WN; ++k) {
+                    if constexpr (b > 0) {
+                        E[k] = up[k] + dn[k];
+                        D[k] = up[k] - dn[k];
+                    } else {
+                        E[k] = up[k];
+                        D[k] = T(0);
+                    }
+                }
+                each<0, R + 1>([&](auto ac) {
+                    constexpr int a = decltype(ac)::value;
+                    each<0, 4>([&](auto pc) {
+                        constexpr int px = decltype(pc)::value & 1, py = decltype(pc)::value >> 1;
+                        if constexpr (uses<Op>(MT, J, px, py, a, b)) {
+#pragma unroll
+                            for (int n = 0; n < NX; ++n) {
+                                const T p = py ? D[RA + n + a] : E[RA + n + a];
+                                const T m = py ? D[RA + n - a] : E[RA + n - a];
+                                const T f = a == 0 ? p : (px ? p - m : p + m);
+                                each<0, NO>([&](auto Oc) {
+                                    constexpr int O = decltype(Oc)::value;
+                                    constexpr Term t = Op::term(O, J);
+                                    if constexpr (t.i >= 0 && t_par(t, 0) == px && t_par(t, 1) == py) {
+                                        each<0, MT + 1>([&](auto cc) {
+                                            constexpr int c = decltype(cc)::value;
+                                            if constexpr (t_nonzero(t, MT, a, b, c)) {
+                                                constexpr int r2 = a * a + b * b + c * c;
+                                                constexpr int oi = t_coord(t.i, a, b, c);
+                                                constexpr int oj = t_coord(t.j < 0 ? 0 : t.j, a, b, c);
+                                                constexpr int id = t.j >= 0 ? kTapIds<MT>.c[r2][oi * oj]
+                                                                            : kTapIds<MT>.a[r2][oi];
+                                                T k;
+                                                if constexpr (t.j >= 0) k = tp.c[id];
+                                                else k = tp.a[id];
+                                                if constexpr (c == 0) a0[O][n] += k * f;
+                                                else {
+                                                    constexpr int pz = t_par(t, 2);
+                                                    T& q = pz ? qo[c][O][n] : qe[c][O][n];
+                                                    if constexpr (starts<Op>(MT, O, pz, c, J, b, a)) q = k * f;
+                                                    else q += k * f;
+                                                }
+                                            }
+                                        });
+                                    }
+                                });
+                            }
+                        }
                     });
                 });
             });
-        }
+        });
         // add the plane sums and shift by one plane
         T out[NO][NX];
         each<0, 2 * MT + 1>([&](auto pc) {
@@ -589,25 +745,46 @@ k_dir3(D3Geo g, D3In<T> in, Taps<T, MT> tp, Ep ep, double* __restrict__ partials
                 }
             });
         });
-        if (outp && nx > 0) ep.template fin<NX>(ob, off, nx, ld, out, red);
+        if (outp) launch_args<D3Args<T, Ep, MT>>().ep.template fin<NX>(at, ld, out, red);
     }
     if constexpr (Ep::NRED > 0) {
         __syncthreads();
         double* sm = reinterpret_cast<double*>(smem_raw);
-        block_reduce_store<Ep::NRED>(red, partials + (long)blockIdx.x * Ep::NRED, sm);
+        block_reduce_store<Ep::NRED>(red, A.partials + (long)blockIdx.x * Ep::NRED, sm);
     }
 }
 
 // Tile of a block and nodes per thread: 32 x 16 columns, two nodes per
-// thread.
-constexpr int kTX3 = 32, kTY3 = 16, kRes3 = 2;
+// thread.  RES: blocks a CU holds at once (by their registers).
 template <class T, class Op, int MT>
 struct Shape3 {
-    static constexpr int TX = kTX3, TY = kTY3, NX = 2, NT = TX / NX * TY;
+    static constexpr int TX = 32, TY = 16, NX = 2, NT = TX / NX * TY;
+    static constexpr int RES = sizeof(T) == 4 ? (Op::NO == 1 ? 4 : (MT <= 3 ? 3 : 2)) : (Op::NO == 1 && MT <= 3 ? 3 : 2);
     static constexpr size_t lds() {
         return sizeof(T) * 2 * Op::NI * (TY + 2 * MT) * (TX + 2 * ((MT + NX - 1) / NX * NX));
     }
 };
+// Planes per chunk: enough blocks for every CU to hold its resident ones, but
+// chunks no shorter than that needs, since each also sweeps up to 2 MT planes
+// of its neighbours: the chunk count that minimises rounds x planes swept, a
+// round being the blocks that 256 CUs hold at once (a last round that is
+// partly empty costs as much as a full one).
+inline int chunk3(const Geo& g, int mt, int tx, int ty, int res) {
+    const long tiles = (long)((g.b1 + tx - 1) / tx) * ((g.b2 + ty - 1) / ty), slots = 256L * res;
+    int best_zc = g.b3;
+    double best = 0;
+    for (int nz = 1; nz <= g.b3; ++nz) {
+        const int zc = (g.b3 + nz - 1) / nz;
+        const long blocks = tiles * ((g.b3 + zc - 1) / zc);
+        const double cost = (double)((blocks + slots - 1) / slots) * (zc + (nz > 1 ? 2.0 * mt : 0.0));
+        if (nz == 1 || cost < 0.98 * best) {
+            best = cost;
+            best_zc = zc;
+        }
+        if (blocks > 4 * slots) break;
+    }
+    return best_zc;
+}
 
 // ------------------------------------------------------------ position update
 template <class T, int D>
