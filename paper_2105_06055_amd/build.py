@@ -3,8 +3,8 @@
 Called by ``__graft_entry__.build()``; also runnable as
 ``python -m paper_2105_06055_amd.build``.  The C entry points (pd_fcbm.hip)
 and fourteen instantiation units of the per-dtype implementation (pd_inst.hip
-with PD_INST_T = float / double and PD_INST_PART = 0 .. 6) and ten of the
-direct-sum kernels (pd_direct.hip, PD_DIR_PART = 0 .. 4) compile in parallel
+with PD_INST_T = float / double and PD_INST_PART = 0 .. 6) and sixteen of
+the direct-sum kernels (pd_direct.hip, PD_DIR_PART = 0 .. 7) compile in parallel
 to objects, which are linked into the library, written in-tree next to this
 file so it travels with the source tree.
 """
@@ -19,13 +19,13 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libpdfcbm.so")
-HEADERS = ["pd_fft.hpp", "pd_ops.hpp", "pd_passes.hpp", "pd_plan.hpp", "pd_direct_api.hpp", "pd_direct.hpp", "pd_direct2.hpp",
-           "pd_impl.hpp"]
+HEADERS = ["pd_fft.hpp", "pd_ops.hpp", "pd_passes.hpp", "pd_plan.hpp", "pd_direct_api.hpp", "pd_direct.hpp",
+           "pd_direct2.hpp", "pd_impl.hpp"]
 UNITS = [("pd_fcbm.hip", [])] + [
     ("pd_inst.hip", ["-DPD_INST_T=%s" % t, "-DPD_INST_PART=%d" % part, "-DPD_INST_F32=%d" % (t == "float")])
     for t in ("float", "double") for part in range(7)] + [
     ("pd_direct.hip", ["-DPD_INST_T=%s" % t, "-DPD_DIR_PART=%d" % part, "-DPD_DIR_FIRST=%d" % (t == "float")])
-    for t in ("float", "double") for part in range(5)]
+    for t in ("float", "double") for part in range(8)]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",

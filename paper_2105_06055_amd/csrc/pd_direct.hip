@@ -1,7 +1,9 @@
-// pd_direct.hip -- launches of the direct horizon sums (pd_direct.hpp),
-// compiled in parallel units: PD_INST_T = float or double, PD_DIR_PART = 0 ..
-// 4 (3D LPS, 3D bond-based and the element-wise kernels, 2D, 2D adjoint and
-// damage, nonlinear).
+// pd_direct.hip -- launches of the direct horizon sums (pd_direct.hpp,
+// pd_direct2.hpp), compiled in parallel units: PD_INST_T = float or double,
+// PD_DIR_PART = 0 .. 2 the 3D LPS kernels at radius 2 .. 4, 3 and 4 the 3D
+// bond-based ones (radius 2 and 3 with the dispatch and the element-wise
+// kernels; radius 4), 5 the 2D force, 6 the 2D adjoint and damage count, 7 the
+// nonlinear model.
 #include <algorithm>
 
 #include "pd_direct2.hpp"
@@ -11,7 +13,7 @@
 #error "PD_INST_T must be defined (float or double)"
 #endif
 #ifndef PD_DIR_PART
-#error "PD_DIR_PART must be defined (0 .. 4)"
+#error "PD_DIR_PART must be defined (0 .. 7)"
 #endif
 
 namespace pdd {
@@ -26,60 +28,59 @@ inline pd_status finish_reduction(pd_plan p, long nblk, int nr, hipStream_t st) 
 }
 
 // ------------------------------------------------------------ 3D launches
+// g0: the interior static value the epilogue takes from scalar registers.
 template <class T, class Op, class Ep, int MT>
-pd_status launch3(pd_plan p, const D3In<T>& in, double ka, const Ep& ep, const char* name, hipStream_t st) {
-    using S = Shape3<T, Op, MT>;
+pd_status launch3(pd_plan p, const D3In<T>& in, double ka, T g0, const Ep& ep, const char* name, hipStream_t st) {
+    using S3 = Shape3<T, Op, MT>;
     const Geo& g = p->geo;
     D3Args<T, Ep, MT> a{};
-    D3Geo& d = a.g;
-    d.b1 = g.b1; d.b2 = g.b2; d.b3 = g.b3;
-    d.ntx = (g.b1 + S::TX - 1) / S::TX;
-    d.nty = (g.b2 + S::TY - 1) / S::TY;
-    d.zc = chunk3(g, MT, S::TX, S::TY, S::RES);
-    d.nzc = (g.b3 + d.zc - 1) / d.zc;
     a.in = in;
     a.partials = p->partials;
+    a.g0 = g0;
     a.ep = ep;
-    Taps<T, MT>& tp = a.tp;
     constexpr TapIds<MT> ids = kTapIds<MT>;
     for (int r2 = 1; r2 <= MT * MT; ++r2) {
         for (int pr = 1; pr <= MT * MT; ++pr)
-            if (ids.c[r2][pr] >= 0) tp.c[ids.c[r2][pr]] = T(p->dir_c[r2] * pr);
-        for (int a = 1; a <= MT; ++a)
-            if (ids.a[r2][a] >= 0) tp.a[ids.a[r2][a]] = T(ka * p->dir_a[r2] * a);
+            if (ids.c[r2][pr] >= 0) a.tp.c[ids.c[r2][pr]] = T(p->dir_c[r2] * pr);
+        for (int k = 1; k <= MT; ++k)
+            if (ids.a[r2][k] >= 0) a.tp.a[ids.a[r2][k]] = T(ka * p->dir_a[r2] * k);
     }
-    const long nblk = (long)d.ntx * d.nty * d.nzc;
-    if (nblk > 0x7fffffffL) return PD_EUNSUPPORTED;
-    if (Ep::NRED > 0 && nblk * Ep::NRED > p->partials_cap) return PD_EINVAL;
-    constexpr size_t lds = S::lds();
-    if (lds > (size_t)p->max_lds) return PD_EUNSUPPORTED;
-    auto kern = k_dir3<T, Op, Ep, MT, S::TX, S::TY, S::NX>;
-    allow_lds(kern, lds);
-    ProfScope ps(p, st);
-    hipLaunchKernelGGL(kern, dim3((unsigned)nblk), dim3(S::NT), lds, st, a);
-    if (p->prof) {
-        char nm[32];
-        std::snprintf(nm, sizeof nm, "%s_m%d", name, MT);
-        ps.done(nm, ep.nbytes() * (double)g.nb);
+    auto go = [&](auto shape) -> pd_status {
+        using S = decltype(shape);
+        D3Geo& d = a.g;
+        d.b1 = g.b1; d.b2 = g.b2; d.b3 = g.b3;
+        d.ntx = (g.b1 + S::TX - 1) / S::TX;
+        d.nty = (g.b2 + S::TY - 1) / S::TY;
+        d.zc = chunk3(g, MT, S::TX, S::TY, S3::RES, S3::LAT);
+        d.nzc = (g.b3 + d.zc - 1) / d.zc;
+        const long nblk = (long)d.ntx * d.nty * d.nzc;
+        if (nblk > 0x7fffffffL) return PD_EUNSUPPORTED;
+        if (Ep::NRED > 0 && nblk * Ep::NRED > p->partials_cap) return PD_EINVAL;
+        constexpr size_t lds = S::template lds<T, Op, MT>();
+        if (lds > (size_t)p->max_lds) return PD_EUNSUPPORTED;
+        auto kern = k_dir3<T, Op, Ep, MT, S>;
+        allow_lds(kern, lds);
+        ProfScope ps(p, st);
+        hipLaunchKernelGGL(kern, dim3((unsigned)nblk), dim3(S::NT), lds, st, a);
+        if (p->prof) {
+            char nm[32];
+            std::snprintf(nm, sizeof nm, "%s_m%d", name, MT);
+            ps.done(nm, ep.nbytes() * (double)g.nb);
+        }
+        if (pd_status s = pdh::check(hipGetLastError()); s != PD_OK) return s;
+        if (Ep::NRED > 0) return finish_reduction(p, nblk, Ep::NRED, st);
+        return PD_OK;
+    };
+    if constexpr (S3::PAIR) {
+        // rows of an odd length: the last thread of a row has one node
+        if (g.b1 % 2 != 0) return go(typename S3::template S<false>{});
     }
-    if (pd_status s = pdh::check(hipGetLastError()); s != PD_OK) return s;
-    if (Ep::NRED > 0) return finish_reduction(p, nblk, Ep::NRED, st);
-    return PD_OK;
+    return go(typename S3::template S<true>{});
 }
 
-template <class T, class Op, class Ep>
-pd_status by_radius(pd_plan p, const D3In<T>& in, double ka, const Ep& ep, const char* name, hipStream_t st) {
-    switch (p->dir_mt) {
-        case 2: return launch3<T, Op, Ep, 2>(p, in, ka, ep, name, st);
-        case 3: return launch3<T, Op, Ep, 3>(p, in, ka, ep, name, st);
-        case 4: return launch3<T, Op, Ep, 4>(p, in, ka, ep, name, st);
-        default: return PD_EUNSUPPORTED;
-    }
-}
-
-template <class T, bool LPS, int NR>
+template <class T, bool LPS, int MT, int KIND>
 pd_status force3(pd_plan p, const Eval<T>& e, hipStream_t st) {
-    EpForce<T, LPS, NR> ep{};
+    EpForce<T, LPS, KIND> ep{};
     ep.c = pdi::ctx<T>(p);
     ep.mode = e.mode;
     ep.ka = T(p->ka);
@@ -89,41 +90,66 @@ pd_status force3(pd_plan p, const Eval<T>& e, hipStream_t st) {
     ep.u_next = e.u_next;
     ep.nanflag = e.nanflag;
     ep.vh_in = e.vh_in; ep.vh_out = e.vh_out;
+    ep.has = (e.b ? 1 : 0) | (e.w ? 2 : 0);
     D3In<T> in{{e.u, e.u + p->nb, e.u + 2 * p->nb, e.theta}, p->chiB};
-    if constexpr (LPS) return by_radius<T, OpB>(p, in, p->ka, ep, "dir3_lps", st);
-    else return by_radius<T, OpC>(p, in, 0.0, ep, "dir3_bb", st);
+    const T g0 = ep.c.sint[0];   // G_xx = G_yy = G_zz; the odd sums vanish
+    if constexpr (LPS) return launch3<T, OpB, EpForce<T, LPS, KIND>, MT>(p, in, p->ka, g0, ep, "dir3_lps", st);
+    else return launch3<T, OpC, EpForce<T, LPS, KIND>, MT>(p, in, 0.0, g0, ep, "dir3_bb", st);
 }
-
-#if PD_DIR_PART == 0
-template <class T>
-pd_status dir3_theta(pd_plan p, const T* u, T* theta, hipStream_t st) {
+// Force sums at radius MT, and the dilatation; each compiled in one unit.
+template <class T, bool LPS, int MT>
+pd_status force3_at(pd_plan p, const Eval<T>& e, hipStream_t st) {
+    if (e.mode >= 2) return force3<T, LPS, MT, SOLVER>(p, e, st);
+    if (e.mode == 0) return force3<T, LPS, MT, FORCE>(p, e, st);
+    if (e.energy) return force3<T, LPS, MT, ENERGY>(p, e, st);
+    return e.vh_in && e.vh_out ? force3<T, LPS, MT, INNER>(p, e, st) : force3<T, LPS, MT, STEP>(p, e, st);
+}
+template <class T, int MT>
+pd_status theta3_at(pd_plan p, const T* u, T* theta, hipStream_t st) {
     EpTheta<T> ep{};
     ep.c = pdi::ctx<T>(p);
     ep.u = u;
     ep.theta = theta;
     D3In<T> in{{u, u + p->nb, u + 2 * p->nb, nullptr}, p->chiB};
-    return by_radius<T, OpA>(p, in, 1.0, ep, "dir3_theta", st);
+    const T g0 = T(3) / ep.c.sint[9];   // 3 / m
+    return launch3<T, OpA, EpTheta<T>, MT>(p, in, 1.0, g0, ep, "dir3_theta", st);
 }
-template pd_status dir3_theta<PD_INST_T>(pd_plan, const PD_INST_T*, PD_INST_T*, hipStream_t);
+
+using R = PD_INST_T;
+#if PD_DIR_PART <= 2
+template pd_status force3_at<R, true, PD_DIR_PART + 2>(pd_plan, const Eval<R>&, hipStream_t);
+template pd_status theta3_at<R, PD_DIR_PART + 2>(pd_plan, const R*, R*, hipStream_t);
+#elif PD_DIR_PART == 4
+template pd_status force3_at<R, false, 4>(pd_plan, const Eval<R>&, hipStream_t);
+#elif PD_DIR_PART == 3
+extern template pd_status force3_at<R, true, 2>(pd_plan, const Eval<R>&, hipStream_t);
+extern template pd_status force3_at<R, true, 3>(pd_plan, const Eval<R>&, hipStream_t);
+extern template pd_status force3_at<R, true, 4>(pd_plan, const Eval<R>&, hipStream_t);
+extern template pd_status force3_at<R, false, 4>(pd_plan, const Eval<R>&, hipStream_t);
+extern template pd_status theta3_at<R, 2>(pd_plan, const R*, R*, hipStream_t);
+extern template pd_status theta3_at<R, 3>(pd_plan, const R*, R*, hipStream_t);
+extern template pd_status theta3_at<R, 4>(pd_plan, const R*, R*, hipStream_t);
 
 template <class T>
-pd_status dir3_lps(pd_plan p, const Eval<T>& e, hipStream_t st) {
-    if (e.mode >= 2) return force3<T, true, 1>(p, e, st);
-    if (e.energy) return force3<T, true, 4>(p, e, st);
-    return force3<T, true, 0>(p, e, st);
+pd_status dir3_theta(pd_plan p, const T* u, T* theta, hipStream_t st) {
+    switch (p->dir_mt) {
+        case 2: return theta3_at<T, 2>(p, u, theta, st);
+        case 3: return theta3_at<T, 3>(p, u, theta, st);
+        case 4: return theta3_at<T, 4>(p, u, theta, st);
+        default: return PD_EUNSUPPORTED;
+    }
 }
-template pd_status dir3_lps<PD_INST_T>(pd_plan, const Eval<PD_INST_T>&, hipStream_t);
-#elif PD_DIR_PART == 1
-template <class T>
-pd_status dir3_lps(pd_plan p, const Eval<T>& e, hipStream_t st);
-
 template <class T>
 pd_status dir3_force(pd_plan p, const Eval<T>& e, hipStream_t st) {
-    if (p->kern.model == PD_LPS_LINEAR) return dir3_lps<T>(p, e, st);
-    if (e.mode >= 2) return force3<T, false, 1>(p, e, st);
-    if (e.energy) return force3<T, false, 4>(p, e, st);
-    return force3<T, false, 0>(p, e, st);
+    const bool lps = p->kern.model == PD_LPS_LINEAR;
+    switch (p->dir_mt) {
+        case 2: return lps ? force3_at<T, true, 2>(p, e, st) : force3_at<T, false, 2>(p, e, st);
+        case 3: return lps ? force3_at<T, true, 3>(p, e, st) : force3_at<T, false, 3>(p, e, st);
+        case 4: return lps ? force3_at<T, true, 4>(p, e, st) : force3_at<T, false, 4>(p, e, st);
+        default: return PD_EUNSUPPORTED;
+    }
 }
+template pd_status dir3_theta<PD_INST_T>(pd_plan, const PD_INST_T*, PD_INST_T*, hipStream_t);
 template pd_status dir3_force<PD_INST_T>(pd_plan, const Eval<PD_INST_T>&, hipStream_t);
 
 template <class T>
@@ -149,11 +175,11 @@ template pd_status dir_drift<PD_INST_T>(pd_plan, const PD_INST_T*, PD_INST_T*, c
 
 #if PD_DIR_FIRST   // once: not per type
 // Most blocks of a launch with a reduction: plate tiles of 32 x 4 nodes, or
-// four rounds of three resident blocks per CU and one more of tiles (chunk3).
+// four rounds of seven resident blocks per CU and one more of tiles (chunk3).
 void dir_launch_shape(pd_plan p) {
     const Geo& g = p->geo;
     const long tiles = (long)((g.b1 + 31) / 32) * ((g.b2 + 3) / 4);
-    p->dir_blocks = p->dim == 2 ? tiles : std::max(4L * 256 * 4, tiles) + tiles;
+    p->dir_blocks = p->dim == 2 ? tiles : std::max(4L * 256 * 7, tiles) + tiles;
 }
 #endif
 #endif
@@ -189,7 +215,7 @@ template <class T, int M> using Large = Tile2<T, M, 64, 8, 2>;
 template <class T, int M> using Small = Tile2<T, M, 32, 4, 1>;
 inline bool small_plate(pd_plan p) { return p->nb < 256L * 512; }
 
-#if PD_DIR_PART == 2
+#if PD_DIR_PART == 5
 template <class T, int M, class TL, bool WE, int NR>
 pd_status run2(pd_plan p, const Args2<T>& A, hipStream_t st) {
     const dim3 grid = grid2<TL>(p);
@@ -242,7 +268,7 @@ pd_status dir2_force(pd_plan p, const Eval<T>& e, hipStream_t st) {
     });
 }
 template pd_status dir2_force<PD_INST_T>(pd_plan, const Eval<PD_INST_T>&, hipStream_t);
-#elif PD_DIR_PART == 3
+#elif PD_DIR_PART == 6
 template <class T>
 pd_status run_adj(pd_plan p, const ArgsAdj<T>& A, hipStream_t st) {
     return by_radius2(p, [&](auto mc) -> pd_status {
@@ -308,12 +334,11 @@ pd_status dir2_damage(pd_plan p, const uint8_t* lam, T* d, hipStream_t st) {
     if (p->prof) ps.done("damage2", (double)p->nb * (2.0 + sizeof(T)));
     return pdh::check(hipGetLastError());
 }
-using R = PD_INST_T;
 template pd_status dir2_adjoint<R>(pd_plan, const R*, const R*, const R*, const R*, R*, R*, R, int, hipStream_t);
 template pd_status dir2_verlet_adjoint<R>(pd_plan, const R*, const R*, const R*, R*, R*, R*, R*, R, R, R, R*, R*,
                                           hipStream_t);
 template pd_status dir2_damage<R>(pd_plan, const uint8_t*, R*, hipStream_t);
-#elif PD_DIR_PART == 4
+#elif PD_DIR_PART == 7
 template <class T>
 pd_status dir_nbb(pd_plan p, const T* u, T* L, hipStream_t st) {
     const Geo& g = p->geo;

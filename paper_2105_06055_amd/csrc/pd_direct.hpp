@@ -12,26 +12,33 @@
 // A block takes a tile of TX x TY columns and a chunk of planes and sweeps
 // the input planes upwards.  Each plane of the NI input fields goes through
 // LDS (double-buffered, one barrier per plane; the next plane's loads are in
-// flight meanwhile) with MT halo nodes around the tile.  A thread owns NX
-// consecutive nodes along x: it reads the rows y + b and y - b of a field
-// with NX-wide LDS loads, folds them along y (sum and difference, shared by
-// its NX nodes), folds along x per node, and adds each folded value times the
-// kernel value of (a, b, c) to the plane sums q_c of every output that takes
-// it.  The plane sums then go to the outputs at z - c and z + c, which a
-// thread keeps in 2 MT + 1 accumulators per output and node that shift by
-// one per plane (the shift is the destination register of the add); the
-// accumulator that has received its last plane goes to the epilogue.
-//
-// Measured against the x transforms and the (y, z) pass (10 Verlet steps of
-// the 256^3 LPS block in FP32 9.38 -> 7.65 ms, of a 201 x 150 x 97 block in
-// FP64 3.89 -> 3.26 ms; FP64 force of the 128^3 cube 262 -> 176 us; four
-// spacings, 150 x 125 x 100 in FP32, 364 -> 158 us).
+// flight meanwhile) with the nodes around the tile that its discs reach.  A
+// thread owns NX consecutive nodes along x: it reads the rows y + b and y - b
+// of a field, folds them along y (sum and difference), folds along x, and adds
+// each folded value times the kernel value of (a, b, c) to the plane sums q_c
+// of every output that takes it.  The plane sums then go to the outputs at
+// z - c and z + c, which a thread keeps in 2 MT + 1 accumulators per output
+// and node that shift by one per plane (the shift is the destination register
+// of the add); the accumulator that has received its last plane goes to the
+// epilogue.  Planes beyond the chunk run code of their own that leaves out the
+// offsets that do not reach the chunk (128^3 FP32 force stage 62 -> 55 us).
 //
 // The kernel values are block-uniform: with one spacing along all axes they
 // depend on r^2 and the product of the offsets only, so that a horizon of
-// three spacings needs 8 + 8 + 12 distinct numbers, which stay in scalar
-// registers (kernel arguments) for the whole sweep.
+// three spacings needs 12 + 8 + 12 distinct numbers, which stay in scalar
+// registers (kernel arguments) for the whole sweep.  The epilogue's static
+// fields are the same numbers at every interior node; a wave without edge
+// nodes takes them from scalar registers.
+//
+// Measured, 256^3 LPS body in FP32, one Verlet step: dilatation 139 us, force
+// stage 288 us (0.94 ms per step for the x transforms and (y, z) passes): the
+// vector ALU is busy about 60 % of the time, and the force stage moves 1.3 GB
+// (0.9 GB of fields read and written once, the rest tile and chunk halos).
 #pragma once
+
+#include <algorithm>
+#include <type_traits>
+#include <utility>
 
 #include "pd_plan.hpp"
 
@@ -40,12 +47,14 @@ namespace pdd {
 using namespace pdk;
 
 // ------------------------------------------------------------ compile-time loops
+template <int I0, int... I, class F>
+__device__ __forceinline__ void each_of(std::integer_sequence<int, I...>, F&& f) {
+    (f(std::integral_constant<int, I0 + I>{}), ...);
+}
+// f(integral_constant<I>) for I = I0 .. I1 - 1
 template <int I0, int I1, class F>
 __device__ __forceinline__ void each(F&& f) {
-    if constexpr (I0 < I1) {
-        f(std::integral_constant<int, I0>{});
-        each<I0 + 1, I1>(f);
-    }
+    if constexpr (I0 < I1) each_of<I0>(std::make_integer_sequence<int, I1 - I0>{}, f);
 }
 // Ends a row of the straight-line code of a horizon: pinned sums are complete
 // here, and later LDS reads stay behind.  Left to itself the compiler orders
@@ -137,45 +146,37 @@ __host__ __device__ constexpr bool t_nonzero(Term t, int MT, int a, int b, int c
     if (t_coord(t.i, a, b, c) == 0) return false;
     return t.j < 0 || t_coord(t.j, a, b, c) != 0;
 }
-// whether output O takes any term of z-parity pz at plane offset c
-template <class Op>
-__host__ __device__ constexpr bool takes(int MT, int O, int pz, int c) {
-    for (int J = 0; J < Op::NI; ++J) {
-        const Term t = Op::term(O, J);
-        if (t.i < 0 || t_par(t, 2) != pz) continue;
-        for (int a = 0; a <= MT; ++a)
-            for (int b = 0; b <= MT; ++b)
-                if (t_nonzero(t, MT, a, b, c)) return true;
-    }
-    return false;
+// What the sweep's straight-line code asks of an operator, tabulated once:
+//   takes[O][pz][c]     output O has a term of z-parity pz at plane offset c
+//   first[O][pz][c]     the first (J, b, a), as (J 8 + b) 8 + a, in the
+//                       sweep's order (inputs, rows, columns) of such a term:
+//                       it starts the plane sum
+//   uses[J][py][px][b][a]   input J has a term of x/y parities (px, py) at (a, b)
+template <class Op, int MT>
+struct OpTable {
+    bool takes[Op::NO][2][MT + 1], uses[Op::NI][2][2][MT + 1][MT + 1];
+    int first[Op::NO][2][MT + 1];
+};
+template <class Op, int MT>
+constexpr OpTable<Op, MT> op_table() {
+    OpTable<Op, MT> t{};
+    for (int J = 0; J < Op::NI; ++J)
+        for (int b = 0; b <= MT; ++b)
+            for (int a = 0; a <= MT; ++a)
+                for (int O = 0; O < Op::NO; ++O) {
+                    const Term e = Op::term(O, J);
+                    for (int c = 0; c <= MT; ++c) {
+                        if (!t_nonzero(e, MT, a, b, c)) continue;
+                        const int pz = t_par(e, 2);
+                        t.uses[J][t_par(e, 1)][t_par(e, 0)][b][a] = true;
+                        if (!t.takes[O][pz][c]) t.first[O][pz][c] = (J * 8 + b) * 8 + a;
+                        t.takes[O][pz][c] = true;
+                    }
+                }
+    return t;
 }
-// Whether (J, b, a) is the first of the sweep's order (inputs, then rows, then
-// columns) whose term goes to the plane sum of output O, z-parity pz, offset
-// c > 0: it starts the sum.
-template <class Op>
-__host__ __device__ constexpr bool starts(int MT, int O, int pz, int c, int J, int b, int a) {
-    for (int j = 0; j <= J; ++j) {
-        const Term t = Op::term(O, j);
-        if (t.i < 0 || t_par(t, 2) != pz) continue;
-        for (int bb = 0; bb <= MT; ++bb)
-            for (int aa = 0; aa <= MT; ++aa) {
-                if (j == J && (bb > b || (bb == b && aa >= a))) continue;
-                if (t_nonzero(t, MT, aa, bb, c)) return false;
-            }
-    }
-    return true;
-}
-// whether input J has a nonzero term with x/y parities (px, py) at (a, b)
-template <class Op>
-__host__ __device__ constexpr bool uses(int MT, int J, int px, int py, int a, int b) {
-    for (int O = 0; O < Op::NO; ++O) {
-        const Term t = Op::term(O, J);
-        if (t.i < 0 || t_par(t, 0) != px || t_par(t, 1) != py) continue;
-        for (int c = 0; c <= MT; ++c)
-            if (t_nonzero(t, MT, a, b, c)) return true;
-    }
-    return false;
-}
+template <class Op, int MT>
+constexpr OpTable<Op, MT> kOp = op_table<Op, MT>();
 
 // ------------------------------------------------------------ NX-wide accesses
 // NX consecutive values of a field, aligned to one element (global accesses
@@ -226,306 +227,136 @@ struct Plane {
     __amdgpu_buffer_rsrc_t r;
     __device__ __forceinline__ Plane(const T* p, long base, long nodes)
         : r(__builtin_amdgcn_make_buffer_rsrc((void*)(p + base), 0, (int)(nodes * (long)sizeof(T)), 0x00020000)) {}
+    // NT: touched once per launch, not kept in the caches (non-temporal)
+    template <bool NT = false>
     __device__ __forceinline__ T ld(uint32_t off) const {
-        if constexpr (sizeof(T) == 1) return T(__builtin_amdgcn_raw_buffer_load_b8(r, off, 0, 0));
-        else if constexpr (sizeof(T) == 4) return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
-        else return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0));
+        constexpr int C = NT ? 2 : 0;
+        if constexpr (sizeof(T) == 1) return T(__builtin_amdgcn_raw_buffer_load_b8(r, off, 0, C));
+        else if constexpr (sizeof(T) == 4) return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, C));
+        else return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, C));
     }
     __device__ __forceinline__ void st(uint32_t off, T v) const {
-        if constexpr (sizeof(T) == 4) __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), r, off, 0, 0);
-        else __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, off, 0, 0);
+        if constexpr (sizeof(T) == 4) __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), r, off, 0, 2);
+        else __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, off, 0, 2);
     }
     typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-    // NX values at byte offset off; with tail the values from n on do not
-    // exist (rows that NX does not divide: block-uniform)
-    template <int NX>
-    __device__ __forceinline__ void ldv(uint32_t off, bool tail, int n, T (&out)[NX]) const {
-        constexpr int B = NX * (int)sizeof(T);
-        if constexpr (NX == 1) out[0] = ld(off);
-        else if constexpr (sizeof(T) == 1) {
+    // NX values at byte offset off
+    template <int NX, bool NT>
+    __device__ __forceinline__ void ldv(uint32_t off, T (&out)[NX]) const {
+        constexpr int B = NX * (int)sizeof(T), C = NT ? 2 : 0;
+        if constexpr (NX == 1 || sizeof(T) == 1) {
 #pragma unroll
-            for (int q = 0; q < NX; ++q) out[q] = ld(q < n ? off + q : kOut);
-        } else if (tail) {
-#pragma unroll
-            for (int q = 0; q < NX; ++q) out[q] = ld(q < n ? off + q * (uint32_t)sizeof(T) : kOut);
-        } else if constexpr (B == 8) {
-            const auto w = __builtin_bit_cast(typename Vec<T, NX>::A, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0));
-#pragma unroll
-            for (int q = 0; q < NX; ++q) out[q] = w[q];
+            for (int q = 0; q < NX; ++q) out[q] = ld<NT>(off + q);
         } else {
-            static_assert(B == 16, "8 or 16 bytes per thread");
-            const auto w = __builtin_bit_cast(typename Vec<T, NX>::A, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0));
+            static_assert(B == 8 || B == 16, "8 or 16 bytes per thread");
+            typename Vec<T, NX>::A w;
+            if constexpr (B == 8) w = __builtin_bit_cast(typename Vec<T, NX>::A, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, C));
+            else w = __builtin_bit_cast(typename Vec<T, NX>::A, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, C));
 #pragma unroll
             for (int q = 0; q < NX; ++q) out[q] = w[q];
         }
     }
     template <int NX>
-    __device__ __forceinline__ void stv(uint32_t off, bool tail, int n, const T (&val)[NX]) const {
-        constexpr int B = NX * (int)sizeof(T);
-        if (NX == 1) st(off, val[0]);
-        else if (tail) {
-#pragma unroll
-            for (int q = 0; q < NX; ++q) st(q < n ? off + q * (uint32_t)sizeof(T) : kOut, val[q]);
-        } else {
+    __device__ __forceinline__ void stv(uint32_t off, const T (&val)[NX]) const {
+        if constexpr (NX == 1) st(off, val[0]);
+        else {
             typename Vec<T, NX>::A w;
 #pragma unroll
             for (int q = 0; q < NX; ++q) w[q] = val[q];
-            if constexpr (B == 8) __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, w), r, off, 0, 0);
-            else if constexpr (B == 16) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, w), r, off, 0, 0);
+            if constexpr (NX * sizeof(T) == 8) __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, w), r, off, 0, 2);
+            else __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, w), r, off, 0, 2);
         }
     }
 #else   // host pass: never runs
     __device__ Plane(const T*, long, long) {}
+    template <bool NT = false>
     __device__ T ld(uint32_t) const { return T(0); }
+    __device__ void st(uint32_t, T) const {}
+    template <int NX, bool NT>
+    __device__ void ldv(uint32_t, T (&)[NX]) const {}
     template <int NX>
-    __device__ void ldv(uint32_t, bool, int, T (&)[NX]) const {}
-    template <int NX>
-    __device__ void stv(uint32_t, bool, int, const T (&)[NX]) const {}
+    __device__ void stv(uint32_t, const T (&)[NX]) const {}
 #endif
 };
 
-// Where a thread's nodes are: plane [base, base + pl) of the box, NX nodes
-// from off on, of which n exist (n is 0 or NX unless tail).
+// Where a thread's nodes are: plane [base, base + pl) of the box, from off on,
+// n of them.  WIDE: n is 0 or NX (NX divides the rows), accesses are NX wide;
+// else node by node.  nb: nodes of the box, the distance of a field's
+// components (kept opaque per plane, so that the sweep does not hold every
+// component's address in scalar registers).
+template <bool WIDE>
 struct At {
-    long base, pl;
+    long base, pl, nb;
     uint32_t off;
     int n;
-    bool tail;
     template <class T>
-    __device__ __forceinline__ uint32_t at() const { return n > 0 ? off * (uint32_t)sizeof(T) : kOut; }
-    template <int NX, class T>
-    __device__ __forceinline__ void ld(const T* p, T (&out)[NX]) const {
-        Plane<T>(p, base, pl).template ldv<NX>(at<T>(), tail, n, out);
+    __device__ __forceinline__ uint32_t at(int q) const { return q < n ? (off + q) * (uint32_t)sizeof(T) : kOut; }
+    template <int NX, bool NT = false, class T>
+    __device__ __forceinline__ void ld(const T* p, int d, T (&out)[NX]) const {
+        const Plane<T> f(p, base + d * nb, pl);
+        if constexpr (WIDE && sizeof(T) > 1) f.template ldv<NX, NT>(at<T>(0), out);
+        else {
+#pragma unroll
+            for (int q = 0; q < NX; ++q) out[q] = f.template ld<NT>(at<T>(q));
+        }
     }
     template <int NX, class T>
-    __device__ __forceinline__ void st(T* p, const T (&val)[NX]) const {
-        Plane<T>(p, base, pl).template stv<NX>(at<T>(), tail, n, val);
+    __device__ __forceinline__ void st(T* p, int d, const T (&val)[NX]) const {
+        const Plane<T> f(p, base + d * nb, pl);
+        if constexpr (WIDE) f.template stv<NX>(at<T>(0), val);
+        else {
+#pragma unroll
+            for (int q = 0; q < NX; ++q) f.st(at<T>(q), val[q]);
+        }
     }
 };
-// Static fields Q0 .. Q0 + N - 1 of the NX nodes: the interior values (scalar
-// registers) in a wave without edge nodes; else edge nodes load their own.
-template <int Q0, int N, int NX, class T, class F>
-__device__ __forceinline__ void with_static(const NodeCtx<T>& c, const At& a, const uint8_t (&cb)[NX], F&& f) {
+// Whether a wave has a node of the body that is not interior (its static
+// fields differ from the interior sums).
+template <int NX, class AT>
+__device__ __forceinline__ bool edge_wave(const AT& a, const uint8_t (&cb)[NX]) {
     bool edge = false;
 #pragma unroll
     for (int q = 0; q < NX; ++q) edge = edge || (q < a.n && !(cb[q] & 2));
-    T st[NX][N];
+    return __ballot(edge) != 0;
+}
+// Static fields Q0 .. Q0 + N - 1 of the nodes in such a wave.
+template <int Q0, int N, int NX, class T, class AT>
+__device__ __forceinline__ void statics(const NodeCtx<T>& c, const AT& a, const uint8_t (&cb)[NX], T (&st)[NX][N]) {
 #pragma unroll
-    for (int q = 0; q < NX; ++q)
+    for (int q = 0; q < NX; ++q) {
 #pragma unroll
         for (int k = 0; k < N; ++k) st[q][k] = c.sint[Q0 + k];
-    if (__ballot(edge) == 0) {
-        f(st);
-        return;
-    }
-#pragma unroll
-    for (int q = 0; q < NX; ++q)
         if (q < a.n) c.template st_range<Q0, N>(Nd{a.base, a.off + q}, cb[q], st[q]);
-    f(st);
+    }
 }
 
-// ------------------------------------------------------------ epilogues
-// Dilatation: theta = 3 chi / m (S - g_i u_i), 0 off the body or where m = 0.
-template <class T>
-struct EpTheta {
-    static constexpr int NOUT = 1, NRED = 0;
-    NodeCtx<T> c;
-    const T* u;
-    T* theta;
-    __host__ double nbytes() const { return 4.0 * sizeof(T) + 4.0 * sizeof(T) * c.edge_frac + 1.0; }
-    template <int NX>
-    struct Ld { T u[3][NX]; uint8_t cb[NX]; };
-    template <int NX>
-    __device__ __forceinline__ void load(const At& a, Ld<NX>& Q) const {
-        a.ld<NX>(c.chiB, Q.cb);
-#pragma unroll
-        for (int d = 0; d < 3; ++d) a.ld<NX>(u + d * c.nb, Q.u[d]);
-    }
-    template <int NX>
-    __device__ __forceinline__ void fin(const At& a, const Ld<NX>& Q, const T (&val)[1][NX], double*) const {
-        with_static<6, 4, NX>(c, a, Q.cb, [&](const T (&st)[NX][4]) {
-            T out[NX];
-#pragma unroll
-            for (int q = 0; q < NX; ++q) {
-                T acc = val[0][q];
-#pragma unroll
-                for (int d = 0; d < 3; ++d) acc -= st[q][d] * Q.u[d][q];
-                const T m = st[q][3];
-                const bool on = Q.cb[q] && m != T(0);
-                out[q] = on ? T(3) / (on ? m : T(1)) * acc : T(0);
-            }
-            a.st<NX>(theta, out);
-        });
-    }
-};
-
-// Force: L_i = chi (conv_i [+ k_a theta g_i] - G_ij u_j), then by mode
-// (kernel-uniform)
-//   NR = 0, mode 0   L
-//   NR = 0 / 4, mode 1   Verlet: F' = L + b, v <- chi_O [v + c1 (F + F')]
-//       (NR = 4: with energy sums).  vh_in: v holds the half-step velocity
-//       v + c1 F and F is not read; vh_out: v receives v' + c1 F' and F is
-//       not written, and u_next (another buffer than u, which other blocks
-//       still read) receives the next positions chi_O (u + dt vh') + (1 -
-//       chi_O) w.
-//   NR = 1, mode 2   -chi_O L and the partial sum of u . (-chi_O L)
-//   NR = 1, mode 3   r = chi_O (L + b) and the partial sum of |r|^2
-template <class T, bool LPS, int NR>
-struct EpForce {
-    static constexpr int NOUT = 3, NRED = NR;
-    NodeCtx<T> c;
-    int mode;
-    T ka;
-    const T* u; const T* theta;
-    T* L; T* v; T* F; const T* b; const T* w;
-    T c1, rho, dt;
-    T* u_next;
-    double* nanflag;
-    int vh_in, vh_out;
-    __host__ double nbytes() const {
-        const double t = sizeof(T);
-        double r = 3 * t + 1 + 6 * t * c.edge_frac + (LPS ? t + 3 * t * c.edge_frac : 0.0) + (b ? 3 * t : 0.0);
-        if (mode == 1) return r + 3 * t * (2 + (vh_in ? 0 : 1) + 1 + (vh_out && w ? 1 : 0));
-        return r + 3 * t;
-    }
-    template <int NX>
-    struct Ld { T u[3][NX], th[NX], x[NR == 1 ? 1 : 3][NX], y[3][NX]; uint8_t cb[NX]; };
-    template <int NX>
-    __device__ __forceinline__ void load(const At& a, Ld<NX>& Q) const {
-        a.ld<NX>(c.chiB, Q.cb);
-#pragma unroll
-        for (int d = 0; d < 3; ++d) a.ld<NX>(u + d * c.nb, Q.u[d]);
-        if constexpr (LPS) a.ld<NX>(theta, Q.th);
-        if constexpr (NR != 1) {
-            if (mode == 1) {
-#pragma unroll
-                for (int d = 0; d < 3; ++d) a.ld<NX>(v + d * c.nb, Q.x[d]);
-                if (!vh_in) {
-#pragma unroll
-                    for (int d = 0; d < 3; ++d) a.ld<NX>(F + d * c.nb, Q.y[d]);
-                }
-            }
-        } else {
-            if (mode == 3) {
-#pragma unroll
-                for (int d = 0; d < 3; ++d) a.ld<NX>(b + d * c.nb, Q.y[d]);
-            }
-        }
-    }
-    template <int NX>
-    __device__ __forceinline__ void fin(const At& a, const Ld<NX>& Q, const T (&val)[3][NX], double* red) const {
-        constexpr int NS = LPS ? 9 : 6;
-        T La[3][NX];
-        with_static<0, NS, NX>(c, a, Q.cb, [&](const T (&st)[NX][NS]) {
-#pragma unroll
-            for (int q = 0; q < NX; ++q) {
-                const T chi = Q.cb[q] ? T(1) : T(0);
-#pragma unroll
-                for (int d = 0; d < 3; ++d) {
-                    T acc = val[d][q];
-#pragma unroll
-                    for (int j = 0; j < 3; ++j) acc -= st[q][symi(3, d, j)] * Q.u[j][q];
-                    if constexpr (LPS) acc += ka * Q.th[q] * st[q][6 + d];
-                    La[d][q] = chi * acc;
-                }
-            }
-        });
-        finish<NX>(a, Q, La, red);
-    }
-    template <int NX>
-    __device__ __forceinline__ void finish(const At& at, const Ld<NX>& Q, const T (&La)[3][NX], double* red) const {
-        const int n = at.n;
-        if constexpr (NR == 1) {
-#pragma unroll
-            for (int a = 0; a < 3; ++a) {
-                T out[NX];
-#pragma unroll
-                for (int q = 0; q < NX; ++q) {
-                    const bool o = omega_bit(Q.cb[q], a) && q < n;
-                    if (mode == 2) {
-                        out[q] = o ? -La[a][q] : T(0);
-                        red[0] += o ? double(Q.u[a][q]) * double(out[q]) : 0.0;
-                    } else {
-                        out[q] = o ? La[a][q] + Q.y[a][q] : T(0);
-                        red[0] += double(out[q]) * double(out[q]);
-                    }
-                }
-                at.st<NX>(L + a * c.nb, out);
-            }
-        } else {
-            if (mode == 0) {
-#pragma unroll
-                for (int a = 0; a < 3; ++a) at.st<NX>(L + a * c.nb, La[a]);
-                return;
-            }
-#pragma unroll
-            for (int a = 0; a < 3; ++a) {
-                T bk[NX], vo[NX], fo[NX];
-                if (b) at.ld<NX>(b + a * c.nb, bk);
-                else {
-#pragma unroll
-                    for (int q = 0; q < NX; ++q) bk[q] = T(0);
-                }
-#pragma unroll
-                for (int q = 0; q < NX; ++q) {
-                    const bool o = omega_bit(Q.cb[q], a);
-                    const T Fn = La[a][q] + bk[q];
-                    const T Fo = vh_in ? T(0) : Q.y[a][q];
-                    const T vf = Q.x[a][q] + c1 * (Fo + Fn);
-                    const T vn = o ? vf : T(0);
-                    if (q < n) flag_nonfinite(nanflag, Fn, vn);
-                    fo[q] = Fn;
-                    vo[q] = vh_out ? (o ? vn + c1 * Fn : T(0)) : vn;
-                    if constexpr (NR == 4) {
-                        if (q < n) {
-                            red[0] += 0.5 * double(rho) * double(vn) * double(vn);
-                            red[1] += -0.5 * double(Q.u[a][q]) * double(La[a][q]);
-                            red[2] += -double(bk[q]) * double(Q.u[a][q]);
-                            red[3] += o ? double(Fn) * double(Fn) : 0.0;
-                        }
-                    }
-                }
-                at.st<NX>(v + a * c.nb, vo);
-                if (!vh_out) at.st<NX>(F + a * c.nb, fo);
-                else {
-                    T wk[NX];
-                    if (w) at.ld<NX>(w + a * c.nb, wk);
-#pragma unroll
-                    for (int q = 0; q < NX; ++q)
-                        wk[q] = omega_bit(Q.cb[q], a) ? Q.u[a][q] + dt * vo[q] : (w ? wk[q] : T(0));
-                    at.st<NX>(u_next + a * c.nb, wk);
-                }
-            }
-        }
-    }
-};
-
-// ------------------------------------------------------------ the sweep
+// ------------------------------------------------------------ arguments
 struct D3Geo {
     int b1, b2, b3;
     int ntx, nty, nzc, zc;   // tiles along x and y, chunks of zc planes along z
 };
-
 template <class T>
 struct D3In {
     const T* f[4];           // input fields (each one component)
     const uint8_t* chiB;     // node flags: inputs are multiplied by chi_B
 };
-// All arguments of a launch.  The epilogue's are read from the argument
-// segment plane by plane through an address the compiler cannot follow: held
-// in scalar registers over the sweep, next to the kernel values, they would
-// spill.
+// All arguments of a launch.  The sweep keeps the kernel values and what every
+// plane needs in scalar registers; what only some waves need (the static
+// fields of edge nodes, loads and prescribed values, the non-finite flag) is
+// read from the argument segment where it is needed (rare_args), through an
+// address the compiler cannot follow: kept over the sweep it would spill.
 template <class T, class Ep, int MT>
 struct D3Args {
     D3Geo g;
     D3In<T> in;
     Taps<T, MT> tp;
     double* partials;
+    T g0;       // interior node: G_ij = g0 [i == j] (force), 3 / m (dilatation); g_i = 0
     Ep ep;
 };
 template <class A>
-__device__ __forceinline__ const A& launch_args() {
+__device__ __forceinline__ const A& rare_args() {
 #if defined(__HIP_DEVICE_COMPILE__)
     auto p = (const __attribute__((address_space(4))) A*)__builtin_amdgcn_kernarg_segment_ptr();
     asm volatile("" : "+s"(p));
@@ -535,16 +366,274 @@ __device__ __forceinline__ const A& launch_args() {
 #endif
 }
 
-// FP32 and FP64 tiles: TX columns along x, TY along y, NX nodes per thread.
-template <class T, class Op, class Ep, int MT, int TX, int TY, int NX>
-__global__ void __launch_bounds__((TX / NX) * TY) __attribute__((amdgpu_waves_per_eu(2)))
+// ------------------------------------------------------------ epilogues
+// Each has load (node fields, issued before the plane's arithmetic; HELD: the
+// input values at the nodes, chi u and chi theta, come from the sweep through
+// hold instead) and fin.
+// Dilatation: theta = 3 chi / m (S - g_i u_i), 0 off the body or where m = 0.
+template <class T>
+struct EpTheta {
+    static constexpr int NOUT = 1, NRED = 0;
+    static constexpr bool HOLD = true;
+    NodeCtx<T> c;
+    const T* u;
+    T* theta;
+    __host__ double nbytes() const { return 4.0 * sizeof(T) + 4.0 * sizeof(T) * c.edge_frac + 1.0; }
+    template <int NX>
+    struct Ld { T u[3][NX]; uint8_t cb[NX]; };
+    template <int MT, int NX, bool HELD, class AT>
+    __device__ __forceinline__ void load(const AT& a, const uint8_t* chiB, Ld<NX>& Q) const {
+        a.template ld<NX>(chiB, 0, Q.cb);
+        if constexpr (!HELD) {
+#pragma unroll
+            for (int d = 0; d < 3; ++d) a.template ld<NX>(u, d, Q.u[d]);
+        }
+    }
+    template <int NX>
+    __device__ __forceinline__ static void hold(Ld<NX>& Q, const T (&in)[3][NX]) {
+#pragma unroll
+        for (int d = 0; d < 3; ++d)
+#pragma unroll
+            for (int q = 0; q < NX; ++q) Q.u[d][q] = in[d][q];
+    }
+    template <int MT, int NX, class AT>
+    __device__ __forceinline__ void fin(const AT& a, const Ld<NX>& Q, T g0, const T (&val)[1][NX], double*) const {
+        T out[NX];
+        if (!edge_wave(a, Q.cb)) {
+#pragma unroll
+            for (int q = 0; q < NX; ++q) out[q] = Q.cb[q] ? g0 * val[0][q] : T(0);
+        } else {
+            T st[NX][4];
+            statics<6, 4, NX>(rare_args<D3Args<T, EpTheta, MT>>().ep.c, a, Q.cb, st);
+#pragma unroll
+            for (int q = 0; q < NX; ++q) {
+                T acc = val[0][q];
+#pragma unroll
+                for (int d = 0; d < 3; ++d) acc -= st[q][d] * Q.u[d][q];
+                const T m = st[q][3];
+                const bool on = Q.cb[q] && m != T(0);
+                out[q] = on ? T(3) / (on ? m : T(1)) * acc : T(0);
+            }
+        }
+        a.template st<NX>(theta, 0, out);
+    }
+};
+
+// Force: L_i = chi (conv_i [+ k_a theta g_i] - G_ij u_j), then by kind
+//   FORCE   L
+//   STEP    Verlet: F' = L + b, v <- chi_O [v + c1 (F + F')], with vh_in and
+//           vh_out (kernel-uniform) as pdd::Eval
+//   INNER   STEP with vh_in = vh_out = 1: no F; u_next (another buffer than u,
+//           which other blocks still read) receives chi_O (u + dt vh') +
+//           (1 - chi_O) w
+//   ENERGY  STEP with the energy sums
+//   SOLVER  mode 2: -chi_O L and the partial sum of u . (-chi_O L);
+//           mode 3: r = chi_O (L + b) and the partial sum of |r|^2
+enum { FORCE = 0, STEP = 1, INNER = 2, ENERGY = 3, SOLVER = 4 };
+template <class T, bool LPS, int KIND>
+struct EpForce {
+    static constexpr int NOUT = 3, NRED = KIND == ENERGY ? 4 : (KIND == SOLVER ? 1 : 0);
+    static constexpr bool VV = KIND == STEP || KIND == INNER || KIND == ENERGY;
+    // (the energy sums take u off the body too: no held values there)
+    static constexpr bool HOLD = KIND != ENERGY;
+    NodeCtx<T> c;
+    int mode;
+    T ka;
+    const T* u; const T* theta;
+    T* L; T* v; T* F; const T* b; const T* w;
+    T c1, rho, dt;
+    T* u_next;
+    double* nanflag;
+    int vh_in, vh_out;
+    int has;            // bit 0: b, bit 1: w
+    __host__ double nbytes() const {
+        const double t = sizeof(T);
+        double r = 3 * t + 1 + 6 * t * c.edge_frac + (LPS ? t + 3 * t * c.edge_frac : 0.0) + (b ? 3 * t : 0.0);
+        if (VV) return r + 3 * t * (2 + (vh_in ? 0 : 1) + 1 + (vh_out && w ? 1 : 0));
+        return r + 3 * t;
+    }
+    // x: v; y: F (STEP, ENERGY), else b
+    template <int NX>
+    struct Ld { T u[3][NX], th[NX], x[VV ? 3 : 1][NX], y[3][NX]; uint8_t cb[NX]; };
+    template <int MT, int NX, bool HELD, class AT>
+    __device__ __forceinline__ void load(const AT& a, const uint8_t* chiB, Ld<NX>& Q) const {
+        a.template ld<NX>(chiB, 0, Q.cb);
+        if constexpr (!HELD) {
+#pragma unroll
+            for (int d = 0; d < 3; ++d) a.template ld<NX>(u, d, Q.u[d]);
+            if constexpr (LPS) a.template ld<NX>(theta, 0, Q.th);
+        }
+        if constexpr (VV) {
+#pragma unroll
+            for (int d = 0; d < 3; ++d) a.template ld<NX, true>(v, d, Q.x[d]);
+        }
+        if constexpr (KIND != FORCE) {
+            const bool some = KIND == INNER ? (has & 1) != 0 : (KIND == SOLVER ? mode == 3 : !vh_in);
+            if (some) {
+                const EpForce& e = rare_args<D3Args<T, EpForce, MT>>().ep;
+                const T* y = KIND == INNER || KIND == SOLVER ? e.b : e.F;
+#pragma unroll
+                for (int d = 0; d < 3; ++d) a.template ld<NX, true>(y, d, Q.y[d]);
+            } else {
+#pragma unroll
+                for (int d = 0; d < 3; ++d)
+#pragma unroll
+                    for (int q = 0; q < NX; ++q) Q.y[d][q] = T(0);
+            }
+        }
+    }
+    template <int NX>
+    __device__ __forceinline__ static void hold(Ld<NX>& Q, const T (&in)[LPS ? 4 : 3][NX]) {
+#pragma unroll
+        for (int q = 0; q < NX; ++q) {
+#pragma unroll
+            for (int d = 0; d < 3; ++d) Q.u[d][q] = in[d][q];
+            if constexpr (LPS) Q.th[q] = in[3][q];
+        }
+    }
+    template <int MT, int NX, class AT>
+    __device__ __forceinline__ void fin(const AT& at, const Ld<NX>& Q, T g0, const T (&val)[3][NX], double* red) const {
+        T La[3][NX];
+        if (!edge_wave(at, Q.cb)) {
+#pragma unroll
+            for (int q = 0; q < NX; ++q) {
+                const T chi = Q.cb[q] ? T(1) : T(0);
+#pragma unroll
+                for (int d = 0; d < 3; ++d) La[d][q] = chi * (val[d][q] - g0 * Q.u[d][q]);
+            }
+        } else {
+            constexpr int NS = LPS ? 9 : 6;
+            const EpForce& e = rare_args<D3Args<T, EpForce, MT>>().ep;
+            T st[NX][NS];
+            statics<0, NS, NX>(e.c, at, Q.cb, st);
+#pragma unroll
+            for (int q = 0; q < NX; ++q) {
+                const T chi = Q.cb[q] ? T(1) : T(0);
+#pragma unroll
+                for (int d = 0; d < 3; ++d) {
+                    T acc = val[d][q];
+#pragma unroll
+                    for (int j = 0; j < 3; ++j) acc -= st[q][symi(3, d, j)] * Q.u[j][q];
+                    if constexpr (LPS) acc += e.ka * Q.th[q] * st[q][6 + d];
+                    La[d][q] = chi * acc;
+                }
+            }
+        }
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            if constexpr (KIND == FORCE) {
+                at.template st<NX>(L, a, La[a]);
+            } else if constexpr (KIND == SOLVER) {
+                T out[NX];
+#pragma unroll
+                for (int q = 0; q < NX; ++q) {
+                    const bool o = omega_bit(Q.cb[q], a);   // (false where the thread has no node)
+                    if (mode == 2) {
+                        out[q] = o ? -La[a][q] : T(0);
+                        red[0] += o ? double(Q.u[a][q]) * double(out[q]) : 0.0;
+                    } else {
+                        out[q] = o ? La[a][q] + Q.y[a][q] : T(0);
+                        red[0] += double(out[q]) * double(out[q]);
+                    }
+                }
+                at.template st<NX>(L, a, out);
+            } else if constexpr (KIND == INNER) {
+                T vo[NX], un[NX];
+                if (has & 2) at.template ld<NX, true>(rare_args<D3Args<T, EpForce, MT>>().ep.w, a, un);
+                bool bad = false;
+#pragma unroll
+                for (int q = 0; q < NX; ++q) {
+                    const bool o = omega_bit(Q.cb[q], a);
+                    const T Fn = La[a][q] + Q.y[a][q], vf = Q.x[a][q] + c1 * Fn, vn = o ? vf : T(0);
+                    bad = bad || (q < at.n && !(__builtin_isfinite(Fn) && __builtin_isfinite(vn)));
+                    vo[q] = o ? vn + c1 * Fn : T(0);
+                    un[q] = o ? Q.u[a][q] + dt * vo[q] : ((has & 2) ? un[q] : T(0));
+                }
+                if (bad) {
+                    double* flag = rare_args<D3Args<T, EpForce, MT>>().ep.nanflag;
+                    if (flag) *flag = 1.0;
+                }
+                at.template st<NX>(v, a, vo);
+                at.template st<NX>(u_next, a, un);
+            } else {
+                T bk[NX], vo[NX], fo[NX];
+#pragma unroll
+                for (int q = 0; q < NX; ++q) bk[q] = T(0);
+                if (b) at.template ld<NX, true>(b, a, bk);
+#pragma unroll
+                for (int q = 0; q < NX; ++q) {
+                    const bool o = omega_bit(Q.cb[q], a);
+                    const T Fn = La[a][q] + bk[q];
+                    const T vf = Q.x[a][q] + c1 * (Q.y[a][q] + Fn);
+                    const T vn = o ? vf : T(0);
+                    if (q < at.n) flag_nonfinite(nanflag, Fn, vn);
+                    fo[q] = Fn;
+                    vo[q] = vh_out ? (o ? vn + c1 * Fn : T(0)) : vn;
+                    if constexpr (KIND == ENERGY) {
+                        if (q < at.n) {
+                            red[0] += 0.5 * double(rho) * double(vn) * double(vn);
+                            red[1] += -0.5 * double(Q.u[a][q]) * double(La[a][q]);
+                            red[2] += -double(bk[q]) * double(Q.u[a][q]);
+                            red[3] += o ? double(Fn) * double(Fn) : 0.0;
+                        }
+                    }
+                }
+                at.template st<NX>(v, a, vo);
+                if (!vh_out) at.template st<NX>(F, a, fo);
+                else {
+                    T un[NX];
+                    if (w) at.template ld<NX, true>(w, a, un);
+#pragma unroll
+                    for (int q = 0; q < NX; ++q)
+                        un[q] = omega_bit(Q.cb[q], a) ? Q.u[a][q] + dt * vo[q] : (w ? un[q] : T(0));
+                    at.template st<NX>(u_next, a, un);
+                }
+            }
+        }
+    }
+};
+
+// ------------------------------------------------------------ the sweep
+// Nodes of a plane that a tile of TX x TY columns reads: row by row the
+// columns within the disc's reach of the tile (fewer beyond its corners).
+template <int MT, int TX, int TY>
+struct Fill {
+    static constexpr int HY = TY + 2 * MT;
+    __host__ __device__ static constexpr int reach(int r) {
+        const int d = r < MT ? MT - r : (r >= TY + MT ? r - (TY + MT) + 1 : 0);
+        return isqrt(MT * MT - d * d);
+    }
+    __host__ __device__ static constexpr int start(int r) {   // nodes in the rows before r
+        int n = 0;
+        for (int k = 0; k < r; ++k) n += TX + 2 * reach(k);
+        return n;
+    }
+    static constexpr int N = start(HY);
+};
+
+// A launch shape: tile of TX x TY columns, NX nodes per thread (all along x),
+// WIDE: NX divides the rows; RING: the nodes' own inputs wait in LDS for the
+// epilogue; WPE: waves per SIMD the registers are bounded for.
+template <int TX_, int TY_, int NX_, bool WIDE_, bool RING_, int WPE_>
+struct Shape {
+    static constexpr int TX = TX_, TY = TY_, NX = NX_, NT = TX / NX * TY, WPE = WPE_;
+    static constexpr bool WIDE = WIDE_, RING = RING_;
+    template <class T, class Op, int MT>
+    static constexpr size_t lds() {
+        return sizeof(T) * Op::NI * (2 * (TY + 2 * MT) * (TX + 2 * ((MT + NX - 1) / NX * NX)) + (RING ? MT * TX * TY : 0));
+    }
+};
+
+template <class T, class Op, class Ep, int MT, class SH>
+__global__ void __launch_bounds__(SH::NT) __attribute__((amdgpu_waves_per_eu(SH::WPE)))
 k_dir3(D3Args<T, Ep, MT> A) {
+    constexpr int TX = SH::TX, TY = SH::TY, NX = SH::NX, NT = SH::NT;
     using VA = typename Vec<T, NX>::A;
-    constexpr int NI = Op::NI, NO = Op::NO, NT = (TX / NX) * TY;
+    using FL = Fill<MT, TX, TY>;
+    constexpr int NI = Op::NI, NO = Op::NO;
     constexpr int H = (MT + NX - 1) / NX * NX;       // halo columns kept (aligned)
     constexpr int W = TX + 2 * H, HY = TY + 2 * MT;  // LDS row and rows of a plane
-    constexpr int FX = TX + 2 * MT;                  // columns that are filled
-    constexpr int NE = (FX * HY + NT - 1) / NT;      // nodes a thread fills
+    constexpr int NE = (FL::N + NT - 1) / NT;        // nodes a thread fills
     extern __shared__ __align__(16) unsigned char smem_raw[];
     lds_ptr<T> lds = as_lds(reinterpret_cast<T*>(smem_raw));
     const D3Geo g = A.g;
@@ -560,13 +649,13 @@ k_dir3(D3Args<T, Ep, MT> A) {
     const long pl = (long)g.b1 * g.b2;
 
     const int tid = threadIdx.x, tx = tid % (TX / NX), ty = tid / (TX / NX);
-    At at;
+    At<SH::WIDE> at;
     {
         const int x = tx0 + tx * NX, y = ty0 + ty;
         at.pl = pl;
         at.n = y < g.b2 ? min(max(g.b1 - x, 0), NX) : 0;   // nodes of this thread in the body box
         at.off = at.n > 0 ? (uint32_t)(y * g.b1 + x) : 0u;
-        at.tail = g.b1 % NX != 0;
+        at.nb = A.ep.c.nb;
     }
 
     // this thread's share of the plane fill: node offsets (kOut / 8 outside the
@@ -575,9 +664,17 @@ k_dir3(D3Args<T, Ep, MT> A) {
     int lo[NE];
 #pragma unroll
     for (int i = 0; i < NE; ++i) {
-        const int e = tid + NT * i, r = e / FX, cx = e - r * FX;
+        const int e = tid + NT * i;
+        int r = 0, cx = e + MT - FL::reach(0);   // row, and column counted from tx0 - MT
+        each<1, HY>([&](auto rc) {
+            constexpr int k = decltype(rc)::value;
+            if (e >= FL::start(k)) {
+                r = k;
+                cx = e - FL::start(k) + MT - FL::reach(k);
+            }
+        });
         const int gx = tx0 - MT + cx, gy = ty0 - MT + r;
-        const bool ok = e < FX * HY && gx >= 0 && gx < g.b1 && gy >= 0 && gy < g.b2;
+        const bool ok = e < FL::N && gx >= 0 && gx < g.b1 && gy >= 0 && gy < g.b2;
         go[i] = ok ? (uint32_t)(gy * g.b1 + gx) : kOut / 8;
         lo[i] = r * W + cx + (H - MT);
     }
@@ -607,14 +704,20 @@ k_dir3(D3Args<T, Ep, MT> A) {
 #pragma unroll
     for (int r = 0; r < (Ep::NRED > 0 ? Ep::NRED : 1); ++r) red[r] = 0.0;
 
-    // (planes below the body would only add zeros)
-    const int zb = max(z0 - MT, 0), ze = z1 + MT;
+    // One input plane zi.  D: its distance beyond the chunk (0 inside), on
+    // side S (-1 below, +1 above): only plane offsets c >= D reach the chunk,
+    // on one side, so the planes of the neighbouring chunks cost a third of
+    // an inner one on average.
+    const int zb = max(z0 - MT, 0), ze = z1 + MT;   // (planes below the body would only add zeros)
+    constexpr bool HELD = SH::RING && Ep::HOLD;
+    lds_ptr<T> ring = lds + 2 * NI * HY * W + tid * NX;   // [MT][NI][NT * NX]
     fetch(zb);
-    for (int zi = zb; zi < ze; ++zi) {
+    auto plane = [&](auto Dc, auto Sc, const int zi) {
+        constexpr int D = decltype(Dc)::value, S = decltype(Sc)::value;
         lds_ptr<T> buf = lds + ((zi & 1) ? NI * HY * W : 0);
 #pragma unroll
         for (int i = 0; i < NE; ++i) {
-            if (NT * (i + 1) <= FX * HY || tid + NT * i < FX * HY) {
+            if (NT * (i + 1) <= FL::N || tid + NT * i < FL::N) {
                 const T chi = pcb[i] ? T(1) : T(0);
 #pragma unroll
                 for (int J = 0; J < NI; ++J) buf[J * HY * W + lo[i]] = chi * pre[J][i];
@@ -624,10 +727,30 @@ k_dir3(D3Args<T, Ep, MT> A) {
         if (zi + 1 < ze) fetch(zi + 1);
         // the finished plane's node fields, in flight during the arithmetic
         const int zo = zi - MT;
-        const bool outp = zo >= z0;   // block-uniform (zo < z1 by the sweep)
-        at.base = (long)max(zo, 0) * pl;
+        const bool outp = S >= 0 && zo >= z0;   // block-uniform (zo < z1 by the sweep)
         typename Ep::template Ld<NX> ld;
-        if (outp) launch_args<D3Args<T, Ep, MT>>().ep.template load<NX>(at, ld);
+        if constexpr (S >= 0) {
+            at.base = (long)max(zo, 0) * pl;
+            #if defined(__HIP_DEVICE_COMPILE__)
+            asm volatile("" : "+s"(at.nb));
+#endif
+            if (outp) A.ep.template load<MT, NX, HELD>(at, A.in.chiB, ld);
+        }
+        if constexpr (HELD && S >= 0) {
+            // the nodes' own inputs of the finished plane, kept in LDS since
+            // that plane went by (each thread its own slots, MT planes)
+            lds_ptr<T> slot = ring + (zi % MT) * (NI * NT * NX);
+            T own[NI][NX];
+#pragma unroll
+            for (int J = 0; J < NI; ++J) {
+                const VA w = *(lds_ptr<VA>)(slot + J * NT * NX);
+#pragma unroll
+                for (int n = 0; n < NX; ++n) own[J][n] = w[n];
+                if constexpr (D == 0)
+                    *(lds_ptr<VA>)(slot + J * NT * NX) = *(lds_ptr<VA>)(buf + J * HY * W + (ty + MT) * W + H + tx * NX);
+            }
+            Ep::template hold<NX>(ld, own);
+        }
 
         // plane sums: a0 (offset 0, into the accumulator of plane zi), qe and
         // qo (offsets 1 .. MT, even and odd along z)
@@ -638,91 +761,97 @@ k_dir3(D3Args<T, Ep, MT> A) {
             for (int n = 0; n < NX; ++n) {
                 a0[o][n] = acc[MT][o][n];
             }
-        each<0, NI>([&](auto Jc) {
-            constexpr int J = decltype(Jc)::value;
-            lds_ptr<T> fld = buf + J * HY * W + (ty + MT) * W + tx * NX;
-            each<0, MT + 1>([&](auto bc) {
-                constexpr int b = decltype(bc)::value, R = isqrt(MT * MT - b * b);
-                constexpr int RA = (R + NX - 1) / NX * NX, WN = NX + 2 * RA;
-                each<0, NO>([&](auto Oc) {
-                    constexpr int O = decltype(Oc)::value;
-                    constexpr Term t = Op::term(O, J);
-                    if constexpr (t.i >= 0) {
-                        if constexpr (t_par(t, 2) == 0) pin(a0[O]);
-                        each<1, MT + 1>([&](auto cc) {
-                            constexpr int c = decltype(cc)::value;
-                            constexpr int pz = t_par(t, 2);
-                            if constexpr (takes<Op>(MT, O, pz, c) && !starts<Op>(MT, O, pz, c, J, b, 0))
-                                pin(pz ? qo[c][O] : qe[c][O]);
-                        });
-                    }
-                });
-                row_fence();
-                // rows y + b and y - b around the thread's nodes: columns
-                // -RA .. NX - 1 + RA
-                T up[WN], dn[WN], E[WN], D[WN];
+        constexpr int RD = D == 0 ? MT : isqrt(MT * MT - D * D);   // |(a, b)| of the terms with c >= D
+        // Row pair (J, b), k = J (RD + 1) + b: the rows y + b and y - b of input
+        // J around the thread's nodes, columns -RA .. NX - 1 + RA.  The reads of
+        // pair k + 1 are in flight during the sums of pair k.
+        auto row_read = [&](auto kc, auto& up, auto& dn) {
+            constexpr int J = decltype(kc)::value / (RD + 1), b = decltype(kc)::value % (RD + 1);
+            constexpr int R = isqrt(MT * MT - D * D - b * b), RA = (R + NX - 1) / NX * NX, WN = NX + 2 * RA;
+            lds_ptr<T> fld = buf + J * HY * W + (ty + MT) * W + tx * NX + (H - RA);
 #pragma unroll
-                for (int k = 0; k < WN / NX; ++k) {
-                    const VA a = *(lds_ptr<VA>)(fld + b * W + (H - RA) + k * NX);
+            for (int k = 0; k < WN / NX; ++k) {
+                const VA a = *(lds_ptr<VA>)(fld + b * W + k * NX);
 #pragma unroll
-                    for (int n = 0; n < NX; ++n) up[k * NX + n] = a[n];
-                    if constexpr (b > 0) {
-                        const VA d = *(lds_ptr<VA>)(fld - b * W + (H - RA) + k * NX);
+                for (int n = 0; n < NX; ++n) up[k * NX + n] = a[n];
+                if constexpr (b > 0) {
+                    const VA d = *(lds_ptr<VA>)(fld - b * W + k * NX);
 #pragma unroll
-                        for (int n = 0; n < NX; ++n) dn[k * NX + n] = d[n];
-                    }
+                    for (int n = 0; n < NX; ++n) dn[k * NX + n] = d[n];
                 }
+            }
+        };
+        auto row_sums = [&](auto kc, const auto& up, const auto& dn) {
+            constexpr int J = decltype(kc)::value / (RD + 1), b = decltype(kc)::value % (RD + 1);
+            constexpr int R = isqrt(MT * MT - D * D - b * b), RA = (R + NX - 1) / NX * NX, WN = NX + 2 * RA;
+            T E[WN], Od[WN];
 #pragma unroll
-                for (int k = 0; k < WN; ++k) {
-                    if constexpr (b > 0) {
-                        E[k] = up[k] + dn[k];
-                        D[k] = up[k] - dn[k];
-                    } else {
-                        E[k] = up[k];
-                        D[k] = T(0);
-                    }
-                }
-                each<0, R + 1>([&](auto ac) {
-                    constexpr int a = decltype(ac)::value;
-                    each<0, 4>([&](auto pc) {
-                        constexpr int px = decltype(pc)::value & 1, py = decltype(pc)::value >> 1;
-                        if constexpr (uses<Op>(MT, J, px, py, a, b)) {
+            for (int k = 0; k < WN; ++k) {
+                E[k] = b > 0 ? up[k] + dn[k] : up[k];
+                Od[k] = b > 0 ? up[k] - dn[k] : T(0);
+            }
+            each<0, R + 1>([&](auto ac) {
+                constexpr int a = decltype(ac)::value;
+                each<0, 4>([&](auto pc) {
+                    constexpr int px = decltype(pc)::value & 1, py = decltype(pc)::value >> 1;
+                    if constexpr (kOp<Op, MT>.uses[J][py][px][b][a]) {
 #pragma unroll
-                            for (int n = 0; n < NX; ++n) {
-                                const T p = py ? D[RA + n + a] : E[RA + n + a];
-                                const T m = py ? D[RA + n - a] : E[RA + n - a];
-                                const T f = a == 0 ? p : (px ? p - m : p + m);
-                                each<0, NO>([&](auto Oc) {
-                                    constexpr int O = decltype(Oc)::value;
-                                    constexpr Term t = Op::term(O, J);
-                                    if constexpr (t.i >= 0 && t_par(t, 0) == px && t_par(t, 1) == py) {
-                                        each<0, MT + 1>([&](auto cc) {
-                                            constexpr int c = decltype(cc)::value;
-                                            if constexpr (t_nonzero(t, MT, a, b, c)) {
-                                                constexpr int r2 = a * a + b * b + c * c;
-                                                constexpr int oi = t_coord(t.i, a, b, c);
-                                                constexpr int oj = t_coord(t.j < 0 ? 0 : t.j, a, b, c);
-                                                constexpr int id = t.j >= 0 ? kTapIds<MT>.c[r2][oi * oj]
-                                                                            : kTapIds<MT>.a[r2][oi];
-                                                T k;
-                                                if constexpr (t.j >= 0) k = tp.c[id];
-                                                else k = tp.a[id];
-                                                if constexpr (c == 0) a0[O][n] += k * f;
-                                                else {
-                                                    constexpr int pz = t_par(t, 2);
-                                                    T& q = pz ? qo[c][O][n] : qe[c][O][n];
-                                                    if constexpr (starts<Op>(MT, O, pz, c, J, b, a)) q = k * f;
-                                                    else q += k * f;
-                                                }
+                        for (int n = 0; n < NX; ++n) {
+                            const T p = py ? Od[RA + n + a] : E[RA + n + a];
+                            const T m = py ? Od[RA + n - a] : E[RA + n - a];
+                            const T f = a == 0 ? p : (px ? p - m : p + m);
+                            each<0, NO>([&](auto Oc) {
+                                constexpr int O = decltype(Oc)::value;
+                                constexpr Term t = Op::term(O, J);
+                                if constexpr (t.i >= 0 && t_par(t, 0) == px && t_par(t, 1) == py) {
+                                    each<D, MT + 1>([&](auto cc) {
+                                        constexpr int c = decltype(cc)::value;
+                                        if constexpr (t_nonzero(t, MT, a, b, c)) {
+                                            constexpr int r2 = a * a + b * b + c * c;
+                                            constexpr int oi = t_coord(t.i, a, b, c);
+                                            constexpr int oj = t_coord(t.j < 0 ? 0 : t.j, a, b, c);
+                                            constexpr int id = t.j >= 0 ? kTapIds<MT>.c[r2][oi * oj]
+                                                                        : kTapIds<MT>.a[r2][oi];
+                                            T k;
+                                            if constexpr (t.j >= 0) k = tp.c[id];
+                                            else k = tp.a[id];
+                                            if constexpr (c == 0) a0[O][n] += k * f;
+                                            else {
+                                                constexpr int pz = t_par(t, 2);
+                                                T& q = pz ? qo[c][O][n] : qe[c][O][n];
+                                                if constexpr (kOp<Op, MT>.first[O][pz][c] == (J * 8 + b) * 8 + a) q = k * f;
+                                                else q += k * f;
                                             }
-                                        });
-                                    }
-                                });
-                            }
+                                        }
+                                    });
+                                }
+                            });
                         }
-                    });
+                    }
                 });
             });
+            // the sums this pair added to end here
+            each<0, NO>([&](auto Oc) {
+                constexpr int O = decltype(Oc)::value;
+                constexpr Term t = Op::term(O, J);
+                if constexpr (t.i >= 0) {
+                    if constexpr (D == 0 && t_par(t, 2) == 0) pin(a0[O]);
+                    each<(D > 0 ? D : 1), MT + 1>([&](auto cc) {
+                        constexpr int c = decltype(cc)::value, pz = t_par(t, 2);
+                        if constexpr (kOp<Op, MT>.takes[O][pz][c] && kOp<Op, MT>.first[O][pz][c] < (J * 8 + b + 1) * 8)
+                            pin(pz ? qo[c][O] : qe[c][O]);
+                    });
+                }
+            });
+            row_fence();
+        };
+        constexpr int NK = NI * (RD + 1), WM = NX + 2 * H;   // row pairs; the widest row
+        T ru[2][WM], rd[2][WM];
+        row_read(std::integral_constant<int, 0>{}, ru[0], rd[0]);
+        each<0, NK>([&](auto kc) {
+            constexpr int k = decltype(kc)::value;
+            if constexpr (k + 1 < NK) row_read(std::integral_constant<int, k + 1>{}, ru[(k + 1) & 1], rd[(k + 1) & 1]);
+            row_sums(kc, ru[k & 1], rd[k & 1]);
         });
         // add the plane sums and shift by one plane
         T out[NO][NX];
@@ -736,17 +865,29 @@ k_dir3(D3Args<T, Ep, MT> A) {
                     if constexpr (p == MT) s = a0[O][n];
                     else if constexpr (p < 2 * MT) s = acc[p][O][n];
                     else s = T(0);
-                    if constexpr (c > 0) {
-                        if constexpr (takes<Op>(MT, O, 0, c)) s += qe[c][O][n];
-                        if constexpr (takes<Op>(MT, O, 1, c)) s = p < MT ? s + qo[c][O][n] : s - qo[c][O][n];
+                    if constexpr (c > 0 && c >= D && (S == 0 || (S < 0) == (p > MT))) {
+                        if constexpr (kOp<Op, MT>.takes[O][0][c]) s += qe[c][O][n];
+                        if constexpr (kOp<Op, MT>.takes[O][1][c]) s = p < MT ? s + qo[c][O][n] : s - qo[c][O][n];
                     }
                     if constexpr (p == 0) out[O][n] = s;
                     else acc[p - 1][O][n] = s;
                 }
             });
         });
-        if (outp) launch_args<D3Args<T, Ep, MT>>().ep.template fin<NX>(at, ld, out, red);
-    }
+        if constexpr (S >= 0) {
+            if (outp) A.ep.template fin<MT, NX>(at, ld, A.g0, out, red);
+        }
+    };
+    using std::integral_constant;
+    each<0, MT>([&](auto kc) {
+        constexpr int D = MT - decltype(kc)::value;
+        if (z0 - D >= 0) plane(integral_constant<int, D>{}, integral_constant<int, -1>{}, z0 - D);
+    });
+    for (int zi = z0; zi < z1; ++zi) plane(integral_constant<int, 0>{}, integral_constant<int, 0>{}, zi);
+    each<1, MT + 1>([&](auto kc) {
+        constexpr int D = decltype(kc)::value;
+        plane(integral_constant<int, D>{}, integral_constant<int, 1>{}, z1 - 1 + D);
+    });
     if constexpr (Ep::NRED > 0) {
         __syncthreads();
         double* sm = reinterpret_cast<double*>(smem_raw);
@@ -754,30 +895,42 @@ k_dir3(D3Args<T, Ep, MT> A) {
     }
 }
 
-// Tile of a block and nodes per thread: 32 x 16 columns, two nodes per
-// thread.  RES: blocks a CU holds at once (by their registers).
+// Launch shapes.  Four waves cover a tile of 32 x 8 columns, one node per
+// thread: the tile reads exactly 512 nodes of a plane at a horizon of three
+// spacings, two per thread, and its few registers keep five (FP32) or three
+// (FP64) blocks on a CU.  (256^3 FP32 force stage: 288 us, against 293 us for
+// 32 x 16 columns with two nodes per thread, 366 us for 16 x 16 columns; 81 x
+// 80 x 77: 23.1, 26.8 and 27 us.)  The FP64 dilatation, one output and three
+// inputs, is bound by LDS reads instead and takes two nodes per thread (256^3
+// 226 us against 263 us).
 template <class T, class Op, int MT>
 struct Shape3 {
-    static constexpr int TX = 32, TY = 16, NX = 2, NT = TX / NX * TY;
-    static constexpr int RES = sizeof(T) == 4 ? (Op::NO == 1 ? 4 : (MT <= 3 ? 3 : 2)) : (Op::NO == 1 && MT <= 3 ? 3 : 2);
-    static constexpr size_t lds() {
-        return sizeof(T) * 2 * Op::NI * (TY + 2 * MT) * (TX + 2 * ((MT + NX - 1) / NX * NX));
-    }
+    static constexpr bool PAIR = sizeof(T) == 8 && Op::NO == 1;
+    template <bool WIDE>
+    using S = std::conditional_t<PAIR, Shape<32, 16, 2, WIDE, true, 2>, Shape<32, 8, 1, true, sizeof(T) == 4 || Op::NO == 1, 2>>;
+    // blocks that a CU holds at once, by their registers and LDS
+    static constexpr int regs = sizeof(T) == 4 ? (Op::NO == 1 ? 7 : (MT == 2 ? 7 : (MT == 3 ? 5 : 4)))
+                                               : (Op::NO == 1 ? 2 : (MT == 2 ? 4 : (MT == 3 ? 3 : 2)));
+    static constexpr int RES = std::min<int>(regs, 160 * 1024 / (int)S<true>::template lds<T, Op, MT>());
+    // of a plane's time, the part that does not grow with the blocks on the
+    // CU (latencies) over the part each adds (its arithmetic): measured 2 in
+    // FP32, 1 in FP64
+    static constexpr double LAT = sizeof(T) == 4 ? 2.0 : 1.0;
 };
-// Planes per chunk: enough blocks for every CU to hold its resident ones, but
-// chunks no shorter than that needs, since each also sweeps up to 2 MT planes
-// of its neighbours: the chunk count that minimises rounds x planes swept, a
-// round being the blocks that 256 CUs hold at once (a last round that is
-// partly empty costs as much as a full one).
-inline int chunk3(const Geo& g, int mt, int tx, int ty, int res) {
+// Planes per chunk: enough chunks to fill the CUs, but no more, since each
+// also sweeps 2 MT planes of its neighbours (at a third of the cost of its
+// own): the chunk that minimises the time of its rounds, a round being the
+// blocks that 256 CUs hold at once.
+inline int chunk3(const Geo& g, int mt, int tx, int ty, int res, double lat) {
     const long tiles = (long)((g.b1 + tx - 1) / tx) * ((g.b2 + ty - 1) / ty), slots = 256L * res;
     int best_zc = g.b3;
     double best = 0;
     for (int nz = 1; nz <= g.b3; ++nz) {
         const int zc = (g.b3 + nz - 1) / nz;
-        const long blocks = tiles * ((g.b3 + zc - 1) / zc);
-        const double cost = (double)((blocks + slots - 1) / slots) * (zc + (nz > 1 ? 2.0 * mt : 0.0));
-        if (nz == 1 || cost < 0.98 * best) {
+        const long blocks = tiles * ((g.b3 + zc - 1) / zc), full = blocks / slots, rest = blocks - full * slots;
+        const double rounds = full * (lat + res) + (rest ? lat + (double)((rest + 255) / 256) : 0.0);
+        const double cost = rounds * (zc + mt + 1);
+        if (nz == 1 || cost < best) {
             best = cost;
             best_zc = zc;
         }
