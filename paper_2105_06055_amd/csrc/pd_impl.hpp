@@ -239,15 +239,16 @@ pd_status launch_xfwd_lg(pd_plan p, const G& gen, cx<T>* SA, hipStream_t st) {
     const Geo& g = p->geo;
     const int Tc = g.Nc / 8, Lt = rows_per_block<T>(p);
     if (x_block_fixed<T, LG>() > 0 && Tc * Lt != x_block_fixed<T, LG>()) return PD_EUNSUPPORTED;
-    dim3 grid((g.b2 + Lt - 1) / Lt, g.b3), block(Tc * Lt);
+    constexpr int FZ = by_field<G>::value;
+    dim3 grid((g.b2 + Lt - 1) / Lt, g.b3, FZ), block(Tc * Lt);
     size_t lds = ((size_t)Lt * row_pitch(g.Nc) + tw_lds_len(g.n1)) * sizeof(cx<T>);
     allow_lds(k_xfwd<T, G, LG>, lds);
     ProfScope ps(p, st);
     hipLaunchKernelGGL((k_xfwd<T, G, LG>), grid, block, lds, st, g, gen, SA, TWp<T>(p));
     if (p->prof) {
         char nm[32];
-        std::snprintf(nm, sizeof nm, "xfwd_%d", G::NIN);
-        ps.done(nm, gen.nbytes() * (double)g.nb + (double)G::NIN * g.b3 * g.h1 * g.b2 * sizeof(cx<T>));
+        std::snprintf(nm, sizeof nm, "xfwd_%d", G::NIN * FZ);
+        ps.done(nm, FZ * gen.nbytes() * (double)g.nb + (double)FZ * G::NIN * g.b3 * g.h1 * g.b2 * sizeof(cx<T>));
     }
     return pdh::check(hipGetLastError());
 }
@@ -607,11 +608,12 @@ pd_status launch_xinv_lg(pd_plan p, const F& fin, const cx<T>* SA, hipStream_t s
     constexpr int XF = x_block_fixed<T, LG, fin_xrows<F>::value>();
     const int Tc = g.Nc / 8, Lt = rows_per_block<T>(p, fin_xrows<F>::value);
     if (XF > 0 && Tc * Lt != XF) return PD_EUNSUPPORTED;
-    dim3 grid((g.b2 + Lt - 1) / Lt, g.b3), block(Tc * Lt);
+    constexpr int FZ = by_field<F>::value;
+    dim3 grid((g.b2 + Lt - 1) / Lt, g.b3, FZ), block(Tc * Lt);
     size_t lds = ((size_t)Lt * row_pitch(g.Nc) + tw_lds_len(g.n1)) * sizeof(cx<T>);
     size_t red_lds = (size_t)((Tc * Lt + 63) / 64) * 8 * sizeof(double);
     lds = std::max(lds, red_lds);
-    const long nblk = (long)grid.x * grid.y;
+    const long nblk = (long)grid.x * grid.y * FZ;
     if (F::NRED > 0 && nblk * F::NRED > p->partials_cap) return PD_EINVAL;
     allow_lds(k_xinv<T, F, LG>, lds);
     ProfScope ps(p, st);
@@ -621,8 +623,9 @@ pd_status launch_xinv_lg(pd_plan p, const F& fin, const cx<T>* SA, hipStream_t s
     if (p->prof) {
         char nm[32];
         if (NCH > 0) std::snprintf(nm, sizeof nm, "xinvfwd_%d_%d", F::NOUT, NCH);
-        else std::snprintf(nm, sizeof nm, "xinv_%d", F::NOUT);
-        ps.done(nm, fin.nbytes() * (double)g.nb + (double)(F::NOUT + NCH) * g.b3 * g.h1 * g.b2 * sizeof(cx<T>));
+        else std::snprintf(nm, sizeof nm, "xinv_%d", F::NOUT * FZ);
+        ps.done(nm, FZ * fin.nbytes() * (double)g.nb +
+                        (double)(F::NOUT * FZ + NCH) * g.b3 * g.h1 * g.b2 * sizeof(cx<T>));
     }
     PD_TRY(pdh::check(hipGetLastError()));
     if (F::NRED > 0) {
@@ -660,7 +663,8 @@ template <class T, class G, class M, class F>
 pd_status run_chain(pd_plan p, const G& gen, const M& mul, const F& fin, hipStream_t st, int sb_off = 0,
                     int out_off = 0, const T* taps = nullptr, int ntap = 0, int nct = 1,
                     uint32_t oddmask = 0xffffffffu) {
-    static_assert(M::NOUT == F::NOUT, "multiplier/epilogue mismatch");
+    constexpr int GIN = G::NIN * by_field<G>::value;   // input fields
+    static_assert(M::NOUT == F::NOUT * by_field<F>::value, "multiplier/epilogue mismatch");
     const Geo& g = p->geo;
     const T* taps_d = nullptr;   // direct-convention taps (plan tables only)
     if (!taps) {
@@ -670,14 +674,14 @@ pd_status run_chain(pd_plan p, const G& gen, const M& mul, const F& fin, hipStre
         nct = p->nct;
         oddmask = p->oddmask;
     }
-    if (std::max(G::NIN, M::NOUT) > p->saf_cap) return PD_EINVAL;
+    if (std::max(GIN, M::NOUT) > p->saf_cap) return PD_EINVAL;
     if constexpr (yz_capable<T, M>()) {
         if (taps_d && use_yz<T, M>(p)) {
             // x transform, (y, z) direct pass, inverse x transform; the generator
             // writes SA slots [sb_off, sb_off + G::NIN), the multiplier reads
             // [0, M::NIN) and writes after its inputs
             const int wo = std::max(out_off, M::NIN);
-            if (sb_off + G::NIN > p->saf_cap || wo + M::NOUT > p->saf_cap) return PD_EINVAL;
+            if (sb_off + GIN > p->saf_cap || wo + M::NOUT > p->saf_cap) return PD_EINVAL;
             PD_TRY(launch_xfwd<T>(p, gen, SAp<T>(p) + (long)sb_off * g.saf, st));
             PD_TRY((launch_yzconv<T, M>(p, mul, 0, wo, st)));
             return launch_xinv<T>(p, fin, SAp<T>(p) + (long)wo * g.saf, st);
@@ -685,12 +689,12 @@ pd_status run_chain(pd_plan p, const G& gen, const M& mul, const F& fin, hipStre
     }
     PD_TRY(launch_xfwd<T>(p, gen, SAp<T>(p), st));
     if (g.dim == 2) {
-        if (G::NIN != M::NIN) return PD_EINVAL;
+        if (GIN != M::NIN) return PD_EINVAL;
         Lines ln{(long)g.h1, (long)g.P2, g.saf, g.b2, g.n2, 0};
         PD_TRY(launch_lastmul<T>(p, ln, mul, SAp<T>(p), taps, taps_d, ntap, nct, oddmask, st));
     } else {
-        if (sb_off + G::NIN > p->sbf_cap || M::NIN > p->sbf_cap || out_off + M::NOUT > p->sbf_cap) return PD_EINVAL;
-        PD_TRY((launch_ytrans<T, -1>(p, G::NIN, sb_off, st)));
+        if (sb_off + GIN > p->sbf_cap || M::NIN > p->sbf_cap || out_off + M::NOUT > p->sbf_cap) return PD_EINVAL;
+        PD_TRY((launch_ytrans<T, -1>(p, GIN, sb_off, st)));
         Lines ln{(long)g.h1 * g.n2, (long)p->Pz, p->sbf, g.b3, g.n3, out_off};
         PD_TRY(launch_lastmul<T>(p, ln, mul, SBp<T>(p), taps, taps_d, ntap, nct, oddmask, st));
         PD_TRY((launch_ytrans<T, 1>(p, M::NOUT, out_off, st)));

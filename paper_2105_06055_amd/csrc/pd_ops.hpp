@@ -828,27 +828,22 @@ struct MulPre {
     }
 };
 
-// Preconditioner input: chi_O r (r in TR, converted to the chain type).
+// Preconditioner input: chi_O r (r in TR, converted to the chain type), one
+// component per block.
 template <class T, int D, class TR>
 struct GenMasked {
-    static constexpr int NIN = D;
+    static constexpr int NIN = 1, FZ = D;
     NodeCtx<T> c;
     const TR* r;
-    __host__ double nbytes() const { return D * double(sizeof(TR)) + 1.0; }
-    struct Ld { TR r[D]; uint8_t o[D]; };
-    __device__ __forceinline__ Ld load(Nd i, uint8_t cb) const {
-        Ld L;
-#pragma unroll
-        for (int d = 0; d < D; ++d) {
-            L.r[d] = ldf(r + d * c.nb, i);
-            L.o[d] = omega_bit(cb, d);
-        }
-        return L;
+    int d;      // component
+    __device__ __forceinline__ void pick(int z) {
+        d = z;
+        r += z * c.nb;
     }
-    __device__ __forceinline__ void gen(Nd, const Ld& L, T (&in)[D]) const {
-#pragma unroll
-        for (int d = 0; d < D; ++d) in[d] = L.o[d] ? T(L.r[d]) : T(0);
-    }
+    __host__ double nbytes() const { return double(sizeof(TR)) + 1.0; }
+    struct Ld { TR r; uint8_t o; };
+    __device__ __forceinline__ Ld load(Nd i, uint8_t cb) const { return {ldf(r, i), omega_bit(cb, d)}; }
+    __device__ __forceinline__ void gen(Nd, const Ld& L, T (&in)[1]) const { in[0] = L.o ? T(L.r) : T(0); }
 };
 
 // Test multiplier: a single kernel component odd in P axes, i^P K.
@@ -1315,31 +1310,26 @@ struct FinAdj {
 };
 
 // Preconditioner output z = chi_O (M^-1 chi_O r), stored as TZ, with the
-// partial sum r . z (FP64) for the preconditioned CG.
+// partial sum r . z (FP64) for the preconditioned CG; one component per block.
 template <class T, int D, class TR, class TZ>
 struct FinPre {
-    static constexpr int NOUT = D, NRED = 1;
+    static constexpr int NOUT = 1, NRED = 1, FZ = D;
     NodeCtx<T> c;
     const TR* r;
     TZ* z;
-    __host__ double nbytes() const { return D * double(sizeof(TR) + sizeof(TZ)) + 1.0; }
-    struct Ld { TR r[D]; uint8_t o[D]; };
-    __device__ __forceinline__ Ld load(Nd i, uint8_t cb) const {
-        Ld Q;
-#pragma unroll
-        for (int d = 0; d < D; ++d) {
-            Q.r[d] = ldf(r + d * c.nb, i);
-            Q.o[d] = omega_bit(cb, d);
-        }
-        return Q;
+    int d;      // component
+    __device__ __forceinline__ void pick(int q) {
+        d = q;
+        r += q * c.nb;
+        z += q * c.nb;
     }
-    __device__ __forceinline__ void fin(Nd i, const Ld& Q, const T (&val)[D], double* red) const {
-#pragma unroll
-        for (int d = 0; d < D; ++d) {
-            const TZ zd = Q.o[d] ? TZ(val[d]) : TZ(0);
-            stf(z + d * c.nb, i, zd);
-            red[0] += double(Q.r[d]) * double(zd);
-        }
+    __host__ double nbytes() const { return double(sizeof(TR) + sizeof(TZ)) + 1.0; }
+    struct Ld { TR r; uint8_t o; };
+    __device__ __forceinline__ Ld load(Nd i, uint8_t cb) const { return {ldf(r, i), omega_bit(cb, d)}; }
+    __device__ __forceinline__ void fin(Nd i, const Ld& Q, const T (&val)[1], double* red) const {
+        const TZ zd = Q.o ? TZ(val[0]) : TZ(0);
+        stf(z, i, zd);
+        red[0] += double(Q.r) * double(zd);
     }
 };
 

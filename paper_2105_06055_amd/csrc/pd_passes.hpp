@@ -76,6 +76,16 @@ struct Geo {
     long sbf;           // b3*h1*n2 (spectral points of the body planes)
 };
 
+// Generators and epilogues that treat their components alike one at a time
+// (FZ components, one per block along the grid's z) declare FZ and pick(z):
+// with few rows, a block per component is three times as many waves, each
+// with a third of the serial transforms.  (Preconditioner of an 81 x 80 x 77
+// body, 128 x 128 x 96 grid: x transform 40 -> 15 us, inverse 26 -> 18 us.)
+template <class F, class = void>
+struct by_field : std::integral_constant<int, 1> {};
+template <class F>
+struct by_field<F, std::void_t<decltype(F::FZ)>> : std::integral_constant<int, F::FZ> {};
+
 // Block-wide deterministic FP64 reduction of NR values; thread 0 writes the
 // block result to out[0..NR).
 template <int NR>
@@ -243,6 +253,10 @@ __global__ void __launch_bounds__(512) k_xfwd(Geo g, G gen, cx<T>* __restrict__ 
     extern __shared__ __align__(16) unsigned char smem_raw[];
     cx<T>* lds = reinterpret_cast<cx<T>*>(smem_raw);
     constexpr int NF = G::NIN, NG = 4;
+    if constexpr (by_field<G>::value > 1) {
+        gen.pick(blockIdx.z);
+        SA += blockIdx.z * g.saf;
+    }
     const int Nc = x_len<LG>(g), Tc = Nc >> 3;
     const int nthr = x_block_fixed<T, LG>() > 0 ? x_block_fixed<T, LG>() : (int)blockDim.x;
     const int Lt = nthr / Tc;
@@ -1304,6 +1318,11 @@ __global__ void __launch_bounds__(512) k_xinv(Geo g, F fin, const cx<T>* __restr
     extern __shared__ __align__(16) unsigned char smem_raw[];
     cx<T>* lds = reinterpret_cast<cx<T>*>(smem_raw);
     constexpr int NO = F::NOUT, NG = node_group<T>();
+    if constexpr (by_field<F>::value > 1) {
+        fin.pick(blockIdx.z);
+        SA += blockIdx.z * g.saf;
+        partials += (long)blockIdx.z * gridDim.x * gridDim.y * F::NRED;
+    }
     const int Nc = x_len<LG>(g), lgNc = x_lg<LG>(g), Tc = Nc >> 3;
     constexpr int XF = x_block_fixed<T, LG, fin_xrows<F>::value>();
     const int nthr = XF > 0 ? XF : (int)blockDim.x;
