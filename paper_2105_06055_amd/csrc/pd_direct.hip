@@ -174,11 +174,11 @@ template pd_status dir_drift<PD_INST_T>(pd_plan, const PD_INST_T*, PD_INST_T*, c
                                         const PD_INST_T*, PD_INST_T, int, hipStream_t);
 
 #if PD_DIR_FIRST   // once: not per type
-// Most blocks of a launch with a reduction: plate tiles of 32 x 4 nodes, or
+// Most blocks of a launch with a reduction: plate tiles of 32 x 8 nodes, or
 // four rounds of seven resident blocks per CU and one more of tiles (chunk3).
 void dir_launch_shape(pd_plan p) {
     const Geo& g = p->geo;
-    const long tiles = (long)((g.b1 + 31) / 32) * ((g.b2 + 3) / 4);
+    const long tiles = (long)((g.b1 + 31) / 32) * ((g.b2 + 7) / 8);
     p->dir_blocks = p->dim == 2 ? tiles : std::max(4L * 256 * 7, tiles) + tiles;
 }
 #endif
@@ -209,11 +209,12 @@ pd_status by_radius2(pd_plan p, F&& f) {
         default: return PD_EUNSUPPORTED;
     }
 }
-// Small plates (fewer nodes than the large tile gives every CU one block of)
-// take a small tile with one node per thread: more blocks, shorter chains.
-template <class T, int M> using Large = Tile2<T, M, 64, 8, 2>;
-template <class T, int M> using Small = Tile2<T, M, 32, 4, 1>;
-inline bool small_plate(pd_plan p) { return p->nb < 256L * 512; }
+// Tile of 32 x 8 nodes, one per thread, for every size: many short blocks.
+// (Verlet step of a 64 x 64 plate, M = 3 in FP32: 4.2 us; 64 x 8 nodes with
+// two per thread 5.3; 1000 x 400, M = 4: 10.4 and 10.9 us; 601 x 241, M = 6 in
+// FP64: 14.3 and 15.3 us.  The pair reads fewer LDS words per node but halves
+// the waves, and a plate has few.)
+template <class T, int M> using Plate = Tile2<T, M, 32, 8, 1>;
 
 #if PD_DIR_PART == 5
 template <class T, int M, class TL, bool WE, int NR>
@@ -258,8 +259,7 @@ pd_status dir2_force(pd_plan p, const Eval<T>& e, hipStream_t st) {
         auto go = [&](auto we, auto nr) -> pd_status {
             constexpr bool WE = decltype(we)::value;
             constexpr int NR = decltype(nr)::value;
-            return small_plate(p) ? run2<T, M, Small<T, M>, WE, NR>(p, A, st)
-                                  : run2<T, M, Large<T, M>, WE, NR>(p, A, st);
+            return run2<T, M, Plate<T, M>, WE, NR>(p, A, st);
         };
         if (e.mode >= 2) return go(std::false_type{}, std::integral_constant<int, 1>{});
         if (e.energy) return go(std::true_type{}, std::integral_constant<int, 4>{});
@@ -273,25 +273,22 @@ template <class T>
 pd_status run_adj(pd_plan p, const ArgsAdj<T>& A, hipStream_t st) {
     return by_radius2(p, [&](auto mc) -> pd_status {
         constexpr int M = decltype(mc)::value;
-        auto go = [&](auto tl) -> pd_status {
-            using TL = decltype(tl);
-            constexpr size_t lds = 5 * TL::PL * sizeof(T);
-            if (lds > (size_t)p->max_lds) return PD_EUNSUPPORTED;
-            auto kern = k_adj2<T, M, TL>;
-            allow_lds(kern, lds);
-            ProfScope ps(p, st);
-            hipLaunchKernelGGL(kern, grid2<TL>(p), dim3(TL::NT), lds, st, geo2(p), radial<T, M>(p), A);
-            if (p->prof) {
-                char nm[32];
-                std::snprintf(nm, sizeof nm, "adj2_m%d", M);
-                const double t = sizeof(T);
-                double by = 2 * t + 1 + (A.wt.s ? t : 0) + (A.wbar ? 2 * t + (A.u2 ? 2 * t : 0) + (A.acc ? 2 : 1) * t : 0);
-                by += A.stage == 0 ? (A.ubar ? 2 * t : 0) : (A.stage == 1 ? 6 * t : 8 * t + (A.bb ? 4 * t : 0));
-                ps.done(nm, by * (double)p->nb);
-            }
-            return pdh::check(hipGetLastError());
-        };
-        return small_plate(p) ? go(Small<T, M>{}) : go(Large<T, M>{});
+        using TL = Plate<T, M>;
+        constexpr size_t lds = 5 * TL::PL * sizeof(T);
+        if (lds > (size_t)p->max_lds) return PD_EUNSUPPORTED;
+        auto kern = k_adj2<T, M, TL>;
+        allow_lds(kern, lds);
+        ProfScope ps(p, st);
+        hipLaunchKernelGGL(kern, grid2<TL>(p), dim3(TL::NT), lds, st, geo2(p), radial<T, M>(p), A);
+        if (p->prof) {
+            char nm[32];
+            std::snprintf(nm, sizeof nm, "adj2_m%d", M);
+            const double t = sizeof(T);
+            double by = 2 * t + 1 + (A.wt.s ? t : 0) + (A.wbar ? 2 * t + (A.u2 ? 2 * t : 0) + (A.acc ? 2 : 1) * t : 0);
+            by += A.stage == 0 ? (A.ubar ? 2 * t : 0) : (A.stage == 1 ? 6 * t : 8 * t + (A.bb ? 4 * t : 0));
+            ps.done(nm, by * (double)p->nb);
+        }
+        return pdh::check(hipGetLastError());
     });
 }
 
@@ -348,17 +345,14 @@ pd_status dir_nbb(pd_plan p, const T* u, T* L, hipStream_t st) {
     if (p->dim == 2) {
         s = by_radius2(p, [&](auto mc) -> pd_status {
             constexpr int M = decltype(mc)::value;
-            auto go = [&](auto tl) -> pd_status {
-                using TL = decltype(tl);
-                constexpr size_t lds = 3 * TL::PL * sizeof(T);
-                if (lds > (size_t)p->max_lds) return PD_EUNSUPPORTED;
-                auto kern = k_nbb2<T, M, TL>;
-                allow_lds(kern, lds);
-                hipLaunchKernelGGL(kern, grid2<TL>(p), dim3(TL::NT), lds, st, geo2(p), radial<T, M>(p, inv), T(p->dx[0]),
-                                   p->chiB, u, L);
-                return pdh::check(hipGetLastError());
-            };
-            return small_plate(p) ? go(Small<T, M>{}) : go(Large<T, M>{});
+            using TL = Plate<T, M>;
+            constexpr size_t lds = 3 * TL::PL * sizeof(T);
+            if (lds > (size_t)p->max_lds) return PD_EUNSUPPORTED;
+            auto kern = k_nbb2<T, M, TL>;
+            allow_lds(kern, lds);
+            hipLaunchKernelGGL(kern, grid2<TL>(p), dim3(TL::NT), lds, st, geo2(p), radial<T, M>(p, inv), T(p->dx[0]),
+                               p->chiB, u, L);
+            return pdh::check(hipGetLastError());
         });
     } else {
         auto go = [&](auto mc) -> pd_status {
