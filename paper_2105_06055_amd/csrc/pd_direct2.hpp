@@ -544,8 +544,9 @@ __global__ void __launch_bounds__(TL::NT) k_nbb2(D2Geo g, Radial<T, M> tp, T dx,
 // M nodes on every side in LDS (u and chi: 75 KB in FP32, 150 KB in FP64 at M
 // = 3), which keeps eight waves on a CU in either type; the 4.6 halo loads
 // per node are small beside the ~2000 vector instructions of 122 bonds.
-// Measured on the 128^3 block: FP32 420 -> 96 us against the 13-field chain of
-// the (y, z) pass.
+// Measured on the 128^3 block: FP32 420 -> 97 us against the 13-field chain of
+// the (y, z) pass, relative error 6e-8 -> 1.2e-7 (sums by plane; 1.4e-7 with
+// the 122 bonds added one by one, 96 us).
 struct Tile3 {
     static constexpr int TX = 16, TY = 8, TZ = 8, NX = 2, NT = TX / NX * TY * TZ;
 };
@@ -601,9 +602,10 @@ __global__ void __launch_bounds__(Tile3::NT) k_nbb3(int b1, int b2, int b3, Radi
         }
     each<0, 2 * M + 1>([&](auto zc) {
         constexpr int cz = decltype(zc)::value - M;
-        T zs[NX];   // sum of s over the plane
+        // sums over the plane (short chains round less)
+        T zs[NX], ps[2][NX], pe[3][NX];
 #pragma unroll
-        for (int n = 0; n < NX; ++n) zs[n] = T(0);
+        for (int n = 0; n < NX; ++n) zs[n] = ps[0][n] = ps[1][n] = pe[0][n] = pe[1][n] = pe[2][n] = T(0);
         each<0, 2 * M + 1>([&](auto rc) {
             constexpr int b = decltype(rc)::value - M, R2 = M * M - b * b - cz * cz;
             if constexpr (R2 >= 0) {
@@ -611,8 +613,8 @@ __global__ void __launch_bounds__(Tile3::NT) k_nbb3(int b1, int b2, int b3, Radi
                 pin(zs);
 #pragma unroll
                 for (int d = 0; d < 3; ++d) {
-                    if (d < 2) pin(so[d]);
-                    pin(se[d]);
+                    if (d < 2) pin(ps[d]);
+                    pin(pe[d]);
                 }
                 row_fence();
                 T w[4][WN];
@@ -640,23 +642,32 @@ __global__ void __launch_bounds__(Tile3::NT) k_nbb3(int b1, int b2, int b3, Radi
                             if constexpr (b != 0) e += T(b) * h[1];
                             if constexpr (cz != 0) e += T(cz) * h[2];
                             const T s = tp.k[r2] * w[3][RA + n + a] * (dx2 * e + h[0] * h[0] + h[1] * h[1] + h[2] * h[2]);
-                            if constexpr (a != 0) so[0][n] += T(a) * s;
+                            if constexpr (a != 0) ps[0][n] += T(a) * s;
                             rs[n] += s;
 #pragma unroll
-                            for (int d = 0; d < 3; ++d) se[d][n] += s * h[d];
+                            for (int d = 0; d < 3; ++d) pe[d][n] += s * h[d];
                         }
                     }
                 });
 #pragma unroll
                 for (int n = 0; n < NX; ++n) {
-                    if constexpr (b != 0) so[1][n] += T(b) * rs[n];
+                    if constexpr (b != 0) ps[1][n] += T(b) * rs[n];
                     zs[n] += rs[n];
                 }
             }
         });
-        if constexpr (cz != 0) {
 #pragma unroll
-            for (int n = 0; n < NX; ++n) so[2][n] += T(cz) * zs[n];
+        for (int n = 0; n < NX; ++n) {
+            so[0][n] += ps[0][n];
+            so[1][n] += ps[1][n];
+            if constexpr (cz != 0) so[2][n] += T(cz) * zs[n];
+#pragma unroll
+            for (int d = 0; d < 3; ++d) se[d][n] += pe[d][n];
+        }
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            pin(so[d]);
+            pin(se[d]);
         }
     });
     if (nx <= 0) return;
