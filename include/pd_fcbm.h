@@ -190,6 +190,10 @@ typedef struct {
  * (for callers that replay a trajectory step by step, such as checkpointed
  * adjoints). */
 #define PD_STATE_EXACT_STEPS 1
+/* pd_state.flags: the call does not wait for its steps and does not report
+ * PD_ENUMERIC (for callers that replay steps which an earlier call has
+ * checked). Without energy_out the call then only enqueues work. */
+#define PD_STATE_NO_STATUS 2
 
 /* Advance nsteps embedded-constraint velocity-Verlet steps (Eq. 67, 83-84):
  *   u <- chi_O [u + dt v + dt^2/(2 rho) F] + (1 - chi_O) w

@@ -89,8 +89,9 @@ class VerletRollout(torch.autograd.Function):
             if s is not None:
                 st["s"] = s
             us = [st["u"].clone()]
+            # the forward pass has checked these steps: no wait for a status
             for _ in range(length):
-                plan.verlet(st, dt, 1, b=b)
+                plan.verlet(st, dt, 1, b=b, status=False)
                 us.append(st["u"].clone())
             for i in range(length - 1, -1, -1):
                 plan.verlet_adjoint(us[i], us[i + 1], ub, vb, dt, s=s, s_bar=sb, b_bar=bb)

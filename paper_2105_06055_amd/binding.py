@@ -61,6 +61,7 @@ class State(C.Structure):
 
 
 STATE_EXACT_STEPS = 1
+STATE_NO_STATUS = 2
 
 
 class SolveInfo(C.Structure):
@@ -233,10 +234,12 @@ class Plan:
                "pd_force_adjoint")
         return (ub, wb) if want_weight_bar else ub
 
-    def verlet(self, state, dt, nsteps, b=None, w=None, energy=False, exact_steps=False):
+    def verlet(self, state, dt, nsteps, b=None, w=None, energy=False, exact_steps=False, status=True):
         """Advance ``state`` (dict with u, v, F and optionally W, lam, s, step).
         exact_steps: every step reads and writes (v, F), so the call equals
-        nsteps one-step calls bit for bit (PD_STATE_EXACT_STEPS)."""
+        nsteps one-step calls bit for bit (PD_STATE_EXACT_STEPS).
+        status=False: do not wait for the steps to report non-finite values
+        (PD_STATE_NO_STATUS; for replays of steps that a call has checked)."""
         for k in ("u", "v", "F"):
             self._vec(state[k], k)
         b = self._vec(b, "b")
@@ -245,7 +248,8 @@ class Plan:
                    W=None if state.get("W") is None else self._sca(state["W"], "W").data_ptr(),
                    lam=None if state.get("lam") is None else self._sca(state["lam"], "lam", torch.uint8).data_ptr(),
                    s=None if state.get("s") is None else self._sca(state["s"], "s").data_ptr(),
-                   step=int(state.get("step", 0)), flags=STATE_EXACT_STEPS if exact_steps else 0)
+                   step=int(state.get("step", 0)),
+                   flags=(STATE_EXACT_STEPS if exact_steps else 0) | (0 if status else STATE_NO_STATUS))
         en = (C.c_double * (4 * nsteps))() if energy else None
         _check(lib().pd_verlet_step(self._h, C.byref(st), _ptr(b), _ptr(w), float(dt), int(nsteps),
                                     en, _stream()), "pd_verlet_step")

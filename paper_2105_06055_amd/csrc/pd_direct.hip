@@ -86,10 +86,10 @@ pd_status force3(pd_plan p, const Eval<T>& e, hipStream_t st) {
     ep.ka = T(p->ka);
     ep.u = e.u; ep.theta = e.theta;
     ep.L = e.L; ep.v = e.v; ep.F = e.F; ep.b = e.b; ep.w = e.w;
-    ep.c1 = e.c1; ep.rho = e.rho; ep.dt = e.dt;
+    ep.c1 = e.c1; ep.c2 = e.c2; ep.rho = e.rho; ep.dt = e.dt;
     ep.u_next = e.u_next;
     ep.nanflag = e.nanflag;
-    ep.vh_in = e.vh_in; ep.vh_out = e.vh_out;
+    ep.vh_in = e.vh_in; ep.vh_out = e.vh_out; ep.next = e.next;
     ep.has = (e.b ? 1 : 0) | (e.w ? 2 : 0);
     D3In<T> in{{e.u, e.u + p->nb, e.u + 2 * p->nb, e.theta}, p->chiB};
     const T g0 = ep.c.sint[0];   // G_xx = G_yy = G_zz; the odd sums vanish
@@ -233,7 +233,7 @@ pd_status run2(pd_plan p, const Args2<T>& A, hipStream_t st) {
         std::snprintf(nm, sizeof nm, "dir2_m%d", M);
         const double t = sizeof(T);
         double by = 2 * t + 1 + (A.wt.lam ? 1 : 0) + (A.wt.s ? t : 0) + (A.Wo ? t : 0) + (A.b ? 2 * t : 0);
-        if (A.mode == 1) by += 2 * t * (3 + (A.vh_in ? 0 : 1)) + (A.vh_out && A.lam_next ? 1 : 0);
+        if (A.mode == 1) by += 2 * t * (2 + (A.vh_in ? 0 : 1) + (A.vh_out ? 0 : 1) + A.next) + (A.next && A.lam_next ? 1 : 0);
         else by += 2 * t;
         ps.done(nm, by * (double)p->nb);
     }
@@ -249,8 +249,8 @@ pd_status dir2_force(pd_plan p, const Eval<T>& e, hipStream_t st) {
     A.u = e.u;
     A.L = e.L; A.Wo = e.W;
     A.v = e.v; A.F = e.F; A.b = e.b; A.w = e.w;
-    A.c1 = e.c1; A.dt = e.dt; A.rho = e.rho;
-    A.vh_in = e.vh_in; A.vh_out = e.vh_out;
+    A.c1 = e.c1; A.c2 = e.c2; A.dt = e.dt; A.rho = e.rho;
+    A.vh_in = e.vh_in; A.vh_out = e.vh_out; A.next = e.next;
     A.u_next = e.u_next; A.lam_next = e.lam_next;
     A.Wc = e.Wc; A.fail = e.fail;
     A.nanflag = e.nanflag;

@@ -46,6 +46,13 @@ namespace pdd {
 
 using namespace pdk;
 
+// Position update u + dt v + c2 F, as fixed multiply-adds: the element-wise
+// pass and the epilogues give the same bits.
+__device__ __forceinline__ float mad(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double mad(double a, double b, double c) { return __builtin_fma(a, b, c); }
+template <class T>
+__device__ __forceinline__ T position_update(T u, T dt, T v, T c2, T F) { return mad(c2, F, mad(dt, v, u)); }
+
 // ------------------------------------------------------------ compile-time loops
 template <int I0, int... I, class F>
 __device__ __forceinline__ void each_of(std::integer_sequence<int, I...>, F&& f) {
@@ -421,11 +428,10 @@ struct EpTheta {
 
 // Force: L_i = chi (conv_i [+ k_a theta g_i] - G_ij u_j), then by kind
 //   FORCE   L
-//   STEP    Verlet: F' = L + b, v <- chi_O [v + c1 (F + F')], with vh_in and
-//           vh_out (kernel-uniform) as pdd::Eval
-//   INNER   STEP with vh_in = vh_out = 1: no F; u_next (another buffer than u,
-//           which other blocks still read) receives chi_O (u + dt vh') +
-//           (1 - chi_O) w
+//   STEP    Verlet: F' = L + b, v <- chi_O [v + c1 (F + F')], with vh_in,
+//           vh_out and next (kernel-uniform) as pdd::Eval; u_next is another
+//           buffer than u, which other blocks still read
+//   INNER   STEP with vh_in = vh_out = next = 1: no F
 //   ENERGY  STEP with the energy sums
 //   SOLVER  mode 2: -chi_O L and the partial sum of u . (-chi_O L);
 //           mode 3: r = chi_O (L + b) and the partial sum of |r|^2
@@ -441,15 +447,15 @@ struct EpForce {
     T ka;
     const T* u; const T* theta;
     T* L; T* v; T* F; const T* b; const T* w;
-    T c1, rho, dt;
+    T c1, c2, rho, dt;
     T* u_next;
     double* nanflag;
-    int vh_in, vh_out;
+    int vh_in, vh_out, next;
     int has;            // bit 0: b, bit 1: w
     __host__ double nbytes() const {
         const double t = sizeof(T);
         double r = 3 * t + 1 + 6 * t * c.edge_frac + (LPS ? t + 3 * t * c.edge_frac : 0.0) + (b ? 3 * t : 0.0);
-        if (VV) return r + 3 * t * (2 + (vh_in ? 0 : 1) + 1 + (vh_out && w ? 1 : 0));
+        if (VV) return r + 3 * t * (2 + (vh_in ? 0 : 1) + (vh_out ? 0 : 1) + (next ? (w ? 2 : 1) : 0));
         return r + 3 * t;
     }
     // x: v; y: F (STEP, ENERGY), else b
@@ -547,7 +553,7 @@ struct EpForce {
                     const T Fn = La[a][q] + Q.y[a][q], vf = Q.x[a][q] + c1 * Fn, vn = o ? vf : T(0);
                     bad = bad || (q < at.n && !(__builtin_isfinite(Fn) && __builtin_isfinite(vn)));
                     vo[q] = o ? vn + c1 * Fn : T(0);
-                    un[q] = o ? Q.u[a][q] + dt * vo[q] : ((has & 2) ? un[q] : T(0));
+                    un[q] = o ? mad(dt, vo[q], Q.u[a][q]) : ((has & 2) ? un[q] : T(0));
                 }
                 if (bad) {
                     double* flag = rare_args<D3Args<T, EpForce, MT>>().ep.nanflag;
@@ -580,12 +586,15 @@ struct EpForce {
                 }
                 at.template st<NX>(v, a, vo);
                 if (!vh_out) at.template st<NX>(F, a, fo);
-                else {
+                if (next) {
                     T un[NX];
                     if (w) at.template ld<NX, true>(w, a, un);
 #pragma unroll
-                    for (int q = 0; q < NX; ++q)
-                        un[q] = omega_bit(Q.cb[q], a) ? Q.u[a][q] + dt * vo[q] : (w ? un[q] : T(0));
+                    for (int q = 0; q < NX; ++q) {
+                        const T x = vh_out ? mad(dt, vo[q], Q.u[a][q])
+                                           : position_update(Q.u[a][q], dt, vo[q], c2, fo[q]);
+                        un[q] = omega_bit(Q.cb[q], a) ? x : (w ? un[q] : T(0));
+                    }
                     at.template st<NX>(u_next, a, un);
                 }
             }
@@ -951,7 +960,7 @@ __global__ void __launch_bounds__(256) k_drift(long n, const uint8_t* __restrict
 #pragma unroll
         for (int d = 0; d < D; ++d) {
             const long k = i + d * n;
-            const T xn = u[k] + dt * v[k] + c2 * F[k];
+            const T xn = position_update(u[k], dt, v[k], c2, F[k]);
             x[d] = omega_bit(cb, d) ? xn : (w ? w[k] : T(0));
         }
 #pragma unroll

@@ -99,8 +99,8 @@ struct Args2 {
     const T* u;
     T* L; T* Wo;
     T* v; T* F; const T* b; const T* w;
-    T c1, dt, rho;
-    int vh_in, vh_out;
+    T c1, c2, dt, rho;
+    int vh_in, vh_out, next;
     T* u_next; uint8_t* lam_next;
     T Wc;
     int fail;
@@ -249,16 +249,19 @@ __global__ void __launch_bounds__(TL::NT) k_dir2(D2Geo g, Radial<T, M> tp, Args2
                 }
                 stn<NX>(A.v + d * g.nb, 0, off, nx, vo);
                 if (!A.vh_out) stn<NX>(A.F + d * g.nb, 0, off, nx, fo);
-                else {
+                if (A.next) {
                     T wk[NX];
                     if (A.w) ldn<NX>(A.w + d * g.nb, 0, off, nx, wk);
 #pragma unroll
-                    for (int n = 0; n < NX; ++n)
-                        wk[n] = omega_bit(cb[n], d) ? (d ? u1[n] : u0[n]) + A.dt * vo[n] : (A.w ? wk[n] : T(0));
+                    for (int n = 0; n < NX; ++n) {
+                        const T un = d ? u1[n] : u0[n];
+                        const T x = A.vh_out ? mad(A.dt, vo[n], un) : position_update(un, A.dt, vo[n], A.c2, fo[n]);
+                        wk[n] = omega_bit(cb[n], d) ? x : (A.w ? wk[n] : T(0));
+                    }
                     stn<NX>(A.u_next + d * g.nb, 0, off, nx, wk);
                 }
             }
-            if (A.vh_out && A.lam_next) {
+            if (A.next && A.lam_next) {
                 uint8_t ln[NX];
                 ldn<NX>(A.wt.lam, 0, off, nx, ln);
                 if constexpr (WE) {

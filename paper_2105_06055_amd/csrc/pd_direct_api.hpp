@@ -17,11 +17,12 @@ void dir_launch_shape(pd_plan p);
 // Fields of one evaluation.  mode 0: L (and W where it is not null);
 // mode 1: Verlet velocity update, F' = L + b, v <- chi_O [v + c1 (F + F')];
 // vh_in: v holds the half-step velocity v + c1 F and F is not read; vh_out: v
-// receives v' + c1 F', F is not written, and the next step's position update
-// chi_O (u + dt v) + (1 - chi_O) w goes to u_next (not u: other blocks still
-// read it), with the next integrity lam && W <= Wc in lam_next; mode 2:
-// L = -chi_O L and red[0] = u . L; mode 3: L = chi_O (L + b) and red[0] =
-// |L|^2.  energy: red[0 .. 3] = the energy sums of mode 1.
+// receives v' + c1 F' and F is not written; next: the next step's position
+// update (position_update, with v' and F', or with the half-step
+// velocity and no F) goes to u_next (not u: other blocks still read it), and
+// the next integrity lam && W <= Wc to lam_next; mode 2: L = -chi_O L and
+// red[0] = u . L; mode 3: L = chi_O (L + b) and red[0] = |L|^2.  energy:
+// red[0 .. 3] = the energy sums of mode 1.
 template <class T>
 struct Eval {
     int mode;
@@ -31,8 +32,8 @@ struct Eval {
     const T* s;            // micromodulus scale, or neither
     T* L; T* W;
     T* v; T* F; const T* b; const T* w;
-    T c1, dt, rho;
-    int vh_in, vh_out, energy;
+    T c1, c2, dt, rho;
+    int vh_in, vh_out, next, energy;
     T* u_next; uint8_t* lam_next;
     T Wc;
     int fail;

@@ -1869,9 +1869,10 @@ inline pd_status verlet_energies(pd_plan p, double dt, double* energy, hipStream
     return PD_OK;
 }
 
-// End of a Verlet call: reads the non-finite flag.
+// End of a Verlet call: reads the non-finite flag (flag null: no status asked
+// for, no wait).
 inline pd_status verlet_end(pd_plan p, double* flag, int nsteps, hipStream_t st) {
-    if (nsteps > 0) {
+    if (nsteps > 0 && flag) {
         if (!p->red_host_dev)
             HIP_TRY(hipMemcpyAsync(p->red_host + kNanSlot, flag, sizeof(double), hipMemcpyDeviceToHost, st));
         HIP_TRY(hipStreamSynchronize(st));
@@ -1881,12 +1882,13 @@ inline pd_status verlet_end(pd_plan p, double* flag, int nsteps, hipStream_t st)
 }
 
 // The steps of a call on the direct sums.  A step is the force stage(s) on
-// updated positions; its epilogue updates the velocities and, inside a
-// multi-step call (kdk), also makes the next step's position (and integrity)
+// updated positions; its epilogue updates the velocities and, but for the
+// last step of the call, also makes the next step's position (and integrity)
 // update into a second buffer, since other blocks still read the current one
-// as neighbours.  The first update of a call, and every one with (v, F) kept,
-// is an element-wise pass; it writes to the buffer from which the alternation
-// ends in the caller's arrays.
+// as neighbours.  The first update of a call is an element-wise pass, which
+// writes to the buffer from which the alternation ends in the caller's arrays.
+// (The two forms of the update are the same sequence of multiply-adds, so
+// that steps with (v, F) kept equal single-step calls bit for bit.)
 template <class T>
 pd_status verlet_direct(pd_plan p, pd_state* S, const T* b, const T* w, double dt, int nsteps, double* energy,
                         bool kdk, double* flag, hipStream_t st) {
@@ -1897,16 +1899,12 @@ pd_status verlet_direct(pd_plan p, pd_state* S, const T* b, const T* w, double d
     const bool lam = p->kern.weight == PD_WEIGHT_INTEGRITY;
     const int fail = (lam && S->W && p->Wc > 0) ? 1 : 0;
     T* W = lam ? reinterpret_cast<T*>(S->W) : nullptr;
-    int cur = 0;   // buffer of the current positions
+    int cur = (nsteps - 1) & 1;   // buffer of the current positions
+    if (nsteps > 0)
+        PD_TRY((pdd::dir_drift<T>(p, ub[0], ub[cur], reinterpret_cast<const T*>(S->v),
+                                  reinterpret_cast<const T*>(S->F), w, T(dt), c2, lam ? lb[0] : nullptr,
+                                  lam ? lb[cur] : nullptr, W, T(p->Wc), fail, st)));
     for (int k = 0; k < nsteps; ++k) {
-        const int vh_in = (kdk && k > 0) ? 1 : 0, vh_out = (kdk && k + 1 < nsteps) ? 1 : 0;
-        if (!vh_in) {
-            const int to = kdk ? ((nsteps - 1) & 1) : 0;
-            PD_TRY((pdd::dir_drift<T>(p, ub[0], ub[to], reinterpret_cast<const T*>(S->v),
-                                      reinterpret_cast<const T*>(S->F), w, T(dt), c2, lam ? lb[0] : nullptr,
-                                      lam ? lb[to] : nullptr, W, T(p->Wc), fail, st)));
-            cur = to;
-        }
         pdd::Eval<T> e{};
         e.mode = 1;
         e.u = ub[cur];
@@ -1916,8 +1914,10 @@ pd_status verlet_direct(pd_plan p, pd_state* S, const T* b, const T* w, double d
         e.v = reinterpret_cast<T*>(S->v);
         e.F = reinterpret_cast<T*>(S->F);
         e.b = b; e.w = w;
-        e.c1 = c1; e.dt = T(dt); e.rho = rho;
-        e.vh_in = vh_in; e.vh_out = vh_out;
+        e.c1 = c1; e.c2 = c2; e.dt = T(dt); e.rho = rho;
+        e.next = k + 1 < nsteps ? 1 : 0;
+        e.vh_in = kdk && k > 0 ? 1 : 0;
+        e.vh_out = kdk && e.next ? 1 : 0;
         e.energy = energy ? 1 : 0;
         e.u_next = ub[1 - cur];
         e.lam_next = lam ? lb[1 - cur] : nullptr;
@@ -1926,7 +1926,7 @@ pd_status verlet_direct(pd_plan p, pd_state* S, const T* b, const T* w, double d
         if (p->kern.model == PD_LPS_LINEAR) PD_TRY((lps_direct<T>(p, e, st)));
         else if (p->dim == 3) PD_TRY((pdd::dir3_force<T>(p, e, st)));
         else PD_TRY((pdd::dir2_force<T>(p, e, st)));
-        if (vh_out) cur = 1 - cur;
+        if (e.next) cur = 1 - cur;
         if (energy) PD_TRY(verlet_energies(p, dt, energy + 4 * k, st));
         S->step += 1;
     }
@@ -1958,7 +1958,7 @@ pd_status verlet_impl(pd_plan p, pd_state* S, const T* b, const T* w, double dt,
     // device slot copied back), cleared here and read once, after the last
     // step of the call.
     double* flag = nullptr;
-    if (nsteps > 0) {
+    if (nsteps > 0 && !(S->flags & PD_STATE_NO_STATUS)) {
         if (p->red_host_dev) {
             p->red_host[kNanSlot] = 0.0;
             flag = p->red_host_dev + kNanSlot;
