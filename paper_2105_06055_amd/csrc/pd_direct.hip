@@ -19,13 +19,8 @@
 namespace pdd {
 
 using pdi::allow_lds;
+using pdi::finish_reduction;
 using pdi::ProfScope;
-
-// p->red[0 .. nr) = the sums of the blocks' partials
-inline pd_status finish_reduction(pd_plan p, long nblk, int nr, hipStream_t st) {
-    hipLaunchKernelGGL(k_reduce_final, dim3(1), dim3(256), 0, st, p->partials, nblk, nr, p->red, (double*)nullptr);
-    return pdh::check(hipGetLastError());
-}
 
 // ------------------------------------------------------------ 3D launches
 // g0: the interior static value the epilogue takes from scalar registers.

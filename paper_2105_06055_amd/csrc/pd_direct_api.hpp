@@ -11,7 +11,7 @@ namespace pdd {
 // and a plan that qualifies (dir_plan).
 inline bool on(pd_plan p) { return p->dir_mt > 0 && p->lastaxis == PD_LASTAXIS_AUTO; }
 
-// Launch shapes of a qualifying plan (dir_nzc, dir_blocks).
+// Launch shapes of a qualifying plan (dir_blocks).
 void dir_launch_shape(pd_plan p);
 
 // Fields of one evaluation.  mode 0: L (and W where it is not null);

@@ -326,7 +326,7 @@ pd_status launch_lastmul(pd_plan p, const Lines& ln, const M& mul, cx<T>* S, con
     // per lane: beyond 16 fields in FP64 it spills heavily (13 + 13: 8.6 ms
     // against 2.4 ms for the transform form on the 128^3 block)
     constexpr bool direct_ok = !M::RT_ODD && !is_nonlocal<M>::value && !(sizeof(T) == 8 && M::NIN + M::NOUT > 16);
-    int path = 2;   // 0 direct, 1 specialised FFT, 2 generic FFT
+    int path = 2;   // 0 direct, 1 specialised FFT, 2 generic FFT, 3 specialised FFT on short lines
     if constexpr (direct_ok) {
         if ((p->lastaxis == PD_LASTAXIS_AUTO || p->lastaxis == PD_LASTAXIS_YFFT) && taps_d && ntap >= 2 && ntap <= 5)
             path = 0;
@@ -335,7 +335,31 @@ pd_status launch_lastmul(pd_plan p, const Lines& ln, const M& mul, cx<T>* S, con
         if (path != 0 && p->lastaxis != PD_LASTAXIS_FFT_GENERIC && (ln.N == 512 || ln.N == 256) && ntap == 4)
             path = 1;
     }
-    if (path == 0) {
+    // the preconditioner's 64- and 128-point lines at two and three spacings:
+    // taps and lengths at compile time, one wave per block (no barrier spans
+    // waves, and the few lines spread evenly over the CUs)
+    if constexpr (is_nonlocal<M>::value) {
+        if (p->lastaxis != PD_LASTAXIS_FFT_GENERIC && (ln.N == 64 || ln.N == 128) && (ntap == 3 || ntap == 4)) path = 3;
+    }
+    if (path == 3) {
+        if constexpr (is_nonlocal<M>::value) {
+            auto go = [&](auto lgc, auto ntc) -> pd_status {
+                constexpr int LG = decltype(lgc)::value, NT = decltype(ntc)::value;
+                constexpr int Lw = 512 >> LG;   // 64 threads
+                const size_t lds = ((size_t)Lw * line_pitch(1 << LG) + tw_lds_len(1 << LG)) * sizeof(cx<T>);
+                if (lds > (size_t)p->max_lds) return PD_EUNSUPPORTED;
+                allow_lds(k_lastmul_f<T, M, LG, NT>, lds);
+                hipLaunchKernelGGL((k_lastmul_f<T, M, LG, NT>), dim3((unsigned)((ln.nlines + Lw - 1) / Lw)), dim3(64),
+                                   lds, st, ln, mul, S, taps, nct, TWp<T>(p));
+                return PD_OK;
+            };
+            using std::integral_constant;
+            auto by_taps = [&](auto lgc) -> pd_status {
+                return ntap == 3 ? go(lgc, integral_constant<int, 3>{}) : go(lgc, integral_constant<int, 4>{});
+            };
+            PD_TRY(ln.N == 64 ? by_taps(integral_constant<int, 6>{}) : by_taps(integral_constant<int, 7>{}));
+        }
+    } else if (path == 0) {
         if constexpr (direct_ok) {
             pd_status s = PD_OK;
             switch (ntap) {
@@ -628,12 +652,7 @@ pd_status launch_xinv_lg(pd_plan p, const F& fin, const cx<T>* SA, hipStream_t s
                         (double)(F::NOUT * FZ + NCH) * g.b3 * g.h1 * g.b2 * sizeof(cx<T>));
     }
     PD_TRY(pdh::check(hipGetLastError()));
-    if (F::NRED > 0) {
-        hipLaunchKernelGGL(k_reduce_final, dim3(1), dim3(256), 0, st, p->partials, nblk, F::NRED, p->red,
-                           (double*)nullptr);
-        PD_TRY(pdh::check(hipGetLastError()));
-    }
-    return PD_OK;
+    return F::NRED > 0 ? finish_reduction(p, nblk, F::NRED, st) : PD_OK;
 }
 template <class T, class F>
 pd_status launch_xinv(pd_plan p, const F& fin, const cx<T>* SA, hipStream_t st, cx<T>* SAout = nullptr) {
@@ -994,7 +1013,7 @@ inline void plan_free(pd_plan p) {
     if (!p) return;
     if (p->stream0) (void)hipStreamSynchronize(p->stream0);
     void* bufs[] = {p->tw, p->tw64, p->taps, p->taps_d, p->taps_yz, p->stat, p->stat_int, p->chiB, p->chiO, p->SA, p->SB, p->theta,
-                    p->vtmp, p->vtmp2, p->partials, p->red, p->offs_dev, p->kval_dev, p->etab};
+                    p->vtmp, p->vtmp2, p->partials, p->cg_partials, p->red, p->offs_dev, p->kval_dev, p->etab};
     for (void* b : bufs)
         if (b) (void)hipFree(b);
     if (p->red_host) (void)hipHostFree(p->red_host);
@@ -1092,6 +1111,7 @@ pd_status plan_alloc(pd_plan p, hipStream_t st, const uint8_t* chiB_h, const uin
         long nblk = (long)((g.b2 + Lt - 1) / Lt) * g.b3;
         p->partials_cap = std::max(std::max(nblk * 8, 4096L), p->dir_blocks * 4);
         HIP_TRY(hipMalloc(&p->partials, sizeof(double) * p->partials_cap));
+        HIP_TRY(hipMalloc(&p->cg_partials, sizeof(double) * kCgBlocks));
         HIP_TRY(hipMalloc(&p->red, sizeof(double) * 16));
         HIP_TRY(hipHostMalloc(&p->red_host, sizeof(double) * 16, hipHostMallocDefault));
         // the device address of the pinned buffer, for reductions that write
@@ -1507,7 +1527,7 @@ namespace pdi {
 
 constexpr int EW_THREADS = 256;
 
-// grid-stride elementwise kernels use at most 2048 blocks (partials capacity)
+// grid-stride elementwise kernels use at most 2048 blocks
 inline unsigned ew_blocks(long n) { return (unsigned)std::max<long>(1, std::min<long>((n + EW_THREADS - 1) / EW_THREADS, 2048L)); }
 
 // y[k] += x[k]  (k < n)
@@ -1527,108 +1547,111 @@ __global__ void k_constrain(T* __restrict__ u, T* __restrict__ t, const T* __res
     }
 }
 
-// Block partial sums of NR FP64 accumulators, written to part[blockIdx*NR].
-template <int NR>
-__device__ __forceinline__ void ew_block_reduce(double (&acc)[NR], double* part) {
-    __shared__ double sm[(EW_THREADS / 64) * 4];
-    block_reduce_store<NR>(acc, part + (long)blockIdx.x * NR, sm);
+// CG vector kernels.  The coefficients stay on the device: every block of the
+// consumer sums the partials of the kernel before (sum_partials), so neither a
+// scalar through the host nor a kernel for the sum stands between two passes.
+// A block holds 512 x 4 values per trip, all loads issued before it waits for
+// the sum, and at most kCgBlocks blocks read the partials.
+constexpr int kCgThreads = 512, kCgUnroll = 4;
+inline unsigned cg_blocks(long n) {
+    constexpr long per = kCgThreads * kCgUnroll;
+    return (unsigned)std::max<long>(1, std::min<long>((n + per - 1) / per, kCgBlocks));
 }
+// num / den (0 when the denominator is 0)
+__device__ __forceinline__ double dev_ratio(double num, double den) { return den != 0.0 ? num / den : 0.0; }
 
-// CG coefficients stay on the device: alpha = rho / (p . Ap) and
-// beta = rho_new / rho are formed by every thread from the reduction results
-// (0 when the denominator is 0), so no scalar travels through the host.
-__device__ __forceinline__ double dev_ratio(const double* __restrict__ num, const double* __restrict__ den) {
-    const double d = den[0];
-    return d != 0.0 ? num[0] / d : 0.0;
-}
-// Thread 0 of block 0 keeps rho_new for the next iteration's alpha (a slot
-// that no thread of the launch reads).
-__device__ __forceinline__ void keep_rho(double* __restrict__ save, const double* __restrict__ num) {
-    if (save && blockIdx.x == 0 && threadIdx.x == 0) save[0] = num[0];
-}
-
-// CG update: x += a p; r -= a Ap; partial |r|^2, a = num / den.  (types may
-// differ: x is the iterate precision, r/p/Ap the operator precision)
+// x += a p;  r -= a Ap (formed in FP64; in the mixed solve r, p and Ap are
+// FP32, and the FP64 residual replaces r before its rounding accumulates);
+// partial |r|^2 in FP64, a = rho / (p . Ap)
 template <class TX, class T>
-__global__ void k_cg_update(TX* __restrict__ x, const T* __restrict__ p, T* __restrict__ r, const T* __restrict__ Ap,
-                            const double* __restrict__ num, const double* __restrict__ den, long n,
-                            double* __restrict__ part) {
-    const double a = dev_ratio(num, den);
+__global__ void __launch_bounds__(kCgThreads) k_cg_update(TX* __restrict__ x, const T* __restrict__ p, T* __restrict__ r,
+                                                          const T* __restrict__ Ap, const double* __restrict__ rho,
+                                                          PartialSum pAp, long n, double* __restrict__ part) {
+    constexpr int U = kCgUnroll, NT = kCgThreads;
+    __shared__ double sa[NT / 64], sr[NT / 64];
+    const long step = (long)gridDim.x * NT * U;
+    long k0 = (long)blockIdx.x * NT * U + threadIdx.x;
+    TX xv[U];
+    T pv[U], rv[U], av[U];
+    auto load = [&] {
+#pragma unroll
+        for (int q = 0; q < U; ++q) {
+            const long k = k0 + q * NT;
+            if (k < n) { xv[q] = x[k]; pv[q] = p[k]; rv[q] = r[k]; av[q] = Ap[k]; }
+        }
+    };
+    load();
+    const double a = dev_ratio(rho[0], sum_partials<NT>(pAp, sa));
     double acc[1] = {0.0};
-    for (long k = (long)blockIdx.x * blockDim.x + threadIdx.x; k < n; k += (long)gridDim.x * blockDim.x) {
-        x[k] = TX(double(x[k]) + a * double(p[k]));
-        T rk = T(double(r[k]) - a * double(Ap[k]));
-        r[k] = rk;
-        acc[0] += double(rk) * double(rk);
+    for (;;) {
+#pragma unroll
+        for (int q = 0; q < U; ++q) {
+            const long k = k0 + q * NT;
+            if (k < n) {
+                x[k] = TX(double(xv[q]) + a * double(pv[q]));
+                const T rk = T(double(rv[q]) - a * double(av[q]));
+                r[k] = rk;
+                acc[0] += double(rk) * double(rk);
+            }
+        }
+        k0 += step;
+        if (k0 >= n) break;
+        load();
     }
-    ew_block_reduce<1>(acc, part);
+    block_reduce_store<1>(acc, part + blockIdx.x, sr);
 }
 
-// p = r + b p, b = num / den
+// p = z + b p, b = num / rho.  Block 0 keeps num in rho_new (a slot that no
+// thread of the launch reads) and the sum rr (num's partials, or others) for
+// the host in rr_out.
 template <class T>
-__global__ void k_cg_dir(T* __restrict__ p, const T* __restrict__ r, const double* __restrict__ num,
-                         const double* __restrict__ den, double* __restrict__ save, long n) {
-    const double b = dev_ratio(num, den);
-    keep_rho(save, num);
-    for (long k = (long)blockIdx.x * blockDim.x + threadIdx.x; k < n; k += (long)gridDim.x * blockDim.x)
-        p[k] = T(double(r[k]) + b * double(p[k]));
+__global__ void __launch_bounds__(kCgThreads) k_cg_dir(T* __restrict__ p, const T* __restrict__ z, PartialSum num,
+                                                       const double* __restrict__ rho, double* __restrict__ rho_new,
+                                                       PartialSum rr, double* __restrict__ rr_out, long n) {
+    constexpr int U = kCgUnroll, NT = kCgThreads;
+    __shared__ double sa[NT / 64], sr[NT / 64];
+    const long step = (long)gridDim.x * NT * U;
+    long k0 = (long)blockIdx.x * NT * U + threadIdx.x;
+    T pv[U], zv[U];
+    auto load = [&] {
+#pragma unroll
+        for (int q = 0; q < U; ++q) {
+            const long k = k0 + q * NT;
+            if (k < n) { pv[q] = p[k]; zv[q] = z[k]; }
+        }
+    };
+    load();
+    const double s = sum_partials<NT>(num, sa), b = dev_ratio(s, rho[0]);
+    if (blockIdx.x == 0) {
+        const double t = rr.part == num.part ? s : sum_partials<NT>(rr, sr);
+        if (threadIdx.x == 0) {
+            rho_new[0] = s;
+            rr_out[0] = t;
+        }
+    }
+    for (;;) {
+#pragma unroll
+        for (int q = 0; q < U; ++q) {
+            const long k = k0 + q * NT;
+            if (k < n) p[k] = T(double(zv[q]) + b * double(pv[q]));
+        }
+        k0 += step;
+        if (k0 >= n) break;
+        load();
+    }
 }
 
-// Mixed-precision CG vectors: the iterate and residual in FP64, the
-// direction in FP32, the precision the operator reads it in.
+// Mixed-precision CG vectors: the iterate in FP64, residual and direction in
+// FP32, the precision the operator reads it in.
 // p32 = (float) r
 static __global__ void k_cgm_start(float* __restrict__ p32, const double* __restrict__ r, long n) {
     for (long k = (long)blockIdx.x * blockDim.x + threadIdx.x; k < n; k += (long)gridDim.x * blockDim.x)
         p32[k] = float(r[k]);
 }
-// x += a p32 (FP64 iterate);  r32 -= a Ap32 (formed in FP64, stored in
-// FP32: the recursively updated residual is replaced by the FP64 one before
-// its rounding accumulates); partial |r32|^2 in FP64, a = num / den
-static __global__ void k_cgm_update(double* __restrict__ x, const float* __restrict__ p32, float* __restrict__ r32,
-                                    const float* __restrict__ Ap32, const double* __restrict__ num,
-                                    const double* __restrict__ den, long n, double* __restrict__ part) {
-    const double a = dev_ratio(num, den);
-    double acc[1] = {0.0};
-    for (long k = (long)blockIdx.x * blockDim.x + threadIdx.x; k < n; k += (long)gridDim.x * blockDim.x) {
-        x[k] += a * double(p32[k]);
-        const float rk = float(double(r32[k]) - a * double(Ap32[k]));
-        r32[k] = rk;
-        acc[0] += double(rk) * double(rk);
-    }
-    ew_block_reduce<1>(acc, part);
-}
-// p32 = (float) (r + b p32), b = num / den
-static __global__ void k_cgm_dir(float* __restrict__ p32, const float* __restrict__ r32,
-                                 const double* __restrict__ num, const double* __restrict__ den,
-                                 double* __restrict__ save, long n) {
-    const double b = dev_ratio(num, den);
-    keep_rho(save, num);
-    for (long k = (long)blockIdx.x * blockDim.x + threadIdx.x; k < n; k += (long)gridDim.x * blockDim.x)
-        p32[k] = float(double(r32[k]) + b * double(p32[k]));
-}
 // r32 = (float) r (the FP64 residual of a replacement)
 static __global__ void k_to32(float* __restrict__ r32, const double* __restrict__ r, long n) {
     for (long k = (long)blockIdx.x * blockDim.x + threadIdx.x; k < n; k += (long)gridDim.x * blockDim.x)
         r32[k] = float(r[k]);
-}
-
-// Preconditioned CG directions: p = z + b p, b = num / den
-template <class T>
-__global__ void k_pcg_dir(T* __restrict__ p, const T* __restrict__ z, const double* __restrict__ num,
-                          const double* __restrict__ den, double* __restrict__ save, long n) {
-    const double b = dev_ratio(num, den);
-    keep_rho(save, num);
-    for (long k = (long)blockIdx.x * blockDim.x + threadIdx.x; k < n; k += (long)gridDim.x * blockDim.x)
-        p[k] = T(double(z[k]) + b * double(p[k]));
-}
-// mixed, preconditioned: p32 = (float) (z32 + b p32), b = num / den
-static __global__ void k_pcgm_dir(float* __restrict__ p32, const float* __restrict__ z32,
-                                  const double* __restrict__ num, const double* __restrict__ den,
-                                  double* __restrict__ save, long n) {
-    const double b = dev_ratio(num, den);
-    keep_rho(save, num);
-    for (long k = (long)blockIdx.x * blockDim.x + threadIdx.x; k < n; k += (long)gridDim.x * blockDim.x)
-        p32[k] = float(double(z32[k]) + b * double(p32[k]));
 }
 
 // Verlet adjoint helpers
@@ -1655,12 +1678,6 @@ __global__ void k_vva_final(T* __restrict__ ub, T* __restrict__ vb, T* __restric
         vb[k] = ak + dt * utk;
         if (bb) bb[k] += c2 * utk + T(2) * c1 * ak;
     }
-}
-
-template <int NR>
-pd_status ew_finish(pd_plan p, unsigned nblk, double* out, hipStream_t st, double* host = nullptr) {
-    hipLaunchKernelGGL(k_reduce_final, dim3(1), dim3(256), 0, st, p->partials, (long)nblk, NR, out, host);
-    return pdh::check(hipGetLastError());
 }
 
 inline pd_status fetch_red(pd_plan p, int n, hipStream_t st, double* dst) {
@@ -2080,10 +2097,10 @@ struct LagRead {
         ev[1] = p->lag_ev[1];
         return (ev[0] && ev[1]) ? PD_OK : PD_EDEVICE;
     }
-    // host slot of iteration k as the reduction kernel addresses it
-    double* dslot(int k) const { return hd ? hd + (k & 1) : nullptr; }
-    pd_status post(int k, const double* src, hipStream_t st) {
-        if (!hd) HIP_TRY(hipMemcpyAsync(h + (k & 1), src, sizeof(double), hipMemcpyDeviceToHost, st));
+    // where k_cg_dir puts |r|^2 of iteration k: the host slot, or dev
+    double* out(int k, double* dev) const { return hd ? hd + (k & 1) : dev; }
+    pd_status post(int k, const double* dev, hipStream_t st) {
+        if (!hd) HIP_TRY(hipMemcpyAsync(h + (k & 1), dev, sizeof(double), hipMemcpyDeviceToHost, st));
         return pdh::check(hipEventRecord(ev[k & 1], st));
     }
     pd_status get(int k, double* v) {
@@ -2093,9 +2110,38 @@ struct LagRead {
     }
 };
 // Device slots of red used by the solvers: [0] the operator's or the
-// preconditioner's reduction, [2] |r|^2 of the last update, [6 + (k & 1)]
-// rho of iteration k (r.r, or r.z when preconditioned).
+// preconditioner's reduction where it is finished, [2] |r|^2 of the last
+// update, [6 + (k & 1)] rho of iteration k (r.r, or r.z when preconditioned).
 constexpr int kRedRR = 2, kRedRho = 6;
+
+// One CG iteration on plan p: Ap = A pp, x += a pp, r -= a Ap, then
+// pp = r + b pp, or z + b pp with z = M^-1 r (z null: no preconditioner).
+template <class TX, class T>
+pd_status cg_iteration(pd_plan p, int k, TX* x, T* r, T* pp, T* Ap, T* z, LagRead& lag, hipStream_t st) {
+    const long n = p->nb * p->dim;
+    const unsigned nb = cg_blocks(n);
+    double* rho = p->red + kRedRho + (k & 1);
+    double* rho_new = p->red + kRedRho + ((k + 1) & 1);
+    struct Raw {   // sums left to their readers until the iteration is queued
+        pd_plan p;
+        ~Raw() { p->raw_sum = false; }
+    } raw{p};
+    p->raw_sum = true;
+    PD_TRY((lin_apply<T, 2>(p, pp, Ap, nullptr, st)));   // p->sum = pp . Ap
+    hipLaunchKernelGGL((k_cg_update<TX, T>), dim3(nb), dim3(kCgThreads), 0, st, x, (const T*)pp, r, (const T*)Ap,
+                       (const double*)rho, p->sum, n, p->cg_partials);
+    PD_TRY(pdh::check(hipGetLastError()));
+    const PartialSum rr{p->cg_partials, (long)nb};
+    PartialSum num = rr;
+    if (z) {
+        PD_TRY((precond_apply<T, T, T>(p, r, z, st)));   // p->sum = r . z
+        num = p->sum;
+    }
+    hipLaunchKernelGGL(k_cg_dir<T>, dim3(nb), dim3(kCgThreads), 0, st, pp, (const T*)(z ? z : r), num,
+                       (const double*)rho, rho_new, rr, lag.out(k, p->red + kRedRR), n);
+    PD_TRY(pdh::check(hipGetLastError()));
+    return lag.post(k, p->red + kRedRR, st);
+}
 
 // Drive a CG loop whose iterations are queued by issue(k): issue more while
 // the lagged |r|^2 is above stop2, then confirm on the last iteration's value
@@ -2138,18 +2184,7 @@ pd_status cg_run(pd_plan p, TX* x_unused, T* xT, T* r, T* pp, T* Ap, double rr0,
     HIP_TRY(hipMemcpyAsync(pp, r, sizeof(T) * n, hipMemcpyDeviceToDevice, st));
     p->red_host[kRedRho] = rr0;
     HIP_TRY(hipMemcpyAsync(dev + kRedRho, p->red_host + kRedRho, sizeof(double), hipMemcpyHostToDevice, st));
-    auto issue = [&](int k) -> pd_status {
-        double* rho = dev + kRedRho + (k & 1);
-        double* rho_new = dev + kRedRho + ((k + 1) & 1);
-        PD_TRY((lin_apply<T, 2>(p, pp, Ap, nullptr, st)));   // red[0] = p.Ap
-        hipLaunchKernelGGL((k_cg_update<T, T>), dim3(nb), dim3(EW_THREADS), 0, st, xT, (const T*)pp, r, (const T*)Ap,
-                           (const double*)rho, (const double*)dev, n, p->partials);
-        PD_TRY(ew_finish<1>(p, nb, rho_new, st, lag.dslot(k)));
-        PD_TRY(lag.post(k, rho_new, st));
-        hipLaunchKernelGGL(k_cg_dir<T>, dim3(nb), dim3(EW_THREADS), 0, st, pp, (const T*)r, (const double*)rho_new,
-                           (const double*)rho, (double*)nullptr, n);
-        return pdh::check(hipGetLastError());
-    };
+    auto issue = [&](int k) -> pd_status { return cg_iteration<T, T>(p, k, xT, r, pp, Ap, nullptr, lag, st); };
     int it = 0;
     double rr = rr0;
     PD_TRY(cg_drive(lag, stop2, maxit, &it, &rr, issue));
@@ -2251,18 +2286,7 @@ inline pd_status static_solve_impl(pd_plan p, const double* b, const double* w, 
             SOLVE_TRY(pdh::check(hipMemcpyAsync(dev + kRedRho, dev, sizeof(double), hipMemcpyDeviceToDevice, st)));
             SOLVE_TRY(pdh::check(hipMemcpyAsync(pp, z, sizeof(double) * n, hipMemcpyDeviceToDevice, st)));
             auto issue = [&](int k) -> pd_status {
-                double* rho = dev + kRedRho + (k & 1);
-                double* rho_new = dev + kRedRho + ((k + 1) & 1);
-                PD_TRY((lin_apply<double, 2>(p, pp, Ap, nullptr, st)));   // red[0] = p.Ap
-                hipLaunchKernelGGL((k_cg_update<double, double>), dim3(nb), dim3(EW_THREADS), 0, st, u,
-                                   (const double*)pp, r, (const double*)Ap, (const double*)rho, (const double*)dev, n,
-                                   p->partials);
-                PD_TRY(ew_finish<1>(p, nb, dev + kRedRR, st, lag.dslot(k)));
-                PD_TRY(lag.post(k, dev + kRedRR, st));
-                PD_TRY((precond_apply<double, double, double>(p, r, z, st)));   // red[0] = r.z
-                hipLaunchKernelGGL(k_pcg_dir<double>, dim3(nb), dim3(EW_THREADS), 0, st, pp, (const double*)z,
-                                   (const double*)dev, (const double*)rho, rho_new, n);
-                return pdh::check(hipGetLastError());
+                return cg_iteration<double, double>(p, k, u, r, pp, Ap, z, lag, st);
             };
             SOLVE_TRY(cg_drive(lag, stop2, maxit, &it, &rr, issue));
             inf.applies_fp64 += it;
@@ -2307,22 +2331,7 @@ inline pd_status static_solve_impl(pd_plan p, const double* b, const double* w, 
         }
         SOLVE_TRY(pdh::check(hipGetLastError()));
         auto issue = [&](int k) -> pd_status {
-            double* rho = dev + kRedRho + (k & 1);
-            double* rho_new = dev + kRedRho + ((k + 1) & 1);
-            PD_TRY((lin_apply<float, 2>(q, p32, Ap32, nullptr, st)));   // q->red[0] = p32 . Ap32
-            hipLaunchKernelGGL(k_cgm_update, dim3(nb), dim3(EW_THREADS), 0, st, u, (const float*)p32, r32,
-                               (const float*)Ap32, (const double*)rho, (const double*)dev, n, q->partials);
-            PD_TRY(ew_finish<1>(q, nb, dev + kRedRR, st, lag.dslot(k)));
-            PD_TRY(lag.post(k, dev + kRedRR, st));
-            if (pre) {
-                PD_TRY((precond_apply<float, float, float>(q, r32, z32, st)));   // q->red[0] = r.z
-                hipLaunchKernelGGL(k_pcgm_dir, dim3(nb), dim3(EW_THREADS), 0, st, p32, (const float*)z32,
-                                   (const double*)dev, (const double*)rho, rho_new, n);
-            } else {
-                hipLaunchKernelGGL(k_cgm_dir, dim3(nb), dim3(EW_THREADS), 0, st, p32, (const float*)r32,
-                                   (const double*)(dev + kRedRR), (const double*)rho, rho_new, n);
-            }
-            return pdh::check(hipGetLastError());
+            return cg_iteration<double, float>(q, k, u, r32, p32, Ap32, pre ? z32 : nullptr, lag, st);
         };
         double rr_rep = rr;   // |r|^2 at the last replacement
         int it = 0, fresh = 0;  // iterations from `fresh` on follow the last replacement

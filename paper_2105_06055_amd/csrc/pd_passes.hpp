@@ -579,11 +579,11 @@ struct QLoop<NQ, NQ> {
 
 // block Lw*(N/8) (Lw lines), LDS Lw*line_pitch(N) + N complex.  From 512
 // points on a line fills whole waves and its taps are wave-uniform (scalar
-// loads); a 256-point line is half a wave, and the taps are per-lane loads.
+// loads); shorter lines share a wave, and the taps are per-lane loads.
 template <class T, class M, int LG, int NT>
 __global__ void __launch_bounds__(256) k_lastmul_f(Lines ln, M mul, cx<T>* S, const T* __restrict__ taps, int nct,
                                                    const cx<T>* __restrict__ twb) {
-    static_assert(LG >= 8 && NT >= 1 && !M::RT_ODD, "specialised pass needs N >= 256");
+    static_assert(LG >= 6 && NT >= 1 && !M::RT_ODD, "specialised pass needs N >= 64");
     extern __shared__ __align__(16) unsigned char smem_raw[];
     cx<T>* lds = reinterpret_cast<cx<T>*>(smem_raw);
     constexpr int NI = M::NIN, NO = M::NOUT, N = 1 << LG, Tn = N >> 3;
@@ -1517,6 +1517,31 @@ static __global__ void k_reduce_final(const double* __restrict__ part, long nblk
         }
         __syncthreads();
     }
+}
+
+// A sum that its reader forms from n partials (n = 1: a finished sum).
+struct PartialSum {
+    const double* part;
+    long n;
+};
+// Block-wide deterministic sum of the partials, in every thread (blocks of NT
+// threads; sm: NT / 64 doubles that nothing else uses).  The loads and two
+// shuffle trees take ~2 us in each block of the reader, where a kernel of its
+// own took 4.2 us and a gap.
+template <int NT>
+__device__ __forceinline__ double sum_partials(const PartialSum& p, double* sm) {
+    constexpr int NW = NT / 64;
+    static_assert(NW >= 1 && NW <= 64 && (NW & (NW - 1)) == 0, "whole waves, a power of two");
+    double s = 0.0;
+    for (long k = threadIdx.x; k < p.n; k += NT) s += p.part[k];
+#pragma unroll
+    for (int w = 32; w > 0; w >>= 1) s += __shfl_xor(s, w);
+    if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = s;
+    __syncthreads();
+    double t = sm[threadIdx.x & (NW - 1)];
+#pragma unroll
+    for (int w = NW / 2; w > 0; w >>= 1) t += __shfl_xor(t, w);
+    return t;
 }
 
 }  // namespace pdk

@@ -69,6 +69,9 @@ struct pd_plan_s {
     void* vtmp2;                 // T [dim][nb]
     double* partials;            // per-block reduction partials
     long partials_cap;
+    double* cg_partials;         // those of the solver's vector updates [kCgBlocks]
+    bool raw_sum;                // finish_reduction leaves single sums to their reader
+    pdk::PartialSum sum;         // the last single sum
     double* red;                 // final reductions [8]
     double* red_host;            // pinned host copy [16]
     double* red_host_dev;        // device address of red_host (null if not mapped)
@@ -83,7 +86,6 @@ struct pd_plan_s {
     // radial factors c and a with C_ij(o) = c[r^2] o_i o_j, a_i(o) = a[r^2] o_i
     int dir_mt;
     double dir_c[65], dir_a[65];
-    int dir_nzc;                 // 3D: chunks along z
     long dir_blocks;             // most blocks of a launch (reduction partials)
     size_t bytes;
     std::vector<ProfRec>* prof;  // non-null while pass timing is enabled
@@ -140,5 +142,22 @@ struct ProfScope {
         a = nullptr;
     }
 };
+
+constexpr int kCgBlocks = 1024;   // most blocks of a CG vector kernel
+
+// p->red[0 .. nr) = the sums of the blocks' partials; or, for a single sum
+// whose reader forms it itself (p->raw_sum), no launch.  Beyond 4096 partials
+// a reader of kCgBlocks blocks would spend more on them than the launch
+// takes: 32 MB from the L2s, ~4 us.
+inline pd_status finish_reduction(pd_plan p, long nblk, int nr, hipStream_t st) {
+    if (p->raw_sum && nr == 1 && nblk <= 4096) {
+        p->sum = {p->partials, nblk};
+        return PD_OK;
+    }
+    p->sum = {p->red, 1};
+    hipLaunchKernelGGL(pdk::k_reduce_final, dim3(1), dim3(256), 0, st, p->partials, nblk, nr, p->red,
+                       (double*)nullptr);
+    return pdh::check(hipGetLastError());
+}
 
 }  // namespace pdi
