@@ -317,12 +317,16 @@ pd_status dir2_verlet_adjoint(pd_plan p, const T* un, const T* unp1, const T* s,
 
 template <class T>
 pd_status dir2_damage(pd_plan p, const uint8_t* lam, T* d, hipStream_t st) {
-    uint64_t member = 0;
-    for (int q = 1; q <= 64; ++q)
-        if (p->dir_c[q] != 0.0) member |= 1ull << (q - 1);
+    const int M = p->dir_mt;
+    DiscRows rows{};
+    for (int b = -M; b <= M; ++b)
+        for (int a = -M; a <= M; ++a) {
+            const int r2 = a * a + b * b;
+            if (r2 == 0 || (r2 <= M * M && p->dir_c[r2] != 0.0)) rows.mask[b + M] |= 1u << (a + M);
+        }
     ProfScope ps(p, st);
-    hipLaunchKernelGGL((k_damage2<T>), dim3((unsigned)((p->geo.b1 + 63) / 64), (unsigned)((p->geo.b2 + 3) / 4)),
-                       dim3(256), 0, st, geo2(p), p->dir_mt, member, pdi::ctx<T>(p), p->beta_comp, lam, d);
+    hipLaunchKernelGGL((k_damage2<T>), dim3((unsigned)((p->geo.b1 + 63) / 64), (unsigned)((p->geo.b2 + 7) / 8)),
+                       dim3(256), 0, st, geo2(p), M, rows, pdi::ctx<T>(p), p->beta_comp, lam, d);
     if (p->prof) ps.done("damage2", (double)p->nb * (2.0 + sizeof(T)));
     return pdh::check(hipGetLastError());
 }
