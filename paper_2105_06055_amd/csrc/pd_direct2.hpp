@@ -166,9 +166,11 @@ __global__ void __launch_bounds__(TL::NT) k_dir2(D2Geo g, Radial<T, M> tp, Args2
         TL::template row<R>(s0 + c + b * W, w0);
         TL::template row<R>(s1 + c + b * W, w1);
         TL::template row<R>(sp + c + b * W, wp);
-        T rs[NX];   // sum of s along the row (it enters L_y times b)
+        // sums along the row (short chains round less; that of s enters L_y
+        // times b)
+        T rs[NX], ra[NX], re[NX];
 #pragma unroll
-        for (int n = 0; n < NX; ++n) rs[n] = T(0);
+        for (int n = 0; n < NX; ++n) rs[n] = ra[n] = re[n] = T(0);
         each<0, 2 * R + 1>([&](auto ac) {
             constexpr int a = decltype(ac)::value - R, r2 = a * a + b * b;
             if constexpr (r2 > 0) {
@@ -178,15 +180,17 @@ __global__ void __launch_bounds__(TL::NT) k_dir2(D2Geo g, Radial<T, M> tp, Args2
                     if constexpr (a != 0) e += T(a) * (w0[RA + n + a] - u0[n]);
                     if constexpr (b != 0) e += T(b) * (w1[RA + n + a] - u1[n]);
                     const T s = tp.k[r2] * wp[RA + n + a] * e;
-                    if constexpr (a != 0) a0[n] += T(a) * s;
+                    if constexpr (a != 0) ra[n] += T(a) * s;
                     if constexpr (b != 0) rs[n] += s;
-                    if constexpr (WE) en[n] += s * e;
+                    if constexpr (WE) re[n] += s * e;
                 }
             }
         });
-        if constexpr (b != 0) {
 #pragma unroll
-            for (int n = 0; n < NX; ++n) a1[n] += T(b) * rs[n];
+        for (int n = 0; n < NX; ++n) {
+            if constexpr (R > 0) a0[n] += ra[n];
+            if constexpr (b != 0) a1[n] += T(b) * rs[n];
+            if constexpr (WE) en[n] += re[n];
         }
     });
     double red[NR > 0 ? NR : 1];
@@ -360,9 +364,9 @@ __global__ void __launch_bounds__(TL::NT) k_adj2(D2Geo g, Radial<T, M> tp, ArgsA
         TL::template row<R>(q0 + c + b * W, h0);
         TL::template row<R>(q1 + c + b * W, h1);
         TL::template row<R>(sp + c + b * W, wp);
-        T rs[NX];
+        T rs[NX], ra[NX], rp[NX];   // sums along the row
 #pragma unroll
-        for (int n = 0; n < NX; ++n) rs[n] = T(0);
+        for (int n = 0; n < NX; ++n) rs[n] = ra[n] = rp[n] = T(0);
         each<0, 2 * R + 1>([&](auto ac) {
             constexpr int a = decltype(ac)::value - R, r2 = a * a + b * b;
             if constexpr (r2 > 0) {
@@ -378,15 +382,17 @@ __global__ void __launch_bounds__(TL::NT) k_adj2(D2Geo g, Radial<T, M> tp, ArgsA
                         f += T(b) * (h1[RA + n + a] - g1[n]);
                     }
                     const T s = tp.k[r2] * wp[RA + n + a] * f;
-                    if constexpr (a != 0) a0[n] += T(a) * s;
+                    if constexpr (a != 0) ra[n] += T(a) * s;
                     if constexpr (b != 0) rs[n] += s;
-                    pb[n] += s * e;
+                    rp[n] += s * e;
                 }
             }
         });
-        if constexpr (b != 0) {
 #pragma unroll
-            for (int n = 0; n < NX; ++n) a1[n] += T(b) * rs[n];
+        for (int n = 0; n < NX; ++n) {
+            if constexpr (R > 0) a0[n] += ra[n];
+            if constexpr (b != 0) a1[n] += T(b) * rs[n];
+            pb[n] += rp[n];
         }
     });
     if (nx <= 0) return;
@@ -544,6 +550,9 @@ __global__ void __launch_bounds__(TL::NT) k_nbb2(D2Geo g, Radial<T, M> tp, T dx,
         TL::template row<R>(s0 + c + b * W, w0);
         TL::template row<R>(s1 + c + b * W, w1);
         TL::template row<R>(sp + c + b * W, wp);
+        T rs[NX], ra[NX], r0[NX], r1[NX];   // sums along the row
+#pragma unroll
+        for (int n = 0; n < NX; ++n) rs[n] = ra[n] = r0[n] = r1[n] = T(0);
         each<0, 2 * R + 1>([&](auto ac) {
             constexpr int a = decltype(ac)::value - R, r2 = a * a + b * b;
             if constexpr (r2 > 0) {
@@ -552,13 +561,20 @@ __global__ void __launch_bounds__(TL::NT) k_nbb2(D2Geo g, Radial<T, M> tp, T dx,
                     const T h0 = w0[RA + n + a] - u0[n], h1 = w1[RA + n + a] - u1[n];
                     const T e = T(a) * h0 + T(b) * h1;
                     const T s = tp.k[r2] * wp[RA + n + a] * (dx2 * e + h0 * h0 + h1 * h1);
-                    o0[n] += T(a) * s;
-                    o1[n] += T(b) * s;
-                    e0[n] += s * h0;
-                    e1[n] += s * h1;
+                    if constexpr (a != 0) ra[n] += T(a) * s;
+                    if constexpr (b != 0) rs[n] += s;
+                    r0[n] += s * h0;
+                    r1[n] += s * h1;
                 }
             }
         });
+#pragma unroll
+        for (int n = 0; n < NX; ++n) {
+            if constexpr (R > 0) o0[n] += ra[n];
+            if constexpr (b != 0) o1[n] += T(b) * rs[n];
+            e0[n] += r0[n];
+            e1[n] += r1[n];
+        }
     });
     if (nx <= 0) return;
     T out[2][NX];
