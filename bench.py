@@ -5,13 +5,13 @@ Workload (default): 3D linearized state-based (LPS) block with 8 seeded
 ellipsoidal voids, 256^3 body nodes on a 512^3 FFT grid, delta = 3 dx,
 E = 70 GPa, nu = 0.25, FP32, seeded impulsive velocity on the x = 0 face.
 A "step" is one embedded-constraint velocity-Verlet step: position update,
-the two-stage LPS force (dilatation convolution, then force convolutions;
-forward real FFTs, spectral multiply, inverse FFTs, assembly) and the
-velocity update.  value = body nodes x steps / time (Gnode/s).
+the two-stage LPS force (dilatation, then force: the convolutions as direct sums
+over the horizon, or on the transform paths forward real FFTs, spectral
+multiply, inverse FFTs, assembly) and the velocity update.
+value = body nodes x steps / time (Gnode/s).
 
-Also reported: the same step in FP64 and in FP32 with transforms along all
-three axes (the last axis otherwise uses the equivalent direct line
-correlation), pd_force alone, per-pass HIP-event timings over the timed
+Also reported: the same step in FP64 and in FP32 with transforms along two
+and all three axes, pd_force alone, per-pass HIP-event timings over the timed
 steps with algorithmic bytes (roofline of the dominant pass; its HBM traffic
 from the committed rocprofv3 counter summary when the sources match), the
 elastostatic CG time to a 1e-10 relative residual on the 128^3-node /
@@ -90,8 +90,8 @@ def pass_roofline(passes, steps):
 
 def run_m_crossover(nb, nfft, reps, warmup, ms=(2, 3, 4, 6)):
     """pd_force (FP32 LPS, the voided block) at horizons of m = delta/dx
-    spacings, on each path the plan offers: the default (the direct (y, z)
-    correlation for m <= 3, else the y transform), the y transform with the
+    spacings, on each path the plan offers: the default (direct horizon sums
+    up to 4 spacings, else the y transform), the y transform with the
     direct z line correlation (transform form beyond 4 spacings) and
     transforms along all three axes."""
     import torch
@@ -497,7 +497,7 @@ def main():
     ap.add_argument("--cg-fft", type=int, default=256)
     ap.add_argument("--lastaxis", choices=("auto", "yfft", "fft"), default="auto",
                     help="force path of the headline step (for profiling the transform paths on their own): "
-                         "auto = the (y, z) correlation pass, yfft = y transform + direct z line correlation, "
+                         "auto = direct horizon sums, yfft = y transform + direct z line correlation, "
                          "fft = transforms on all three axes")
     ap.add_argument("--copy-calib", action="store_true",
                     help="run one 1 GiB device copy first (reference for HBM byte counters)")
@@ -559,7 +559,7 @@ def main():
                          "finite": rm["finite"], "roofline": rf, "passes": rm["passes"]})
             log(f"[bench] min-padding n1={n1}: step {rm['s_per_step'] * 1e3:.3f} ms")
         minpad = {"workload": f"FP32 LPS EC Verlet step, {args.size}^3 voided block, x grid n1 (y, z grids "
-                              f"{args.fft}; the (y, z) pass works on the body planes only)", "rows": rows}
+                              f"{args.fft}; the direct sums use no grid beyond the body)", "rows": rows}
     mcross = None
     if not args.no_mcross:
         mcross = {"workload": f"FP32 LPS pd_force, {args.size}^3 voided block on {args.fft}^3, delta = m dx",
@@ -654,7 +654,7 @@ def main():
         "config": {"workload": f"3D LPS EC velocity-Verlet step, {args.size}^3 body nodes (8 seeded ellipsoidal "
                                f"voids) on a {args.fft}^3 FFT grid, delta=3dx, E=70GPa, nu=0.25",
                    "body_nodes": nodes, "fft_grid": args.fft ** 3, "parallelism": "single GPU",
-                   "path": {"auto": "x transform + (y, z) correlation", "yfft": "x, y transforms + z line correlation",
+                   "path": {"auto": "direct horizon sums", "yfft": "x, y transforms + z line correlation",
                             "fft": "transforms on all three axes"}[args.lastaxis]},
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS,

@@ -23,15 +23,21 @@ extern "C" {
  * Synchronises the stream. */
 pd_status pd_test_conv(pd_plan plan, const void* x, const int* shift, int parity, void* out, void* stream);
 
-/* Kernel selection after the x transform, for A/B tests (every later call
- * on `plan`, and on its FP32 operator for PD_PLAN_MIXED plans):
- *   PD_LASTAXIS_AUTO         3D: direct 2D correlation over (y, z) per
+/* Kernel selection, for A/B tests (every later call on `plan`, and on its
+ * FP32 operator for PD_PLAN_MIXED plans):
+ *   PD_LASTAXIS_AUTO         (default) equal spacings along all axes and a
+ *                            horizon of up to 8 (2D) or 4 (3D) spacings:
+ *                            direct sums over the horizon, no transforms
+ *                            (but for the convolution form of W and, in 3D,
+ *                            the nonlinear model at 4 spacings).  Otherwise,
+ *                            after the x transform,
+ *                            3D: direct 2D correlation over (y, z) per
  *                            x-wavenumber when the horizon's (y, z) footprint
  *                            is a disc of radius 2 or 3 spacings, for the LPS
  *                            and unweighted bond-based chains; otherwise as
  *                            PD_LASTAXIS_YFFT.
- *                            2D: as PD_LASTAXIS_YFFT (default)
- *   PD_LASTAXIS_YFFT         transform along y (3D), then the direct line
+ *                            2D: as PD_LASTAXIS_YFFT
+ *   PD_LASTAXIS_YFFT         transforms along x and y (3D), then the direct line
  *                            correlation along the last axis when the horizon
  *                            spans at most 4 spacings there, else the
  *                            transform form

@@ -305,9 +305,10 @@ class Plan:
     LASTAXIS = {"auto": 0, "fft": 1, "fft_generic": 2, "yfft": 3}
 
     def set_lastaxis(self, mode="auto"):
-        """Kernel choice after the x transform (A/B tests): 'auto' (3D: the
-        direct (y, z) correlation where it applies), 'yfft' (transform along
-        y, direct line correlation along the last axis), 'fft' (transforms on
+        """Kernel choice (A/B tests): 'auto' (direct horizon sums where they
+        apply, else in 3D the direct (y, z) correlation where that applies),
+        'yfft' (transform along x and, in 3D, y, direct line correlation
+        along the last axis), 'fft' (transforms on
         every axis, spectral multiply, specialised where it applies) or
         'fft_generic'."""
         _check(lib().pd_test_set_lastaxis(self._h, self.LASTAXIS[mode]), "pd_test_set_lastaxis")

@@ -31,9 +31,11 @@
 // nodes takes them from scalar registers.
 //
 // Measured, 256^3 LPS body in FP32, one Verlet step: dilatation 139 us, force
-// stage 288 us (0.94 ms per step for the x transforms and (y, z) passes): the
-// vector ALU is busy about 60 % of the time, and the force stage moves 1.3 GB
-// (0.9 GB of fields read and written once, the rest tile and chunk halos).
+// stage 288 us (0.94 ms per step for the x transforms and (y, z) passes).  The
+// force stage issues 1.27e8 wave instructions (485 per node: 208 us at one per
+// CU and cycle, 72 % of the time) and moves 1.25 GB (0.97 GB of fields), the
+// dilatation 4.6e7 (176 per node, 55 %, its LDS pipe as busy) and 0.53 GB (0.31
+// GB of fields, the rest tile and chunk halos: 3.8 TB/s).
 #pragma once
 
 #include <algorithm>

@@ -13,7 +13,7 @@
 // registers.  A plate of 400,000 nodes (48 bonds) stays in the caches, so one
 // launch per step replaces four passes over padded spectra; the sums are
 // bound by the vector ALU (~9 instructions a bond).  Measured against the
-// transform passes: 20 FP32 fracture steps of the 1000 x 400 plate 1461 -> 269
+// transform passes: 20 FP32 fracture steps of the 1000 x 400 plate 1461 -> 281
 // us, 20 FP64 steps of a 601 x 241 plate at six spacings 3912 -> 358 us, 10
 // steps forward and backward on the 512 x 512 plate 3215 -> 680 us, the force
 // of a 64 x 64 plate 22.4 -> 9.1 us.

@@ -2177,7 +2177,6 @@ pd_status cg_run(pd_plan p, TX* x_unused, T* xT, T* r, T* pp, T* Ap, double rr0,
                  int* applies, double* rr_out, hipStream_t st) {
     (void)x_unused;
     const long n = p->nb * p->dim;
-    const unsigned nb = ew_blocks(n);
     double* dev = p->red;
     LagRead lag;
     PD_TRY(lag.init(p));

@@ -9,6 +9,10 @@
 // periodic box (Sec. 4.2.2) is known to be zero on the way in and is not
 // needed on the way out, so each pass is pruned to the body extent.
 //
+// Equal spacings with a horizon of up to 8 (2D) or 4 (3D) spacings take the
+// sums of pd_direct.hpp instead; these passes serve the others, the
+// preconditioner and the test modes.
+//
 // Passes (2D: xfwd, lastmul, xinv; 3D: xfwd, ytf, lastmul, yti, xinv):
 //   k_xfwd     real rows of the body -> generator -> r2c FFT along x (length
 //              n1 via an n1/2 complex FFT) -> transposed store into SA
