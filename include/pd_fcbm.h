@@ -160,6 +160,7 @@ pd_status pd_plan_query(pd_plan plan, pd_plan_info* info);
  *          dtype s [body] for SCALE
  *   L_out  [dim][body]  force density (N/m^3), zero outside chi_B
  *   W_out  [body] strain energy density (Eq. 102) or NULL; bond-based only
+ * L_out may be u where W_out is NULL (in place).
  * PD_EINVAL for NULL u/L_out or a weight that does not match the plan. */
 pd_status pd_force(pd_plan plan, const void* u, const void* weight, void* L_out, void* W_out,
                    void* stream);
@@ -169,6 +170,7 @@ pd_status pd_force(pd_plan plan, const void* u, const void* weight, void* L_out,
  *              operator is symmetric for fixed weights)
  *   weight_bar [body] = d<g_bar, L>/d weight, only for PD_WEIGHT_SCALE
  *              (NULL to skip); bond-based only.
+ * u_bar may be g_bar or u, and weight_bar may be weight (in place).
  * Derived from Eq. 46/100 (the paper gives no adjoint). */
 pd_status pd_force_adjoint(pd_plan plan, const void* u, const void* weight, const void* g_bar,
                            void* u_bar, void* weight_bar, void* stream);

@@ -11,6 +11,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <initializer_list>
 #include <type_traits>
 #include <vector>
 
@@ -1381,6 +1382,39 @@ pd_status run_lps(pd_plan p, const GA& gA, const FinTheta<T>& fA, const MulLPSB<
     return run_chain<T>(p, gB, mB, fB, st, 3);
 }
 
+// In-place calls (L_out == u, u_bar == g_bar, weight_bar == s, ...).  A block
+// of the direct sums reads its neighbours' inputs while other blocks store
+// their results, so an input that overlaps a result is read from a copy.  The
+// copies lie in SA, the transform passes' workspace, which a direct call leaves
+// free: at least 2 dim + 3 complex fields of body size, for at most 2 dim + 3
+// real ones.
+struct Mem {
+    const void* p;
+    size_t bytes;
+    bool overlaps(const Mem& o) const {
+        const uintptr_t a = reinterpret_cast<uintptr_t>(p), b = reinterpret_cast<uintptr_t>(o.p);
+        return p && o.p && a < b + o.bytes && b < a + bytes;
+    }
+};
+template <class T>
+struct Inputs {
+    pd_plan p;
+    hipStream_t st;
+    size_t used = 0;   // bytes of SA
+    // in: n values, replaced by the copy where a result overlaps them
+    template <class U>
+    pd_status apart(const U*& in, long n, std::initializer_list<Mem> results) {
+        const Mem m{in, sizeof(U) * (size_t)n};
+        if (std::none_of(results.begin(), results.end(), [&](const Mem& r) { return m.overlaps(r); })) return PD_OK;
+        if (used + m.bytes > sizeof(cx<T>) * (size_t)p->geo.saf * p->saf_cap) return PD_EINVAL;
+        U* copy = reinterpret_cast<U*>(reinterpret_cast<char*>(p->SA) + used);
+        used += (m.bytes + 255) / 256 * 256;
+        HIP_TRY(hipMemcpyAsync(copy, in, m.bytes, hipMemcpyDeviceToDevice, st));
+        in = copy;
+        return PD_OK;
+    }
+};
+
 // The two LPS stages as direct sums: theta, then the force of e.u.
 template <class T>
 pd_status lps_direct(pd_plan p, pdd::Eval<T>& e, hipStream_t st) {
@@ -1395,21 +1429,26 @@ pd_status force_impl(pd_plan p, const T* u, const void* weight, T* L, T* W, hipS
     const int D = p->dim;
     const pd_weight_kind wk = p->kern.weight;
     if (wk != PD_WEIGHT_NONE && !weight) return PD_EINVAL;
-    if (pdd::on(p)) {
+    bool direct = pdd::on(p);
+    if (p->kern.model == PD_BB_NONLINEAR) direct = direct && pdd::nbb_on(p);
+    else if (p->kern.model == PD_BB_LINEAR && D == 3) direct = direct && wk == PD_WEIGHT_NONE && !W;
+    else if (p->kern.model == PD_BB_LINEAR) direct = direct && (!W || p->energy_form == PD_ENERGY_DIRECT);
+    if (direct) {
+        if (W && p->kern.model != PD_BB_LINEAR) return PD_EUNSUPPORTED;
+        const Mem mL{L, sizeof(T) * (size_t)(p->nb * D)}, mW{W, sizeof(T) * (size_t)p->nb};
+        Inputs<T> in{p, st};
         pdd::Eval<T> e{};
+        if (wk == PD_WEIGHT_INTEGRITY) e.lam = reinterpret_cast<const uint8_t*>(weight);
+        if (wk == PD_WEIGHT_SCALE) e.s = reinterpret_cast<const T*>(weight);
+        PD_TRY(in.apart(u, p->nb * D, {mL, mW}));
+        PD_TRY(in.apart(e.lam, p->nb, {mL, mW}));
+        PD_TRY(in.apart(e.s, p->nb, {mL, mW}));
         e.u = u;
         e.L = L;
-        if (p->kern.model == PD_LPS_LINEAR) return W ? PD_EUNSUPPORTED : lps_direct<T>(p, e, st);
-        if (p->kern.model == PD_BB_NONLINEAR) {
-            if (pdd::nbb_on(p)) return W ? PD_EUNSUPPORTED : pdd::dir_nbb<T>(p, u, L, st);
-        } else if (D == 3) {
-            if (wk == PD_WEIGHT_NONE && !W) return pdd::dir3_force<T>(p, e, st);
-        } else if (!W || p->energy_form == PD_ENERGY_DIRECT) {
-            e.W = W;
-            if (wk == PD_WEIGHT_INTEGRITY) e.lam = reinterpret_cast<const uint8_t*>(weight);
-            if (wk == PD_WEIGHT_SCALE) e.s = reinterpret_cast<const T*>(weight);
-            return pdd::dir2_force<T>(p, e, st);
-        }
+        e.W = W;
+        if (p->kern.model == PD_LPS_LINEAR) return lps_direct<T>(p, e, st);
+        if (p->kern.model == PD_BB_NONLINEAR) return pdd::dir_nbb<T>(p, u, L, st);
+        return D == 3 ? pdd::dir3_force<T>(p, e, st) : pdd::dir2_force<T>(p, e, st);
     }
     if (p->kern.model == PD_LPS_LINEAR) {
         if (W) return PD_EUNSUPPORTED;
@@ -1695,6 +1734,8 @@ pd_status lin_apply(pd_plan p, const T* x, T* out, const T* b, hipStream_t st) {
     const int D = p->dim;
     if (pdd::on(p)) {
         pdd::Eval<T> e{};
+        Inputs<T> in{p, st};
+        PD_TRY(in.apart(x, p->nb * D, {Mem{out, sizeof(T) * (size_t)(p->nb * D)}}));
         e.mode = MODE;
         e.u = x;
         e.L = out;
@@ -2032,9 +2073,17 @@ pd_status adjoint_impl(pd_plan p, const T* u, const T* u2, const void* weight, c
     if (p->kern.weight != PD_WEIGHT_SCALE || p->kern.model != PD_BB_LINEAR) return PD_EUNSUPPORTED;
     if (!weight) return PD_EINVAL;
     if (p->dim != 2) return PD_EUNSUPPORTED;
-    if (pdd::on(p))
-        return pdd::dir2_adjoint<T>(p, u, u2, reinterpret_cast<const T*>(weight), g, ubar, wbar, wscale, accumulate,
-                                    st);
+    if (pdd::on(p)) {
+        const long n = p->nb * p->dim;
+        const Mem mu{ubar, sizeof(T) * (size_t)n}, mw{wbar, sizeof(T) * (size_t)p->nb};
+        const T* s = reinterpret_cast<const T*>(weight);
+        Inputs<T> in{p, st};
+        PD_TRY(in.apart(u, n, {mu, mw}));
+        PD_TRY(in.apart(u2, n, {mu, mw}));
+        PD_TRY(in.apart(g, n, {mu, mw}));
+        PD_TRY(in.apart(s, p->nb, {mu, mw}));
+        return pdd::dir2_adjoint<T>(p, u, u2, s, g, ubar, wbar, wscale, accumulate, st);
+    }
     auto go = [&](auto Dc) -> pd_status {
         constexpr int DD = decltype(Dc)::value;
         GenAdj<T, DD, WK_SCALE> gg{};
@@ -2065,6 +2114,12 @@ pd_status verlet_adjoint_impl(pd_plan p, const T* un, const T* unp1, const T* s,
     (void)rho;
     if (pdd::on(p) && p->dim == 2) {
         if (sb && p->kern.weight != PD_WEIGHT_SCALE) return PD_EUNSUPPORTED;
+        const size_t vec = sizeof(T) * (size_t)n;
+        const Mem r[4] = {{ub, vec}, {vb, vec}, {bb, vec}, {sb, sizeof(T) * (size_t)p->nb}};
+        Inputs<T> in{p, st};
+        PD_TRY(in.apart(un, n, {r[0], r[1], r[2], r[3]}));
+        PD_TRY(in.apart(unp1, n, {r[0], r[1], r[2], r[3]}));
+        PD_TRY(in.apart(s, p->nb, {r[0], r[1], r[2], r[3]}));
         return pdd::dir2_verlet_adjoint<T>(p, un, unp1, s, ub, vb, sb, bb, c1, c2, T(dt), ut, La, st);
     }
     const void* wgt = (p->kern.weight == PD_WEIGHT_SCALE) ? (const void*)s : nullptr;
