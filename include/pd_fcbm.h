@@ -220,7 +220,8 @@ typedef struct {
  * velocity value of any step became NaN or infinite: the velocity-update
  * epilogue raises a flag, which the call reads once after its last step (it
  * synchronises the stream for that), and with energy_out also if an energy
- * sum is not finite. */
+ * sum is not finite: the call then ends at that step, and u, v, F, W and
+ * lambda are that step's, while state->step counts the steps before it. */
 pd_status pd_verlet_step(pd_plan plan, pd_state* state, const void* b, const void* w, double dt,
                          int nsteps, double* energy_out, void* stream);
 

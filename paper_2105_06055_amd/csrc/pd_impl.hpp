@@ -1984,8 +1984,20 @@ pd_status verlet_direct(pd_plan p, pd_state* S, const T* b, const T* w, double d
         if (p->kern.model == PD_LPS_LINEAR) PD_TRY((lps_direct<T>(p, e, st)));
         else if (p->dim == 3) PD_TRY((pdd::dir3_force<T>(p, e, st)));
         else PD_TRY((pdd::dir2_force<T>(p, e, st)));
+        if (energy) {
+            const pd_status s = verlet_energies(p, dt, energy + 4 * k, st);
+            if (s != PD_OK) {
+                // the call ends at this step: its positions and integrity, where
+                // they are not in the caller's arrays (which hold the next step's)
+                if (cur == 1) {
+                    HIP_TRY(hipMemcpyAsync(ub[0], ub[1], sizeof(T) * (size_t)(p->nb * p->dim),
+                                           hipMemcpyDeviceToDevice, st));
+                    if (lam) HIP_TRY(hipMemcpyAsync(lb[0], lb[1], (size_t)p->nb, hipMemcpyDeviceToDevice, st));
+                }
+                return s;
+            }
+        }
         if (e.next) cur = 1 - cur;
-        if (energy) PD_TRY(verlet_energies(p, dt, energy + 4 * k, st));
         S->step += 1;
     }
     return PD_OK;
