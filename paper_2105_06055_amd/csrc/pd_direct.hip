@@ -340,7 +340,8 @@ pd_status dir_nbb(pd_plan p, const T* u, T* L, hipStream_t st) {
     const Geo& g = p->geo;
     ProfScope ps(p, st);
     pd_status s = PD_EUNSUPPORTED;
-    const double inv = 1.0 / (p->dx[0] * p->dx[0]);   // c per bond, not per o_i o_j
+    // c per bond, not per o_i o_j, for the spacing as the kernel holds it
+    const double dxT = (double)T(p->dx[0]), inv = 1.0 / (dxT * dxT);
     if (p->dim == 2) {
         s = by_radius2(p, [&](auto mc) -> pd_status {
             constexpr int M = decltype(mc)::value;

@@ -1,0 +1,49 @@
+"""FP32 forces of the direct bond sums against FP64 references: the L2 error over
+the field relative to the field, in units of u = 2^-24.
+
+The terms of a bond go through about six roundings (the difference of the
+displacements, the elongation, its product with the kernel value and the
+weight, the sums), each of rms ~0.4 u of the term, and the bonds' errors add up
+as the bonds themselves do, so a force is off by about u; 1.5 u leaves room for
+the sums.  A factor of all bonds that is rounded (the spacing: off by 0.98 u
+here, once in the elongation and once in the direction) would add its whole
+error to every force."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from paper_2105_06055_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+ULP = 2.0 ** -24
+DX = 2.0 ** -10 * (1 + 0.98 * ULP)   # rounds to 2^-10 in FP32
+
+
+def _field(body, amp, seed):
+    """A smooth field with nodal noise, as the oracle and the GPU both hold it."""
+    rng = np.random.default_rng(seed)
+    g = np.meshgrid(*[(np.arange(n) + 0.5) / n for n in body], indexing="ij")
+    u = np.stack([sum(np.sin(2 * np.pi * (1 + (k + d) % 2) * x + rng.uniform(0, 6)) for k, x in enumerate(g))
+                  for d in range(len(body))])
+    return (amp * (0.2 * u + rng.standard_normal(u.shape))).astype(np.float32)
+
+
+def _error(L, Lo):
+    return float(np.linalg.norm(L.double().cpu().numpy() - Lo) / np.linalg.norm(Lo)) / ULP
+
+
+@pytest.mark.parametrize("body,m", [((90, 131), 2), ((90, 131), 3), ((90, 131), 4), ((90, 131), 6), ((90, 131), 8),
+                                    ((25, 34, 43), 2), ((25, 34, 43), 3)])
+def test_nonlinear_force_fp32(orc, body, m):
+    from paper_2105_06055_amd import binding
+    u = _field(body, 0.1 * DX, 91)
+    plan = binding.Plan(tuple(wl._grid_len(n, m) for n in body), body, DX, m * DX, model="nbb", E=72e9,
+                        dtype=torch.float32)
+    Lo = orc.nbb_force(orc.geom(body, DX, m * DX), orc.bb_alpha(len(body), 72e9, m * DX), np.ones(body),
+                       u.astype(np.float64))
+    e = _error(plan.force(torch.tensor(u, device="cuda")), Lo)
+    print(f"nonlinear {body} m={m}: {e:.2f} u", flush=True)
+    assert e <= 1.5, e
+    plan.close()
