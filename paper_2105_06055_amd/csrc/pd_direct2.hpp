@@ -91,6 +91,18 @@ struct Tile2 {
     }
 };
 
+// Type of the sums over the rows of a disc.  The sum along a row is short, the
+// one over the rows runs through terms of b times a row's, which cancel between
+// b and -b: in FP32 it made an unweighted force of eight spacings less accurate
+// than the transforms (L2 error 7.1e-8 against 4.5e-8; in FP64 3.7e-8).  Two
+// conversions and two FP64 adds a row.  The kernels with the energy density
+// keep T: their error is below the weighted transforms' (4 spacings 5.9e-8
+// against 8.9e-8).
+template <class T, bool WIDE>
+struct RowSum {
+    using type = std::conditional_t<WIDE, double, T>;
+};
+
 // ------------------------------------------------------------ force, 2D
 template <class T>
 struct Args2 {
@@ -148,13 +160,16 @@ __global__ void __launch_bounds__(TL::NT) k_dir2(D2Geo g, Radial<T, M> tp, Args2
     }
     __syncthreads();
     const int c = (ty + M) * W + tx * NX + TL::H;
-    T u0[NX], u1[NX], ph[NX], a0[NX], a1[NX], en[NX];
+    using TS = typename RowSum<T, !WE>::type;
+    T u0[NX], u1[NX], ph[NX], en[NX];
+    TS a0[NX], a1[NX];
 #pragma unroll
     for (int n = 0; n < NX; ++n) {
         u0[n] = s0[c + n];
         u1[n] = s1[c + n];
         ph[n] = sp[c + n];
-        a0[n] = a1[n] = en[n] = T(0);
+        a0[n] = a1[n] = TS(0);
+        en[n] = T(0);
     }
     each<0, 2 * M + 1>([&](auto rc) {
         constexpr int b = decltype(rc)::value - M, R = isqrt(M * M - b * b), RA = (R + NX - 1) / NX * NX;
@@ -188,8 +203,8 @@ __global__ void __launch_bounds__(TL::NT) k_dir2(D2Geo g, Radial<T, M> tp, Args2
         });
 #pragma unroll
         for (int n = 0; n < NX; ++n) {
-            if constexpr (R > 0) a0[n] += ra[n];
-            if constexpr (b != 0) a1[n] += T(b) * rs[n];
+            if constexpr (R > 0) a0[n] += TS(ra[n]);
+            if constexpr (b != 0) a1[n] += TS(b) * TS(rs[n]);
             if constexpr (WE) en[n] += re[n];
         }
     });
@@ -200,8 +215,8 @@ __global__ void __launch_bounds__(TL::NT) k_dir2(D2Geo g, Radial<T, M> tp, Args2
         T L[2][NX], Wn[NX];
 #pragma unroll
         for (int n = 0; n < NX; ++n) {
-            L[0][n] = ph[n] * a0[n];
-            L[1][n] = ph[n] * a1[n];
+            L[0][n] = ph[n] * T(a0[n]);
+            L[1][n] = ph[n] * T(a1[n]);
             Wn[n] = T(0.5) * ph[n] * en[n];
         }
         if constexpr (WE) {
@@ -537,11 +552,13 @@ __global__ void __launch_bounds__(TL::NT) k_nbb2(D2Geo g, Radial<T, M> tp, T dx,
     const uint32_t off = nx > 0 ? (uint32_t)(y * g.b1 + x) : 0u;
     const int c = (ty + M) * W + tx * NX + TL::H;
     const T dx2 = T(2) * dx;
-    T u0[NX], u1[NX], o0[NX], o1[NX], e0[NX], e1[NX];
+    using TS = typename RowSum<T, true>::type;
+    T u0[NX], u1[NX];
+    TS o0[NX], o1[NX], e0[NX], e1[NX];
 #pragma unroll
     for (int n = 0; n < NX; ++n) {
         u0[n] = s0[c + n]; u1[n] = s1[c + n];
-        o0[n] = o1[n] = e0[n] = e1[n] = T(0);
+        o0[n] = o1[n] = e0[n] = e1[n] = TS(0);
     }
     each<0, 2 * M + 1>([&](auto rc) {
         constexpr int b = decltype(rc)::value - M, R = isqrt(M * M - b * b), RA = (R + NX - 1) / NX * NX;
@@ -574,10 +591,10 @@ __global__ void __launch_bounds__(TL::NT) k_nbb2(D2Geo g, Radial<T, M> tp, T dx,
         });
 #pragma unroll
         for (int n = 0; n < NX; ++n) {
-            if constexpr (R > 0) o0[n] += ra[n];
-            if constexpr (b != 0) o1[n] += T(b) * rs[n];
-            e0[n] += r0[n];
-            e1[n] += r1[n];
+            if constexpr (R > 0) o0[n] += TS(ra[n]);
+            if constexpr (b != 0) o1[n] += TS(b) * TS(rs[n]);
+            e0[n] += TS(r0[n]);
+            e1[n] += TS(r1[n]);
         }
     });
     if (nx <= 0) return;
@@ -585,8 +602,8 @@ __global__ void __launch_bounds__(TL::NT) k_nbb2(D2Geo g, Radial<T, M> tp, T dx,
 #pragma unroll
     for (int n = 0; n < NX; ++n) {
         const T ph = T(0.5) * sp[c + n];
-        out[0][n] = ph * (dx * o0[n] + e0[n]);
-        out[1][n] = ph * (dx * o1[n] + e1[n]);
+        out[0][n] = ph * T(TS(dx) * o0[n] + e0[n]);
+        out[1][n] = ph * T(TS(dx) * o1[n] + e1[n]);
     }
     stn<NX>(L, 0, off, nx, out[0]);
     stn<NX>(L + g.nb, 0, off, nx, out[1]);

@@ -47,3 +47,21 @@ def test_nonlinear_force_fp32(orc, body, m):
     print(f"nonlinear {body} m={m}: {e:.2f} u", flush=True)
     assert e <= 1.5, e
     plan.close()
+
+
+@pytest.mark.parametrize("m", [2, 3, 4, 6, 8])
+def test_plate_force_fp32_against_transforms(orc, m):
+    """The unweighted plate: no less accurate than the transform chain of the
+    same plan (a tenth for two sets of roundings on 23,600 values)."""
+    from paper_2105_06055_amd import binding
+    body = (90, 131)
+    u = _field(body, 1e-3 * DX, 92)
+    plan = binding.Plan(tuple(wl._grid_len(n, m) for n in body), body, DX, m * DX, E=72e9, dtype=torch.float32)
+    Lo = orc.bb_force(orc.geom(body, DX, m * DX), orc.bb_alpha(2, 72e9, m * DX), np.ones(body), u.astype(np.float64))
+    e = {}
+    for mode in ("auto", "yfft"):
+        plan.set_lastaxis(mode)
+        e[mode] = _error(plan.force(torch.tensor(u, device="cuda")), Lo)
+    print(f"plate m={m}: direct {e['auto']:.2f} u, transforms {e['yfft']:.2f} u", flush=True)
+    assert e["auto"] <= 1.1 * e["yfft"], e
+    plan.close()
