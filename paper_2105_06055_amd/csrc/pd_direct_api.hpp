@@ -11,6 +11,10 @@ namespace pdd {
 // and a plan that qualifies (dir_plan).
 inline bool on(pd_plan p) { return p->dir_mt > 0 && p->lastaxis == PD_LASTAXIS_AUTO; }
 
+// Whether the unweighted linear operator (force without W, Verlet, solves) runs
+// them: plans whose bond sums cost less than its transforms (dir_plan).
+inline bool linear_on(pd_plan p) { return on(p) && p->dir_linear; }
+
 // Launch shapes of a qualifying plan (dir_blocks).
 void dir_launch_shape(pd_plan p);
 

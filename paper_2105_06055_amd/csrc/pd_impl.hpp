@@ -1154,6 +1154,21 @@ inline void dir_plan(pd_plan p, const std::vector<Bond>& S) {
         p->dir_a[r2] = w * p->dx[0] * p->dV;
     }
     p->dir_mt = mt;
+    // The unweighted plate's transforms carry two fields, so that at eight
+    // spacings (196 bonds; seven run the same code) its bond sums lose on large
+    // plates that fill their grid.  Measured: sums 41 (FP32) and 77 ps (FP64) per
+    // node, transforms 29 us + 22 ps and 32 us + 38 ps per point of a padded row,
+    // ~20 us more for a mixed-radix x length (force, FP64: 1000 x 1000 on 1024 x
+    // 1024 77 against 68 us, 1400 x 900 on 2048 x 1024 96 against 103 us).  At six
+    // spacings the sums win everywhere (2030 x 1010, FP64: 90 against 106 us).
+    p->dir_linear = true;
+    if (D == 2 && mt == 8 && p->kern.model == PD_BB_LINEAR && p->kern.weight == PD_WEIGHT_NONE) {
+        const bool f32 = p->dtype == PD_F32;
+        const double row = (double)p->geo.n1 * p->geo.b2;
+        const double sums = (f32 ? 41e-6 : 77e-6) * (double)p->nb;   // us
+        const double fft = (f32 ? 29.0 + 22e-6 * row : 32.0 + 38e-6 * row) + (is_pow2(p->geo.n1) ? 0.0 : 20.0);
+        p->dir_linear = sums <= fft;
+    }
     pdd::dir_launch_shape(p);
 }
 
@@ -1432,7 +1447,7 @@ pd_status force_impl(pd_plan p, const T* u, const void* weight, T* L, T* W, hipS
     bool direct = pdd::on(p);
     if (p->kern.model == PD_BB_NONLINEAR) direct = direct && pdd::nbb_on(p);
     else if (p->kern.model == PD_BB_LINEAR && D == 3) direct = direct && wk == PD_WEIGHT_NONE && !W;
-    else if (p->kern.model == PD_BB_LINEAR) direct = direct && (!W || p->energy_form == PD_ENERGY_DIRECT);
+    else if (p->kern.model == PD_BB_LINEAR) direct = W ? direct && p->energy_form == PD_ENERGY_DIRECT : pdd::linear_on(p);
     if (direct) {
         if (W && p->kern.model != PD_BB_LINEAR) return PD_EUNSUPPORTED;
         const Mem mL{L, sizeof(T) * (size_t)(p->nb * D)}, mW{W, sizeof(T) * (size_t)p->nb};
@@ -1732,7 +1747,7 @@ inline pd_status fetch_red(pd_plan p, int n, hipStream_t st, double* dst) {
 template <class T, int MODE>
 pd_status lin_apply(pd_plan p, const T* x, T* out, const T* b, hipStream_t st) {
     const int D = p->dim;
-    if (pdd::on(p)) {
+    if (pdd::linear_on(p)) {
         pdd::Eval<T> e{};
         Inputs<T> in{p, st};
         PD_TRY(in.apart(x, p->nb * D, {Mem{out, sizeof(T) * (size_t)(p->nb * D)}}));
@@ -2046,7 +2061,7 @@ pd_status verlet_impl(pd_plan p, pd_state* S, const T* b, const T* w, double dt,
     // Steps with energy output, and calls with PD_STATE_EXACT_STEPS, keep
     // (v, F) throughout.
     const bool kdk = !energy && !(S->flags & PD_STATE_EXACT_STEPS);
-    if (pdd::on(p) && (p->dim == 2 || p->kern.weight == PD_WEIGHT_NONE) &&
+    if (pdd::linear_on(p) && (p->dim == 2 || p->kern.weight == PD_WEIGHT_NONE) &&
         !(S->W && p->energy_form != PD_ENERGY_DIRECT)) {
         PD_TRY((verlet_direct<T>(p, S, b, w, dt, nsteps, energy, kdk, flag, st)));
         return verlet_end(p, flag, nsteps, st);

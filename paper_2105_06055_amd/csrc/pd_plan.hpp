@@ -86,6 +86,7 @@ struct pd_plan_s {
     // radial factors c and a with C_ij(o) = c[r^2] o_i o_j, a_i(o) = a[r^2] o_i
     int dir_mt;
     double dir_c[65], dir_a[65];
+    bool dir_linear;             // the unweighted linear calls too (pdd::linear_on)
     long dir_blocks;             // most blocks of a launch (reduction partials)
     size_t bytes;
     std::vector<ProfRec>* prof;  // non-null while pass timing is enabled
