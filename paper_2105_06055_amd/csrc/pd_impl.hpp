@@ -2139,7 +2139,9 @@ pd_status verlet_adjoint_impl(pd_plan p, const T* un, const T* unp1, const T* s,
     T* Lut = ut + n;
     const T rho = T(p->kern.rho), c1 = T(dt / (2.0 * p->kern.rho)), c2 = T(dt * dt / (2.0 * p->kern.rho));
     (void)rho;
-    if (pdd::on(p) && p->dim == 2) {
+    // (no weights: the kernel's third sum has no use, and from six spacings on
+    // two operator calls cost less)
+    if (pdd::on(p) && p->dim == 2 && (p->kern.weight == PD_WEIGHT_SCALE || p->dir_mt < 6)) {
         if (sb && p->kern.weight != PD_WEIGHT_SCALE) return PD_EUNSUPPORTED;
         const size_t vec = sizeof(T) * (size_t)n;
         const Mem r[4] = {{ub, vec}, {vb, vec}, {bb, vec}, {sb, sizeof(T) * (size_t)p->nb}};

@@ -1,11 +1,15 @@
 """Which kernels a plate at eight spacings runs (the rule by measured costs in
-dir_plan)."""
+dir_plan), and the unweighted calls at the radii on both sides of the rules."""
 import ctypes as C
 
 import numpy as np
 import pytest
 
 torch = pytest.importorskip("torch")
+
+from paper_2105_06055_amd import workloads as wl
+
+import parity
 
 pytestmark = pytest.mark.gpu
 
@@ -51,4 +55,40 @@ def test_plate_of_eight_spacings(dtype, body, fft, direct, m):
     assert names == {"dir2_m8"}, names
     tol = 1e-12 if dtype == torch.float64 else 1e-5
     assert float((out["L"] - out["E"][0]).abs().max() / out["L"].abs().max()) <= tol
+    plan.close()
+
+
+@pytest.mark.parametrize("m", [3, 5, 6, 8])
+def test_unweighted_plate_adjoint_and_energies(orc, m):
+    """The reverse steps of an unweighted plate (one kernel per half up to five
+    spacings, operator calls beyond) and a step's energies without W."""
+    from paper_2105_06055_amd import binding
+    body, dx, rho, dt, nsteps = (33, 41), 1e-3, 2440.0, 2e-8, 3
+    chi = wl.random_mask(body, 95)
+    omega = np.stack([chi] * 2)
+    omega[:, :2] = 0
+    rng = np.random.default_rng(96)
+    plan = binding.Plan(tuple(wl._grid_len(n, m) for n in body), body, dx, m * dx, E=72e9, rho=rho, chiB=chi,
+                        chiO=omega, dtype=torch.float64)
+    g, al = orc.geom(body, dx, m * dx), orc.bb_alpha(2, 72e9, m * dx)
+    u, v = rng.normal(0, 1e-6, (2,) + body) * omega, rng.normal(0, 1.0, (2,) + body) * omega
+    gu, gv = rng.normal(0, 1.0, (2,) + body), rng.normal(0, 1e-8, (2,) + body)
+    st = {"u": _dev(u), "v": _dev(v), "F": torch.zeros((2,) + body, dtype=torch.float64, device="cuda"), "step": 0}
+    us = [st["u"].clone()]
+    en = []
+    for _ in range(nsteps):
+        en.append(plan.verlet(st, dt, 1, energy=True)[0])
+        us.append(st["u"].clone())
+    ub, vb = _dev(gu), _dev(gv)
+    for k in range(nsteps - 1, -1, -1):
+        plan.verlet_adjoint(us[k], us[k + 1], ub, vb, dt)
+    uo, vo, _ = orc.verlet_adjoint(g, al, rho, omega, chi.astype(float), np.zeros((2,) + body), u, v, dt, nsteps, gu,
+                                   gv)
+    assert parity.rel_max(ub.cpu().numpy(), uo) <= 1e-11 and parity.rel_max(vb.cpu().numpy(), vo) <= 1e-11
+    # the energies of the last step from the oracle's force of its state
+    un, vn = (st[k].cpu().numpy() for k in ("u", "v"))
+    Lo, dV = orc.bb_force(g, al, chi.astype(float), un), dx * dx
+    ke, pe, sh = 0.5 * rho * np.sum(vn ** 2) * dV, -0.5 * np.sum(un * Lo) * dV, np.sum((omega * Lo) ** 2) * dV
+    ref = np.array([ke, pe, 0.0, ke + pe - dt * dt / (8 * rho) * sh])
+    assert np.max(np.abs(np.array(en[-1]) - ref)) <= 1e-11 * np.max(np.abs(ref))
     plan.close()
