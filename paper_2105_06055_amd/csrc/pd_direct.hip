@@ -257,7 +257,8 @@ pd_status dir2_force(pd_plan p, const Eval<T>& e, hipStream_t st) {
             return run2<T, M, Plate<T, M>, WE, NR>(p, A, st);
         };
         if (e.mode >= 2) return go(std::false_type{}, std::integral_constant<int, 1>{});
-        if (e.energy) return go(std::true_type{}, std::integral_constant<int, 4>{});
+        if (e.energy && e.W) return go(std::true_type{}, std::integral_constant<int, 4>{});
+        if (e.energy) return go(std::false_type{}, std::integral_constant<int, 4>{});
         if (e.W) return go(std::true_type{}, std::integral_constant<int, 0>{});
         return go(std::false_type{}, std::integral_constant<int, 0>{});
     });
