@@ -156,7 +156,8 @@ inline pd_status finish_reduction(pd_plan p, long nblk, int nr, hipStream_t st) 
         return PD_OK;
     }
     p->sum = {p->red, 1};
-    hipLaunchKernelGGL(pdk::k_reduce_final, dim3(1), dim3(256), 0, st, p->partials, nblk, nr, p->red,
+    if (nr < 1 || nr > pdk::kReduceThreads || (nr & (nr - 1)) != 0) return PD_EINVAL;
+    hipLaunchKernelGGL(pdk::k_reduce_final, dim3(1), dim3(pdk::kReduceThreads), 0, st, p->partials, nblk, nr, p->red,
                        (double*)nullptr);
     return pdh::check(hipGetLastError());
 }
