@@ -65,3 +65,39 @@ def test_plate_force_fp32_against_transforms(orc, m):
     print(f"plate m={m}: direct {e['auto']:.2f} u, transforms {e['yfft']:.2f} u", flush=True)
     assert e["auto"] <= 1.1 * e["yfft"], e
     plan.close()
+
+
+@pytest.mark.parametrize("body,m", [((31, 33), 3), ((31, 33), 5), ((31, 33), 8), ((13, 17, 15), 2), ((13, 17, 15), 3),
+                                    ((13, 17, 15), 4)])
+def test_kernel_values_fp64(body, m):
+    """The FP64 force of one displaced node is the kernel's values, C_ij(o) =
+    alpha dV o_i o_j dx^2 / (r dx)^3 with alpha as the plan has it: a factor of
+    r^2 rounded once and at most two roundings more (its products with o), 3
+    units of 2^-53."""
+    from decimal import Decimal, getcontext
+
+    from paper_2105_06055_amd import binding
+    getcontext().prec = 40
+    dim, dx = len(body), 1.1e-3
+    plan = binding.Plan(tuple(wl._grid_len(n, m) for n in body), body, dx, m * dx, E=72e9, dtype=torch.float64)
+    at = tuple(n // 2 for n in body)
+    u = torch.zeros((dim,) + body, dtype=torch.float64, device="cuda")
+    u[(0,) + at] = 1.0
+    L = plan.force(u).cpu().numpy()
+    worst, h, alpha = 0.0, Decimal(dx), Decimal(plan.info["alpha"])
+    for o in np.ndindex(*[2 * m + 1] * dim):
+        o = tuple(q - m for q in o)[::-1]   # (x, y, z)
+        r2 = sum(q * q for q in o)
+        if not 0 < r2 <= m * m:
+            continue
+        node = tuple(a - q for a, q in zip(at, o[::-1]))   # the node whose bond o ends at the displaced one
+        for d in range(dim):
+            want = alpha * h ** dim * o[0] * o[d] * h * h / (Decimal(r2).sqrt() * h) ** 3
+            got = Decimal(float(L[(d,) + node]))
+            if want == 0:
+                assert got == 0
+            else:
+                worst = max(worst, float(abs(got / want - 1)) * 2.0 ** 53)
+    print(f"kernel values {body} m={m}: {worst:.2f} units of 2^-53", flush=True)
+    assert worst <= 3.0, worst
+    plan.close()
