@@ -37,6 +37,8 @@ pd_status pd_test_conv(pd_plan plan, const void* x, const int* shift, int parity
  *                            and unweighted bond-based chains; otherwise as
  *                            PD_LASTAXIS_YFFT.
  *                            2D: as PD_LASTAXIS_YFFT
+ *   PD_LASTAXIS_TRANSFORM    the choice of PD_LASTAXIS_AUTO without the direct
+ *                            sums, that of plans which do not qualify for them
  *   PD_LASTAXIS_YFFT         transforms along x and y (3D), then the direct line
  *                            correlation along the last axis when the horizon
  *                            spans at most 4 spacings there, else the
@@ -48,7 +50,13 @@ pd_status pd_test_conv(pd_plan plan, const void* x, const int* shift, int parity
  *   PD_LASTAXIS_FFT_GENERIC  transform form, runtime-length kernel only
  * All compute the same correlation; results agree to rounding.  PD_EINVAL
  * for a null plan or an unknown mode. */
-enum { PD_LASTAXIS_AUTO = 0, PD_LASTAXIS_FFT = 1, PD_LASTAXIS_FFT_GENERIC = 2, PD_LASTAXIS_YFFT = 3 };
+enum {
+    PD_LASTAXIS_AUTO = 0,
+    PD_LASTAXIS_FFT = 1,
+    PD_LASTAXIS_FFT_GENERIC = 2,
+    PD_LASTAXIS_YFFT = 3,
+    PD_LASTAXIS_TRANSFORM = 4
+};
 pd_status pd_test_set_lastaxis(pd_plan plan, int mode);
 
 /* How the strain energy density W of the weighted bond-based solid is

@@ -302,11 +302,12 @@ class Plan:
         _check(lib().pd_test_conv(self._h, _ptr(x), sh, int(parity), _ptr(out), _stream()), "pd_test_conv")
         return out
 
-    LASTAXIS = {"auto": 0, "fft": 1, "fft_generic": 2, "yfft": 3}
+    LASTAXIS = {"auto": 0, "fft": 1, "fft_generic": 2, "yfft": 3, "transform": 4}
 
     def set_lastaxis(self, mode="auto"):
         """Kernel choice (A/B tests): 'auto' (direct horizon sums where they
         apply, else in 3D the direct (y, z) correlation where that applies),
+        'transform' (the same without the direct sums),
         'yfft' (transform along x and, in 3D, y, direct line correlation
         along the last axis), 'fft' (transforms on
         every axis, spectral multiply, specialised where it applies) or

@@ -215,7 +215,7 @@ pd_status pd_test_conv(pd_plan p, const void* x, const int* shift, int parity, v
 }
 
 pd_status pd_test_set_lastaxis(pd_plan p, int mode) {
-    if (!p || mode < PD_LASTAXIS_AUTO || mode > PD_LASTAXIS_YFFT) return PD_EINVAL;
+    if (!p || mode < PD_LASTAXIS_AUTO || mode > PD_LASTAXIS_TRANSFORM) return PD_EINVAL;
     p->lastaxis = mode;
     if (p->sub32) p->sub32->lastaxis = mode;
     return PD_OK;

@@ -329,7 +329,7 @@ pd_status launch_lastmul(pd_plan p, const Lines& ln, const M& mul, cx<T>* S, con
     constexpr bool direct_ok = !M::RT_ODD && !is_nonlocal<M>::value && !(sizeof(T) == 8 && M::NIN + M::NOUT > 16);
     int path = 2;   // 0 direct, 1 specialised FFT, 2 generic FFT, 3 specialised FFT on short lines
     if constexpr (direct_ok) {
-        if ((p->lastaxis == PD_LASTAXIS_AUTO || p->lastaxis == PD_LASTAXIS_YFFT) && taps_d && ntap >= 2 && ntap <= 5)
+        if ((default_lines(p) || p->lastaxis == PD_LASTAXIS_YFFT) && taps_d && ntap >= 2 && ntap <= 5)
             path = 0;
     }
     if constexpr (!M::RT_ODD) {
@@ -577,7 +577,7 @@ template <class T, class M>
 bool use_yz(pd_plan p) {
     if constexpr (!yz_capable<T, M>()) return false;
     else {
-        if (p->geo.dim != 3 || !p->taps_yz || p->lastaxis != PD_LASTAXIS_AUTO) return false;
+        if (p->geo.dim != 3 || !p->taps_yz || !default_lines(p)) return false;
         switch (p->yz_mt) {
             case 2: return yz_fits<T, M, 2>();
             case 3: return yz_fits<T, M, 3>();
@@ -1515,7 +1515,7 @@ pd_status force_impl(pd_plan p, const T* u, const void* weight, T* L, T* W, hipS
                 // the outputs exceed the registers of two waves and spill),
                 // written after the inputs
                 constexpr int NI = MulNBB<T, 2>::NIN, NO = MulNBB<T, 2>::NOUT;
-                if (p->lastaxis == PD_LASTAXIS_AUTO && p->saf_cap >= NI + NO) {
+                if (default_lines(p) && p->saf_cap >= NI + NO) {
                     PD_TRY(launch_xfwd<T>(p, gg, SAp<T>(p), st));
                     PD_TRY((nbb2_lines_from<T, 0>(p, NI, st)));
                     return launch_xinv<T>(p, ff, SAp<T>(p) + (long)NI * p->geo.saf, st);

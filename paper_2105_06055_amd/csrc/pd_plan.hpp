@@ -94,6 +94,12 @@ struct pd_plan_s {
     pd_plan_s* parent;           // set on sub32
 };
 
+// Whether the transform chains of a plan take their default forms (the plans
+// without direct sums, and PD_LASTAXIS_TRANSFORM on the others).
+inline bool default_lines(pd_plan p) {
+    return p->lastaxis == PD_LASTAXIS_AUTO || p->lastaxis == PD_LASTAXIS_TRANSFORM;
+}
+
 namespace pdh {
 
 pd_status check(hipError_t e);
