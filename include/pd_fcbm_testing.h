@@ -59,6 +59,12 @@ enum {
 };
 pd_status pd_test_set_lastaxis(pd_plan plan, int mode);
 
+/* Planes per block of the 3D direct sums (every later call on `plan` and on
+ * its FP32 operator): planes >= 1, or 0 for the default rule.  PD_EINVAL for a
+ * null plan or a negative number; a call whose reductions then have more
+ * blocks than the plan has room for returns PD_EINVAL. */
+pd_status pd_test_set_planes(pd_plan plan, int planes);
+
 /* How the strain energy density W of the weighted bond-based solid is
  * evaluated (pd_force's W_out and the energy failure rule of
  * pd_verlet_step), for A/B tests:

@@ -74,7 +74,8 @@ SOLVE_MIXED, SOLVE_PRECOND = 1, 2
 
 EXPORTS = ["pd_plan_create", "pd_plan_destroy", "pd_plan_query", "pd_force", "pd_force_adjoint",
            "pd_verlet_step", "pd_verlet_adjoint", "pd_static_solve", "pd_static_solve_noalloc", "pd_damage_index",
-           "pd_status_str", "pd_test_conv", "pd_test_set_lastaxis", "pd_test_set_energy_form"]
+           "pd_status_str", "pd_test_conv", "pd_test_set_lastaxis", "pd_test_set_energy_form",
+           "pd_test_set_planes"]
 
 _lib = None
 
@@ -109,6 +110,7 @@ def lib():
     L.pd_test_conv.argtypes = [vp, vp, C.POINTER(C.c_int), C.c_int, vp, vp]
     L.pd_test_set_lastaxis.argtypes = [vp, C.c_int]
     L.pd_test_set_energy_form.argtypes = [vp, C.c_int]
+    L.pd_test_set_planes.argtypes = [vp, C.c_int]
     for name in EXPORTS:
         if name not in ("pd_plan_destroy", "pd_status_str"):
             getattr(L, name).restype = C.c_int
@@ -313,6 +315,10 @@ class Plan:
         every axis, spectral multiply, specialised where it applies) or
         'fft_generic'."""
         _check(lib().pd_test_set_lastaxis(self._h, self.LASTAXIS[mode]), "pd_test_set_lastaxis")
+
+    def set_planes(self, planes=0):
+        """Planes per block of the 3D direct sums (tests); 0: the default rule."""
+        _check(lib().pd_test_set_planes(self._h, int(planes)), "pd_test_set_planes")
 
     ENERGY_FORMS = {"direct": 0, "convolution": 1}
 

@@ -46,7 +46,7 @@ pd_status launch3(pd_plan p, const D3In<T>& in, double ka, T g0, const Ep& ep, c
         d.b1 = g.b1; d.b2 = g.b2; d.b3 = g.b3;
         d.ntx = (g.b1 + S::TX - 1) / S::TX;
         d.nty = (g.b2 + S::TY - 1) / S::TY;
-        d.zc = chunk3(g, MT, S::TX, S::TY, S3::RES, S3::LAT);
+        d.zc = p->dir_planes > 0 ? std::min(p->dir_planes, g.b3) : chunk3(g, MT, S::TX, S::TY, S3::RES, S3::LAT);
         d.nzc = (g.b3 + d.zc - 1) / d.zc;
         const long nblk = (long)d.ntx * d.nty * d.nzc;
         if (nblk > 0x7fffffffL) return PD_EUNSUPPORTED;

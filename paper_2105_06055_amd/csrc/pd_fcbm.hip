@@ -221,6 +221,13 @@ pd_status pd_test_set_lastaxis(pd_plan p, int mode) {
     return PD_OK;
 }
 
+pd_status pd_test_set_planes(pd_plan p, int planes) {
+    if (!p || planes < 0) return PD_EINVAL;
+    p->dir_planes = planes;
+    if (p->sub32) p->sub32->dir_planes = planes;
+    return PD_OK;
+}
+
 pd_status pd_test_set_energy_form(pd_plan p, int form) {
     if (!p || form < PD_ENERGY_DIRECT || form > PD_ENERGY_CONVOLUTION) return PD_EINVAL;
     p->energy_form = form;

@@ -88,6 +88,7 @@ struct pd_plan_s {
     double dir_c[65], dir_a[65];
     bool dir_linear;             // the unweighted linear calls too (pdd::linear_on)
     long dir_blocks;             // most blocks of a launch (reduction partials)
+    int dir_planes;              // planes per block in 3D (test mode; 0: chunk3)
     size_t bytes;
     std::vector<ProfRec>* prof;  // non-null while pass timing is enabled
     pd_plan_s* sub32;            // FP32 operator for the mixed solve
