@@ -193,8 +193,10 @@ typedef struct {
  * adjoints). */
 #define PD_STATE_EXACT_STEPS 1
 /* pd_state.flags: the call does not wait for its steps and does not report
- * PD_ENUMERIC (for callers that replay steps which an earlier call has
- * checked). Without energy_out the call then only enqueues work. */
+ * PD_ENUMERIC for their forces and velocities (for callers that replay steps
+ * which an earlier call has checked): it only enqueues work.  With energy_out
+ * it still waits for every step's energies and returns PD_ENUMERIC where one
+ * is not finite. */
 #define PD_STATE_NO_STATUS 2
 
 /* Advance nsteps embedded-constraint velocity-Verlet steps (Eq. 67, 83-84):
