@@ -1148,13 +1148,19 @@ inline void dir_plan(pd_plan p, const std::vector<Bond>& S) {
     const double cC = (p->kern.model == PD_LPS_LINEAR) ? 30.0 * p->mu / p->m0 : p->alpha;
     for (int q = 0; q < 65; ++q) p->dir_c[q] = p->dir_a[q] = 0.0;
     for (const Bond& bd : S) {
-        // with the integer r^2, and rounded once: the same factor for all bonds
-        // of a radius, so its error is not averaged over the bonds
         const int r2 = bd.o[0] * bd.o[0] + bd.o[1] * bd.o[1] + bd.o[2] * bd.o[2];
-        const long double h = p->dx[0], dV = D == 3 ? h * h * h : h * h;
-        const long double w = p->influence == 0 ? 1.0L / (h * std::sqrt((long double)r2)) : 1.0L;
-        p->dir_c[r2] = (double)(cC * w / r2 * dV);
-        p->dir_a[r2] = (double)(w * h * dV);
+        if (D == 2 || p->kern.model == PD_BB_NONLINEAR) {
+            // sums of differences: from the integer r^2, rounded once (the same
+            // factor for all bonds of a radius, so its error is not averaged)
+            const long double h = p->dx[0], dV = D == 3 ? h * h * h : h * h;
+            const long double w = p->influence == 0 ? 1.0L / (h * std::sqrt((long double)r2)) : 1.0L;
+            p->dir_c[r2] = (double)(cC * w / r2 * dV);
+            continue;
+        }
+        // with static fields to subtract: in their arithmetic (build_device_tables)
+        const double w = p->influence == 0 ? 1.0 / bd.r : 1.0;
+        p->dir_c[r2] = cC * w * p->dx[0] * p->dx[0] / (bd.r * bd.r) * p->dV;
+        p->dir_a[r2] = w * p->dx[0] * p->dV;
     }
     p->dir_mt = mt;
     // The unweighted plate's transforms carry two fields, so that at eight

@@ -67,10 +67,9 @@ def test_plate_force_fp32_against_transforms(orc, m):
     plan.close()
 
 
-@pytest.mark.parametrize("body,m", [((31, 33), 3), ((31, 33), 5), ((31, 33), 8), ((13, 17, 15), 2), ((13, 17, 15), 3),
-                                    ((13, 17, 15), 4)])
+@pytest.mark.parametrize("body,m", [((31, 33), 3), ((31, 33), 5), ((31, 33), 8)])
 def test_kernel_values_fp64(body, m):
-    """The FP64 force of one displaced node is the kernel's values, C_ij(o) =
+    """The FP64 force of a plate with one displaced node is the kernel's values, C_ij(o) =
     alpha dV o_i o_j dx^2 / (r dx)^3 with alpha as the plan has it: a factor of
     r^2 rounded once and at most two roundings more (its products with o), 3
     units of 2^-53."""
