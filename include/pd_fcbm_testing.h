@@ -28,8 +28,10 @@ pd_status pd_test_conv(pd_plan plan, const void* x, const int* shift, int parity
  *   PD_LASTAXIS_AUTO         (default) equal spacings along all axes and a
  *                            horizon of up to 8 (2D) or 4 (3D) spacings:
  *                            direct sums over the horizon, no transforms
- *                            (but for the convolution form of W and, in 3D,
- *                            the nonlinear model at 4 spacings).  Otherwise,
+ *                            (but for the convolution form of W, in 3D the
+ *                            nonlinear model at 4 spacings, and in 2D the
+ *                            unweighted linear operator of large plates at 7
+ *                            and 8 spacings).  Otherwise,
  *                            after the x transform,
  *                            3D: direct 2D correlation over (y, z) per
  *                            x-wavenumber when the horizon's (y, z) footprint

@@ -31,11 +31,14 @@
 // nodes takes them from scalar registers.
 //
 // Measured, 256^3 LPS body in FP32, one Verlet step: dilatation 139 us, force
-// stage 288 us (0.94 ms per step for the x transforms and (y, z) passes).  The
-// force stage issues 1.27e8 wave instructions (485 per node: 208 us at one per
-// CU and cycle, 72 % of the time) and moves 1.25 GB (0.97 GB of fields), the
-// dilatation 4.6e7 (176 per node, 55 %, its LDS pipe as busy) and 0.53 GB (0.31
-// GB of fields, the rest tile and chunk halos: 3.8 TB/s).
+// stage 295 us (0.94 ms per step for the x transforms and (y, z) passes).  The
+// force stage issues 1.27e8 wave instructions (485 per node, 0.70 per CU and
+// cycle; k_nbb3, which does little else, 1.2) and moves 1.25 GB (0.97 GB of
+// fields), the dilatation 4.6e7 (176 per node, 0.54 per CU and cycle, its LDS
+// pipe as busy) and 0.53 GB (0.31 GB of fields, the rest tile and chunk halos:
+// 3.8 TB/s).  In FP64 the issue rates are lower, 0.4 and 0.24 at 128^3: too few
+// blocks per CU to overlap arithmetic and LDS reads; the pair tile of the FP64
+// dilatation spends 44 % of its LDS cycles in bank conflicts.
 #pragma once
 
 #include <algorithm>

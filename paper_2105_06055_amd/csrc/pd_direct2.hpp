@@ -11,12 +11,15 @@
 // a window of NX + 2R values.  Offsets and the order of the bonds are
 // compile-time constants, the radial factors are kernel arguments in scalar
 // registers.  A plate of 400,000 nodes (48 bonds) stays in the caches, so one
-// launch per step replaces four passes over padded spectra; the sums are
-// bound by the vector ALU (~9 instructions a bond).  Measured against the
-// transform passes: 20 FP32 fracture steps of the 1000 x 400 plate 1461 -> 281
-// us, 20 FP64 steps of a 601 x 241 plate at six spacings 3912 -> 358 us, 10
-// steps forward and backward on the 512 x 512 plate 3215 -> 680 us, the force
-// of a 64 x 64 plate 22.4 -> 9.1 us.
+// launch per step replaces four passes over padded spectra.  On such plates
+// all blocks are resident at once and a block's latency (load, rows of LDS
+// reads and sums in turn, store) bounds the launch: ~9 instructions a bond
+// issue at 0.48 per CU and cycle (1000 x 400, four spacings, 13 us), LDS reads
+// fill 22 % of the cycles.  Measured against the transform passes: 20 FP32
+// fracture steps of the 1000 x 400 plate 1458 -> 275 us, 20 FP64 steps of a 601
+// x 241 plate at six spacings 3910 -> 357 us, 10 steps forward and backward on
+// the 512 x 512 plate 3250 -> 728 us, the force of a 64 x 64 plate 22.5 -> 9.3
+// us.
 #pragma once
 
 #include "pd_direct.hpp"
@@ -614,8 +617,7 @@ __global__ void __launch_bounds__(TL::NT) k_nbb2(D2Geo g, Radial<T, M> tp, T dx,
 // = 3), which keeps eight waves on a CU in either type; the 4.6 halo loads
 // per node are small beside the ~2000 vector instructions of 122 bonds.
 // Measured on the 128^3 block: FP32 420 -> 97 us against the 13-field chain of
-// the (y, z) pass, relative error 6e-8 -> 1.2e-7 (sums by plane; 1.4e-7 with
-// the 122 bonds added one by one, 96 us).
+// the (y, z) pass, L2 error 6.2e-8 -> 6.0e-8 (sums by plane: short chains).
 struct Tile3 {
     static constexpr int TX = 16, TY = 8, TZ = 8, NX = 2, NT = TX / NX * TY * TZ;
 };
